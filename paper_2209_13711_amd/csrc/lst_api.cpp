@@ -53,6 +53,9 @@ struct lst_ctx {
     size_t stage_cap = 0;   // bytes
     hipEvent_t stage_done = nullptr;
     bool stage_pending = false;
+    // pinned results: the getters' kernels store a header and their rows here
+    char *res_host = nullptr;
+    size_t res_cap = 0;     // bytes
     hipStream_t cap_stream = nullptr;
     hipGraphExec_t graph = nullptr;
     Tuning tune{};
@@ -160,6 +163,8 @@ size_t carve(lst_ctx *c, char *base, const lst_caps &k, EvDev &E, void **zero_ba
     E.cap_keys = (int32_t)keys;
     E.desc = cv.take<int32_t>(D_COUNT);
     E.bar = cv.take<uint32_t>(33 * 64);   // 33 barrier counters, one 256-byte line each
+    E.rd_cnt = cv.take<uint32_t>(PACK_BLOCKS);
+    E.rd_part = cv.take<uint64_t>(count_part_size(c->n_mod, k.events));
     E.cap_hits = k.hits;
     const int64_t caps[OT_COUNT] = {k.md, k.seg, k.t3, k.t5};
     size_t span[OT_COUNT];
@@ -376,6 +381,7 @@ void lst_destroy(lst_ctx *c)
     if (c->stage_done) (void)hipEventSynchronize(c->stage_done);
     if (c->stage_done) (void)hipEventDestroy(c->stage_done);
     if (c->stage_host) (void)hipHostFree(c->stage_host);
+    if (c->res_host) (void)hipHostFree(c->res_host);
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->geo_dev) (void)hipFree(c->geo_dev);
     for (float *p : c->mlp_dev)
@@ -556,6 +562,19 @@ int lst_arena_bytes(const lst_ctx *cc, const lst_caps *caps, size_t *bytes)
     return LST_OK;
 }
 
+// room for `body` bytes of results after the header (nothing may be writing there)
+constexpr size_t RES_BODY = (sizeof(ReadHdr) + 255) & ~(size_t)255, RES_FIRST = 1 << 20;
+static int res_reserve(lst_ctx *c, size_t body)
+{
+    if (c->res_cap >= RES_BODY + body) return LST_OK;
+    if (c->res_host) HIPCHK(c, hipHostFree(c->res_host));
+    c->res_host = nullptr;
+    c->res_cap = 0;
+    HIPCHK(c, hipHostMalloc((void **)&c->res_host, RES_BODY + body, hipHostMallocDefault));
+    c->res_cap = RES_BODY + body;
+    return LST_OK;
+}
+
 int lst_attach_arena(lst_ctx *c, void *dev_ptr, size_t bytes, const lst_caps *caps)
 {
     if (!c) return LST_E_INVALID;
@@ -579,6 +598,9 @@ int lst_attach_arena(lst_ctx *c, void *dev_ptr, size_t bytes, const lst_caps *ca
         c->stage_cap = want;
     }
     if (!c->stage_done) HIPCHK(c, hipEventCreateWithFlags(&c->stage_done, hipEventDisableTiming));
+    // a dozen times the kept quintuplets of a PU200-like event; a getter whose
+    // rows do not fit grows it
+    if ((rc = res_reserve(c, RES_FIRST))) return rc;
     c->arena = (char *)dev_ptr;
     c->arena_bytes = bytes;
     c->caps = *caps;
@@ -1301,13 +1323,6 @@ struct ShardCounts {
     uint32_t rc[OT_COUNT];
     uint32_t n(int t, int s) const { return std::min(gc[gc_shard(t, s)], rc[t]); }
     size_t span(int t) const { return (size_t)rc[t] * NSH; }
-    // capacity that would have let every shard fit
-    int64_t required(int t) const
-    {
-        uint32_t m = 0;
-        for (int s = 0; s < NSH; ++s) m = std::max(m, gc[gc_shard(t, s)]);
-        return (int64_t)m * NSH;
-    }
     int64_t stored(int t) const
     {
         int64_t k = 0;
@@ -1340,20 +1355,23 @@ static int check_fault(lst_ctx *c, uint32_t err)
                 err);
 }
 
-// Per-event statistics, reduced on the host from the device arrays (the
-// reporting path; the stage kernels carry no statistics atomics).
-static int compute_counts(lst_ctx *c)
+// Per-event statistics, summed on the device (the reporting path; the stage
+// kernels carry no statistics atomics).
+static int compute_counts(lst_ctx *c, hipStream_t stream)
 {
     const EvDev &E = c->E;
-    const int n_ev = c->n_events, nm = c->n_mod;
-    ShardCounts S;
-    int rc = read_shards(c, S);
+    const int n_ev = c->n_events;
+    int rc = res_reserve(c, std::max(n_ev * sizeof(EventSums), RES_FIRST));
     if (rc) return rc;
+    ReadHdr *h = (ReadHdr *)c->res_host;
+    const EventSums *sums = (const EventSums *)(c->res_host + RES_BODY);
+    HIPCHK(c, launch_read_counts(E, c->M, n_ev, c->stage, h, (EventSums *)sums, stream));
+    if ((rc = sync_stream(c, stream))) return rc;
     c->counts.assign(n_ev, lst_counts{});
     for (int e = 0; e < n_ev; ++e) {
         c->counts[e].n_hits = c->hit_off[e + 1] - c->hit_off[e];
-        c->counts[e].overflow_mask = (int32_t)S.gc[GC_OVERFLOW];
-        c->counts[e].error_flags = (int32_t)S.gc[GC_ERROR];
+        c->counts[e].overflow_mask = (int32_t)h->overflow;
+        c->counts[e].error_flags = (int32_t)h->error;
         c->counts[e].mlp_fallback = c->fallback ? 1 : 0;
     }
     if (capped(c) && c->stage >= 3) {
@@ -1364,70 +1382,38 @@ static int compute_counts(lst_ctx *c)
             for (int t = 0; t < OT_COUNT; ++t)
                 c->counts[e].dropped[t] = c->stage >= 3 + t ? nd[(size_t)e * OT_COUNT + t] : 0;
     }
-    if (S.gc[GC_OVERFLOW]) {
-        // arrays are incomplete: report the batch-wide requirement instead
+    if (h->overflow) {
+        // arrays are incomplete: report the batch-wide requirement instead,
+        // the capacity that would have let every shard fit
+        int64_t need[OT_COUNT];
+        for (int t = 0; t < OT_COUNT; ++t)
+            need[t] = (int64_t)*std::max_element(h->shard[t], h->shard[t] + NSH) * NSH;
         for (auto &k : c->counts) {
-            k.n_md = S.required(OT_MD);
-            k.n_seg = S.required(OT_SEG);
-            k.n_t3 = S.required(OT_T3);
-            k.n_t5 = S.required(OT_T5);
+            k.n_md = need[OT_MD];
+            k.n_seg = need[OT_SEG];
+            k.n_t3 = need[OT_T3];
+            k.n_t5 = need[OT_T5];
         }
         c->counts_valid = true;
         return LST_OK;
     }
-    const size_t slots = (size_t)n_ev * nm;
-    std::vector<uint32_t> boff;
-    std::vector<int32_t> mds, mdc, mslot, ss, sc, so, ts, tc, tcc, t50;
-    std::vector<uint8_t> keep;
-    const size_t nmd = S.span(OT_MD), nseg = S.span(OT_SEG), nt3 = S.span(OT_T3), nt5 = S.span(OT_T5);
-    if ((rc = d2h(c, boff, E.boff, 2 * slots + 1)) || (rc = d2h(c, mds, E.md_start, slots)) ||
-        (rc = d2h(c, mdc, E.md_cnt, slots)))
-        return rc;
-    if (c->stage >= 3 && (rc = d2h(c, mslot, E.md_slot, nmd))) return rc;
-    if (c->stage >= 4 && ((rc = d2h(c, ss, E.seg_start, nmd)) || (rc = d2h(c, sc, E.seg_cnt, nmd)) ||
-                          (rc = d2h(c, so, E.seg_out, nseg))))
-        return rc;
-    if (c->stage >= 5 && ((rc = d2h(c, ts, E.t3_start, nmd)) || (rc = d2h(c, tc, E.t3_cnt, nmd)) ||
-                          (rc = d2h(c, tcc, E.t3_c, nt3))))
-        return rc;
-    if (c->stage >= 6 && (rc = d2h(c, t50, E.t5_md0, nt5))) return rc;
-    if (c->stage >= 7 && (rc = d2h(c, keep, E.t5_keep, nt5))) return rc;
     for (int e = 0; e < n_ev; ++e) {
         lst_counts &k = c->counts[e];
-        for (int m = 0; m < nm; ++m) {
-            const size_t sl = (size_t)e * nm + m;
-            const int64_t nlo = boff[2 * sl + 1] - boff[2 * sl];
-            const int64_t nup = boff[2 * sl + 2] - boff[2 * sl + 1];
-            k.cand_md += nlo * nup;
-            if (c->stage < 3 || mdc[sl] == 0) continue;
-            k.n_md += mdc[sl];
-            int64_t outer = 0;
-            for (int32_t q = c->map_ptr[m]; q < c->map_ptr[m + 1]; ++q)
-                outer += mdc[(size_t)e * nm + c->map_col[q]];
-            k.cand_seg += (int64_t)mdc[sl] * outer;
-            if (c->stage < 4) continue;
-            for (int32_t a = mds[sl]; a < mds[sl] + mdc[sl]; ++a) {
-                k.n_seg += sc[a];
-                for (int32_t s1 = ss[a]; s1 < ss[a] + sc[a]; ++s1) k.cand_t3 += sc[so[s1]];
-                if (c->stage < 5) continue;
-                k.n_t3 += tc[a];
-                for (int32_t t1 = ts[a]; t1 < ts[a] + tc[a]; ++t1) k.cand_t5 += tc[tcc[t1]];
-            }
-        }
-    }
-    std::vector<uint8_t> clean;
-    if (c->stage >= 8 && (rc = d2h(c, clean, E.t5_clean, nt5))) return rc;
-    if (c->stage >= 6) {
-        for (int s = 0; s < NSH; ++s)
-            for (uint32_t q = 0; q < S.n(OT_T5, s); ++q) {
-                const size_t t = (size_t)s * S.rc[OT_T5] + q;
-                const int e = mslot[t50[t]] / nm;
-                c->counts[e].n_t5++;
-                if (c->stage >= 7) c->counts[e].n_t5_kept += keep[t];
-                if (c->stage >= 8) c->counts[e].n_tc += clean[t];
-            }
+        const auto &q = sums[e].sum;
+        k.cand_md = (int64_t)q[0][0];
+        k.n_md = (int64_t)q[0][1];
+        k.cand_seg = (int64_t)q[0][2];
+        k.n_seg = (int64_t)q[1][0];
+        k.cand_t3 = (int64_t)q[1][1];
+        k.n_t3 = (int64_t)q[2][0];
+        k.cand_t5 = (int64_t)q[2][1];
+        k.n_t5 = (int64_t)q[3][0];
+        k.n_t5_kept = (int64_t)q[3][1];
+        k.n_tc = (int64_t)q[3][2];
     }
     if (c->stage >= 8) {
+        ShardCounts S;
+        if ((rc = read_shards(c, S))) return rc;
         const uint32_t n5 = std::min<uint32_t>(S.gc[GC_PX5], (uint32_t)E.cap_pxc);
         const uint32_t n3 = std::min<uint32_t>(S.gc[GC_PX3], (uint32_t)E.cap_pxc);
         const int64_t n_sd = c->sd_off[n_ev];
@@ -1456,6 +1442,37 @@ static int compute_counts(lst_ctx *c)
     return LST_OK;
 }
 
+// One event's objects of a type (their hit tuples, or `field`) as rows in
+// the pinned result buffer, in array order; *n_rows of row_bytes each.
+static int pack_rows(lst_ctx *c, int type, int32_t event, bool kept_only, const void *field,
+                     size_t row_bytes, int64_t *n_rows, void *stream)
+{
+    HIPCHK(c, hipSetDevice(c->device));
+    hipStream_t s = (hipStream_t)stream;
+    int rc = c->res_host ? LST_OK : res_reserve(c, RES_FIRST);
+    if (rc) return rc;
+    for (;;) {
+        ReadHdr *h = (ReadHdr *)c->res_host;
+        PackArgs A{};
+        A.lo_slot = event * c->n_mod;
+        A.hi_slot = A.lo_slot + c->n_mod;
+        A.whole_batch = c->n_events == 1;
+        A.kept_only = kept_only;
+        A.field = field;
+        A.hdr = h;
+        A.out = c->res_host + RES_BODY;
+        A.cap_rows = (uint32_t)std::min<size_t>((c->res_cap - RES_BODY) / row_bytes, 0xffffffffu);
+        if (field) HIPCHK(c, launch_pack_field(c->E, type, (int)row_bytes, A, s));
+        else HIPCHK(c, launch_pack_tuples(c->E, type, A, s));
+        if ((rc = sync_stream(c, stream)) || (rc = check_fault(c, h->error))) return rc;
+        if (h->overflow) return fail(c, LST_E_CAPACITY, "capacity overflow (mask %u)", h->overflow);
+        *n_rows = h->rows;
+        if (h->rows <= A.cap_rows) return LST_OK;
+        // more rows than the buffer holds: grow it to the need and pack again
+        if ((rc = res_reserve(c, (size_t)h->rows * row_bytes))) return rc;
+    }
+}
+
 extern "C" {
 
 int lst_get_counts(lst_ctx *c, int32_t event, lst_counts *out, void *stream)
@@ -1463,9 +1480,9 @@ int lst_get_counts(lst_ctx *c, int32_t event, lst_counts *out, void *stream)
     if (!c || !out) return LST_E_INVALID;
     if (c->stage < 2) return fail(c, LST_E_STATE, "no chain has run");
     if (event < 0 || event >= c->n_events) return fail(c, LST_E_INVALID, "event %d", event);
-    int rc = sync_stream(c, stream);
+    HIPCHK(c, hipSetDevice(c->device));
+    int rc = c->counts_valid ? sync_stream(c, stream) : compute_counts(c, (hipStream_t)stream);
     if (rc) return rc;
-    if (!c->counts_valid && (rc = compute_counts(c))) return rc;
     *out = c->counts[event];
     if ((rc = check_fault(c, (uint32_t)out->error_flags))) return rc;
     if (out->overflow_mask)
@@ -1499,68 +1516,17 @@ int lst_get_objects(lst_ctx *c, int32_t event, int32_t kind, int32_t *out, int64
     if (event < 0 || event >= c->n_events) return fail(c, LST_E_INVALID, "event %d", event);
     const int need = kind == LST_MD ? 3 : kind == LST_SEG ? 4 : kind == LST_T3 ? 5 : kind == LST_T5 ? 6 : 7;
     if (c->stage < need) return fail(c, LST_E_STATE, "stage for kind %d has not run", kind);
-    int rc = sync_stream(c, stream);
-    if (rc) return rc;
-    const EvDev &E = c->E;
-    ShardCounts S;
-    if ((rc = read_shards(c, S)) || (rc = check_fault(c, S.gc[GC_ERROR]))) return rc;
-    if (S.gc[GC_OVERFLOW])
-        return fail(c, LST_E_CAPACITY, "capacity overflow (mask %u)", S.gc[GC_OVERFLOW]);
-    const size_t n_sorted = S.gc[GC_N_SORTED];
-    const size_t nmd = S.span(OT_MD);
-    std::vector<int32_t> sorig, hlo, hup, slot;
-    if ((rc = sorted_orig(c, sorig, n_sorted)) || (rc = d2h(c, hlo, E.md_hlo, nmd)) ||
-        (rc = d2h(c, hup, E.md_hup, nmd)) || (rc = d2h(c, slot, E.md_slot, nmd)))
-        return rc;
-    const int lo_slot = event * c->n_mod, hi_slot = (event + 1) * c->n_mod;
-    auto in_ev = [&](int32_t md) { return slot[md] >= lo_slot && slot[md] < hi_slot; };
-    auto put = [&](std::vector<int32_t> &tup, int32_t md) {
-        tup.push_back(sorig[hlo[md]]);
-        tup.push_back(sorig[hup[md]]);
-    };
-    std::vector<int32_t> tup;
-    int width = 2;
     const int type = kind == LST_MD ? OT_MD : kind == LST_SEG ? OT_SEG : kind == LST_T3 ? OT_T3 : OT_T5;
-    const size_t sp = S.span(type);
-    std::vector<int32_t> a, b, d, e4, f5;
-    std::vector<uint8_t> keep;
-    if (kind == LST_SEG) {
-        width = 4;
-        if ((rc = d2h(c, a, E.seg_in, sp)) || (rc = d2h(c, b, E.seg_out, sp))) return rc;
-    } else if (kind == LST_T3) {
-        width = 6;
-        if ((rc = d2h(c, a, E.t3_a, sp)) || (rc = d2h(c, b, E.t3_b, sp)) || (rc = d2h(c, d, E.t3_c, sp)))
-            return rc;
-    } else if (kind >= LST_T5) {
-        width = 10;
-        if ((rc = d2h(c, a, E.t5_md0, sp)) || (rc = d2h(c, b, E.t5_md1, sp)) ||
-            (rc = d2h(c, d, E.t5_md2, sp)) || (rc = d2h(c, e4, E.t5_md3, sp)) ||
-            (rc = d2h(c, f5, E.t5_md4, sp)) || (rc = d2h(c, keep, E.t5_keep, sp)))
-            return rc;
-    }
-    for (int s = 0; s < NSH; ++s) {
-        for (uint32_t q = 0; q < S.n(type, s); ++q) {
-            const size_t i = (size_t)s * S.rc[type] + q;
-            if (kind == LST_MD) {
-                if (in_ev((int32_t)i)) put(tup, (int32_t)i);
-            } else if (kind == LST_SEG) {
-                if (in_ev(a[i])) { put(tup, a[i]); put(tup, b[i]); }
-            } else if (kind == LST_T3) {
-                if (in_ev(a[i])) { put(tup, a[i]); put(tup, b[i]); put(tup, d[i]); }
-            } else {
-                if (!in_ev(a[i]) || (kind == LST_T5_KEPT && !keep[i])) continue;
-                put(tup, a[i]); put(tup, b[i]); put(tup, d[i]); put(tup, e4[i]); put(tup, f5[i]);
-            }
-        }
-    }
-    const int64_t nt = (int64_t)tup.size() / width;
+    const int width = kind == LST_MD ? 2 : kind == LST_SEG ? 4 : kind == LST_T3 ? 6 : 10;
+    int64_t nt = 0;
+    int rc = pack_rows(c, type, event, kind == LST_T5_KEPT, nullptr, width * sizeof(int32_t), &nt, stream);
+    if (rc) return rc;
     if (n_tuples) *n_tuples = nt;
     if (nt > cap)
         return fail(c, LST_E_CAPACITY, "%lld tuples, capacity %lld", (long long)nt, (long long)cap);
-    if (out && nt) std::memcpy(out, tup.data(), sizeof(int32_t) * tup.size());
+    if (out && nt) std::memcpy(out, c->res_host + RES_BODY, (size_t)nt * width * sizeof(int32_t));
     return LST_OK;
 }
-
 
 }  // extern "C"
 
@@ -1573,27 +1539,11 @@ static int obj_field(lst_ctx *c, int type, int32_t event, const T *src, int widt
     if (!c) return LST_E_INVALID;
     if (event < 0 || event >= c->n_events) return fail(c, LST_E_INVALID, "event %d", event);
     if (c->stage < (type == OT_T3 ? 5 : 6)) return fail(c, LST_E_STATE, "objects have not been built");
-    int rc = sync_stream(c, stream);
-    if (rc) return rc;
-    const EvDev &E = c->E;
-    ShardCounts S;
-    if ((rc = read_shards(c, S)) || (rc = check_fault(c, S.gc[GC_ERROR]))) return rc;
-    if (S.gc[GC_OVERFLOW])
-        return fail(c, LST_E_CAPACITY, "capacity overflow (mask %u)", S.gc[GC_OVERFLOW]);
-    std::vector<int32_t> m0, slot;
-    std::vector<T> val;
-    if ((rc = d2h(c, m0, type == OT_T3 ? E.t3_a : E.t5_md0, S.span(type))) ||
-        (rc = d2h(c, val, src, S.span(type) * width)) || (rc = d2h(c, slot, E.md_slot, S.span(OT_MD))))
-        return rc;
-    const int lo_slot = event * c->n_mod, hi_slot = (event + 1) * c->n_mod;
     int64_t k = 0;
-    for (int sh = 0; sh < NSH; ++sh)
-        for (uint32_t q = 0; q < S.n(type, sh); ++q) {
-            const size_t i = (size_t)sh * S.rc[type] + q;
-            if (slot[m0[i]] < lo_slot || slot[m0[i]] >= hi_slot) continue;
-            if (out && k < cap) std::memcpy(&out[width * k], &val[width * i], width * sizeof(T));
-            ++k;
-        }
+    int rc = pack_rows(c, type, event, false, src, width * sizeof(T), &k, stream);
+    if (rc) return rc;
+    if (out && cap > 0 && k > 0)
+        std::memcpy(out, c->res_host + RES_BODY, (size_t)std::min(k, cap) * width * sizeof(T));
     if (n_out) *n_out = k;
     if (k > cap)
         return fail(c, LST_E_CAPACITY, "%lld %s, capacity %lld", (long long)k, what, (long long)cap);

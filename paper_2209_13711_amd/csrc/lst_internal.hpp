@@ -53,6 +53,9 @@ constexpr int GC_COUNT = GC_SH + OT_COUNT * NSH * GC_PAD;
 // still cached, on the same XCD.  Correctness never depends on the mapping.
 constexpr int NXCD = 8;
 
+// blocks of the result packing at most (lst_read.hip)
+constexpr int PACK_BLOCKS = 512;
+
 struct ModDev {
     const float *cx, *cy, *cz, *ux, *uy, *uz, *vx, *vy, *vz, *g, *rl, *wx, *wy, *wz;
     const int32_t *barrel;   // 1 barrel, 0 endcap
@@ -160,6 +163,8 @@ struct EvDev {
     // counters (zeroed at chain start)
     uint32_t *gc;                    // [GC_COUNT]
     uint32_t *bar;                   // persistent-chain barrier counters [33]
+    uint32_t *rd_cnt;                // [PACK_BLOCKS] rows per block of the result packing
+    uint64_t *rd_part;               // [count_part_size] per-block sums of the counts
 };
 
 constexpr int TIE_SLOTS = 8;
@@ -203,6 +208,35 @@ hipError_t launch_pixel(const EvDev &E, const Consts &K, const PixConsts &P, hip
 // per-module capacity `cap` of object type `type` (lst_cap.hip): objects of
 // a module beyond it removed, the type's arrays compacted in place
 hipError_t launch_cap(const EvDev &E, int type, int32_t cap, hipStream_t s);
+// results for the host (lst_read.hip), written into pinned host memory:
+// counters of the chain, and how many rows the selection has
+struct ReadHdr {
+    uint32_t overflow, error, rows, pad;
+    uint32_t shard[OT_COUNT][NSH];   // as reserved: may exceed the region
+};
+// one event's objects as rows: its slots, quintuplets kept or all, the field
+// array of a field packing, where the rows go and how many fit
+struct PackArgs {
+    int32_t lo_slot, hi_slot;
+    int32_t whole_batch;             // the batch is this one event
+    int32_t kept_only;
+    const void *field;
+    ReadHdr *hdr;
+    void *out;
+    uint32_t cap_rows;
+};
+hipError_t launch_pack_tuples(const EvDev &E, int type, const PackArgs &A, hipStream_t s);
+// type OT_T3 or OT_T5; row_bytes 1, 4 or 160
+hipError_t launch_pack_field(const EvDev &E, int type, int row_bytes, const PackArgs &A, hipStream_t s);
+// the counts of every event: candidate and stored mini-doublets, candidate
+// segments; then number and candidates of the segments and of the triplets,
+// number, kept and cleaned of the quintuplets
+struct EventSums {
+    uint64_t sum[4][3];
+};
+size_t count_part_size(int n_mod, int n_events);
+hipError_t launch_read_counts(const EvDev &E, const ModDev &M, int n_events, int stage, ReadHdr *hdr,
+                              EventSums *out, hipStream_t s);
 // stop: PERS_FULL runs every stage; PERS_TO_T5 ends after the quintuplets,
 // PERS_TO_T3 after the triplets (learned scoring follows as its own
 // launches); lanes: group width of its four object stages

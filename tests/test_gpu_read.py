@@ -1,0 +1,81 @@
+"""Results packed on the device (objects, object fields, counts) at the sizes
+where the packing changes: no object, one row, more rows than a tile, more
+than the pinned buffer first holds, events selected out of a batch."""
+import numpy as np
+import pytest
+
+import oracle
+from synth import events as E
+from synth import geometry as G
+from synth import params as PR
+from tests.parity import assert_parity
+
+pytestmark = pytest.mark.gpu
+
+
+def _ctx(cid, features=0):
+    import paper_2209_13711_amd as lst
+    cfg = E.CONFIGS[cid]
+    geo = G.get(cfg.geometry)
+    params = PR.make(w=cfg.window)
+    return lst, lst.Context(params, geo.f32, geo.i32, device=0), oracle.Oracle(params, geo.f32, geo.i32)
+
+
+@pytest.mark.parametrize("cid,tracks", [(1, (1, 0, 37)), (2, (900, 1, 300, 2)), (5, (1200,))])
+def test_every_kind_of_every_event(cid, tracks):
+    """every event's objects and counts against the oracle run on it alone,
+    and a second read of the same chain gives the same rows in the same order"""
+    lst, ctx, orc = _ctx(cid)
+    evs = [E.generate(cid, 500 + i, n_tracks=n) for i, n in enumerate(tracks)]
+    b = E.concat(evs)
+    print(f"case read cfg{cid} tracks {tracks}", flush=True)
+    ctx.run_batch(b.offsets, b.x, b.y, b.z, b.module, b.sensor)
+    for e, ev in enumerate(evs):
+        ref = orc.run_event(ev)
+        got = {k: ctx.objects(e, k) for k in range(5)}
+        assert_parity(got, ref)
+        c = ctx.counts(e)
+        assert [c["n_md"], c["n_seg"], c["n_t3"], c["n_t5"], c["n_t5_kept"]] == \
+            [len(got[k]) for k in range(5)]
+        assert [c["cand_md"], c["cand_seg"], c["cand_t3"], c["cand_t5"]] == list(ref.cands[:4])
+        for k in range(5):
+            np.testing.assert_array_equal(ctx.objects(e, k), got[k])
+
+
+def test_counts_after_each_stage():
+    """counts of a chain that has run to a stage hold that stage's and the
+    earlier ones' objects and candidates, nothing later"""
+    lst, ctx, orc = _ctx(2)
+    ev = E.generate(2, 510, n_tracks=400)
+    ref = orc.run_event(ev)
+    ctx.run_event(ev)
+    print("case read counts by stage", flush=True)
+    ctx.load_hits(np.array([0, ev.n_hits], np.int32), ev.x, ev.y, ev.z, ev.module, ev.sensor)
+    n = ("n_md", "n_seg", "n_t3", "n_t5", "n_t5_kept")
+    cand = ("cand_md", "cand_seg", "cand_t3", "cand_t5")
+    steps = (ctx.run_sort, ctx.run_md, ctx.run_segments, ctx.run_triplets, ctx.run_quintuplets,
+             ctx.run_dedup)
+    for i, fn in enumerate(steps):
+        fn()
+        c = ctx.counts(0)
+        assert [c[k] for k in n] == [len(ref.tuples[k]) if k < i else 0 for k in range(5)], i
+        assert [c[k] for k in cand] == [ref.cands[k] if k <= i else 0 for k in range(4)], i
+
+
+def test_field_rows_follow_the_objects_and_outgrow_the_buffer():
+    """3,000-track event: its triplet features (160 bytes a row, more than the
+    buffer first holds) are the rows of lst_get_objects, in its order"""
+    lst, ctx, orc = _ctx(2)
+    ev = E.generate(2, 520, n_tracks=3000)
+    ctx.reserve(dict(lst.default_caps(1, ev.n_hits), features=1))
+    print("case read features", flush=True)
+    ctx.run_event(ev)
+    ctx.run_t3_features()
+    t3, f = ctx.objects(0, lst.LST_T3), ctx.t3_features(0)
+    assert len(t3) == len(f) and f.nbytes > 1 << 20
+    r = np.hypot(ev.x.astype(np.float64), ev.y.astype(np.float64))
+    for j in range(3):   # anchor radius and z over 100 cm, FP32
+        np.testing.assert_allclose(f[:, 5 * j], r[t3[:, 2 * j]] * 0.01, rtol=1e-6)
+        np.testing.assert_allclose(f[:, 5 * j + 1], ev.z[t3[:, 2 * j]] * np.float32(0.01), rtol=1e-6,
+                                   atol=1e-9)
+    np.testing.assert_array_equal(ctx.t3_features(0), f)
