@@ -8,7 +8,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -163,7 +162,7 @@ size_t carve(lst_ctx *c, char *base, const lst_caps &k, EvDev &E, void **zero_ba
     E.cap_keys = (int32_t)keys;
     E.desc = cv.take<int32_t>(D_COUNT);
     E.bar = cv.take<uint32_t>(33 * 64);   // 33 barrier counters, one 256-byte line each
-    E.rd_cnt = cv.take<uint32_t>(PACK_BLOCKS);
+    E.rd_cnt = cv.take<uint32_t>(PACK_BLOCKS + 1);
     E.rd_part = cv.take<uint64_t>(count_part_size(c->n_mod, k.events));
     E.cap_hits = k.hits;
     const int64_t caps[OT_COUNT] = {k.md, k.seg, k.t3, k.t5};
@@ -296,6 +295,9 @@ size_t carve(lst_ctx *c, char *base, const lst_caps &k, EvDev &E, void **zero_ba
         E.hmin_p = cv.take<unsigned long long>(k.px_hits);
         E.hflag_o = cv.take<uint8_t>(k.hits);
         E.hflag_p = cv.take<uint8_t>(k.px_hits);
+        const size_t rows = 2 * (size_t)k.px_cand + nt5 + k.seeds;
+        E.rd_key = cv.take<uint64_t>(rows);
+        E.rd_src = cv.take<int2>(rows);
     }
     return (cv.off + 255) & ~(size_t)255;
 }
@@ -1442,28 +1444,26 @@ static int compute_counts(lst_ctx *c, hipStream_t stream)
     return LST_OK;
 }
 
-// One event's objects of a type (their hit tuples, or `field`) as rows in
-// the pinned result buffer, in array order; *n_rows of row_bytes each.
-static int pack_rows(lst_ctx *c, int type, int32_t event, bool kept_only, const void *field,
-                     size_t row_bytes, int64_t *n_rows, void *stream)
+// Rows of one event packed by launch(A) into the pinned result buffer;
+// *n_rows of row_bytes each.
+template <class F>
+static int pack_event(lst_ctx *c, int32_t event, size_t row_bytes, int64_t *n_rows, void *stream,
+                      F &&launch)
 {
     HIPCHK(c, hipSetDevice(c->device));
-    hipStream_t s = (hipStream_t)stream;
     int rc = c->res_host ? LST_OK : res_reserve(c, RES_FIRST);
     if (rc) return rc;
     for (;;) {
         ReadHdr *h = (ReadHdr *)c->res_host;
         PackArgs A{};
+        A.event = event;
         A.lo_slot = event * c->n_mod;
         A.hi_slot = A.lo_slot + c->n_mod;
         A.whole_batch = c->n_events == 1;
-        A.kept_only = kept_only;
-        A.field = field;
         A.hdr = h;
         A.out = c->res_host + RES_BODY;
         A.cap_rows = (uint32_t)std::min<size_t>((c->res_cap - RES_BODY) / row_bytes, 0xffffffffu);
-        if (field) HIPCHK(c, launch_pack_field(c->E, type, (int)row_bytes, A, s));
-        else HIPCHK(c, launch_pack_tuples(c->E, type, A, s));
+        HIPCHK(c, launch(A));
         if ((rc = sync_stream(c, stream)) || (rc = check_fault(c, h->error))) return rc;
         if (h->overflow) return fail(c, LST_E_CAPACITY, "capacity overflow (mask %u)", h->overflow);
         *n_rows = h->rows;
@@ -1471,6 +1471,18 @@ static int pack_rows(lst_ctx *c, int type, int32_t event, bool kept_only, const 
         // more rows than the buffer holds: grow it to the need and pack again
         if ((rc = res_reserve(c, (size_t)h->rows * row_bytes))) return rc;
     }
+}
+
+// an event's objects of a type (their hit tuples, or `field`), in array order
+static int pack_rows(lst_ctx *c, int type, int32_t event, bool kept_only, const void *field,
+                     size_t row_bytes, int64_t *n_rows, void *stream)
+{
+    return pack_event(c, event, row_bytes, n_rows, stream, [&](PackArgs &A) {
+        A.kept_only = kept_only;
+        A.field = field;
+        return field ? launch_pack_field(c->E, type, (int)row_bytes, A, (hipStream_t)stream)
+                     : launch_pack_tuples(c->E, type, A, (hipStream_t)stream);
+    });
 }
 
 extern "C" {
@@ -1586,68 +1598,26 @@ int lst_get_t5_features(lst_ctx *c, int32_t event, float *out, int64_t cap, int6
     return obj_field(c, OT_T5, event, c->E.t5_feat, 40, out, cap, n_out, stream, "feature rows");
 }
 
-// the pixel stage's device arrays, read back for one event's getters
-struct PixRead {
-    std::vector<int32_t> sorig, hlo, hup, slot, t5m[5], t3a, t3b, t3c;
-    std::vector<int32_t> s5, o5, s3, o3, sev, sloc;
-    std::vector<float> f5, f3;
-    std::vector<uint8_t> k5, k3, clean, sk, keep;
-    ShardCounts S;
-};
-
-static int pix_read(lst_ctx *c, void *stream, PixRead &R)
+// track candidates (what -1) or pT5 (0) or pT3 (1) link candidates of an event, sorted
+static int pixel_rows(lst_ctx *c, int32_t event, int32_t what, int width, int32_t *out, int64_t cap,
+                      int64_t *n, void *stream)
 {
     if (c->stage < 8) return fail(c, LST_E_STATE, "the pixel stage has not run");
-    int rc = sync_stream(c, stream);
+    int64_t rows = 0;
+    int rc = pack_event(c, event, width * sizeof(int32_t), &rows, stream, [&](PackArgs &A) {
+        A.what = what;
+        A.width = width;
+        A.type_of[0] = LST_TC_PT5;
+        A.type_of[1] = LST_TC_PT3;
+        A.type_of[2] = LST_TC_T5;
+        A.type_of[3] = LST_TC_PLS;
+        return launch_pack_pixel(c->E, A, (hipStream_t)stream);
+    });
     if (rc) return rc;
-    const EvDev &E = c->E;
-    ShardCounts &S = R.S;
-    if ((rc = read_shards(c, S)) || (rc = check_fault(c, S.gc[GC_ERROR]))) return rc;
-    if (S.gc[GC_OVERFLOW])
-        return fail(c, LST_E_CAPACITY, "capacity overflow (mask %u)", S.gc[GC_OVERFLOW]);
-    const uint32_t n5 = std::min<uint32_t>(S.gc[GC_PX5], (uint32_t)E.cap_pxc);
-    const uint32_t n3 = std::min<uint32_t>(S.gc[GC_PX3], (uint32_t)E.cap_pxc);
-    const int64_t n_sd = c->sd_off[c->n_events];
-    const size_t nmd = S.span(OT_MD), nt3 = S.span(OT_T3), nt5 = S.span(OT_T5);
-    if ((rc = sorted_orig(c, R.sorig, S.gc[GC_N_SORTED])) || (rc = d2h(c, R.hlo, E.md_hlo, nmd)) ||
-        (rc = d2h(c, R.hup, E.md_hup, nmd)) || (rc = d2h(c, R.slot, E.md_slot, nmd)) ||
-        (rc = d2h(c, R.t5m[0], E.t5_md0, nt5)) || (rc = d2h(c, R.t5m[1], E.t5_md1, nt5)) ||
-        (rc = d2h(c, R.t5m[2], E.t5_md2, nt5)) || (rc = d2h(c, R.t5m[3], E.t5_md3, nt5)) ||
-        (rc = d2h(c, R.t5m[4], E.t5_md4, nt5)) || (rc = d2h(c, R.t3a, E.t3_a, nt3)) ||
-        (rc = d2h(c, R.t3b, E.t3_b, nt3)) || (rc = d2h(c, R.t3c, E.t3_c, nt3)) ||
-        (rc = d2h(c, R.s5, E.c5_seed, n5)) || (rc = d2h(c, R.o5, E.c5_obj, n5)) ||
-        (rc = d2h(c, R.f5, E.c5_score, n5)) || (rc = d2h(c, R.k5, E.c5_keep, n5)) ||
-        (rc = d2h(c, R.s3, E.c3_seed, n3)) || (rc = d2h(c, R.o3, E.c3_obj, n3)) ||
-        (rc = d2h(c, R.f3, E.c3_score, n3)) || (rc = d2h(c, R.k3, E.c3_keep, n3)) ||
-        (rc = d2h(c, R.clean, E.t5_clean, nt5)) || (rc = d2h(c, R.keep, E.t5_keep, nt5)) ||
-        (rc = d2h(c, R.sev, E.sd_ev, n_sd)) || (rc = d2h(c, R.sloc, E.sd_local, n_sd)) ||
-        (rc = d2h(c, R.sk, E.sd_keep, n_sd)))
-        return rc;
-    R.s5.resize(n5); R.s3.resize(n3);
-    return LST_OK;
-}
-
-// outer hit tuple (per-event indices) of a quintuplet (w 10) or triplet (w 6)
-static void pix_tuple(const PixRead &R, int w, int32_t t, int32_t *out)
-{
-    for (int j = 0; j < w / 2; ++j) {
-        const int32_t m = w == 10 ? R.t5m[j][t] : j == 0 ? R.t3a[t] : j == 1 ? R.t3b[t] : R.t3c[t];
-        out[2 * j] = R.sorig[R.hlo[m]];
-        out[2 * j + 1] = R.sorig[R.hup[m]];
-    }
-    for (int k = w; k < 10; ++k) out[k] = -1;
-}
-
-static int put_rows(lst_ctx *c, std::vector<std::array<int32_t, 13>> &rows, int width,
-                    int32_t *out, int64_t cap, int64_t *n)
-{
-    std::sort(rows.begin(), rows.end());
-    if (n) *n = (int64_t)rows.size();
-    if ((int64_t)rows.size() > cap)
-        return fail(c, LST_E_CAPACITY, "%lld rows, capacity %lld", (long long)rows.size(), (long long)cap);
-    if (out)
-        for (size_t i = 0; i < rows.size(); ++i)
-            std::memcpy(&out[(size_t)width * i], rows[i].data(), sizeof(int32_t) * width);
+    if (n) *n = rows;
+    if (rows > cap)
+        return fail(c, LST_E_CAPACITY, "%lld rows, capacity %lld", (long long)rows, (long long)cap);
+    if (out && rows) std::memcpy(out, c->res_host + RES_BODY, (size_t)rows * width * sizeof(int32_t));
     return LST_OK;
 }
 
@@ -1656,40 +1626,7 @@ int lst_get_track_candidates(lst_ctx *c, int32_t event, int32_t *out, int64_t ca
 {
     if (!c) return LST_E_INVALID;
     if (event < 0 || event >= c->n_events) return fail(c, LST_E_INVALID, "event %d", event);
-    PixRead R;
-    int rc = pix_read(c, stream, R);
-    if (rc) return rc;
-    std::vector<std::array<int32_t, 13>> rows;
-    std::array<int32_t, 13> r{};
-    for (size_t i = 0; i < R.s5.size(); ++i)
-        if (R.k5[i] && R.sev[R.s5[i]] == event) {
-            r[0] = LST_TC_PT5; r[1] = R.sloc[R.s5[i]];
-            pix_tuple(R, 10, R.o5[i], &r[2]);
-            rows.push_back(r);
-        }
-    for (size_t i = 0; i < R.s3.size(); ++i)
-        if (R.k3[i] && R.sev[R.s3[i]] == event) {
-            r[0] = LST_TC_PT3; r[1] = R.sloc[R.s3[i]];
-            pix_tuple(R, 6, R.o3[i], &r[2]);
-            rows.push_back(r);
-        }
-    const int lo_slot = event * c->n_mod, hi_slot = (event + 1) * c->n_mod;
-    for (int sh = 0; sh < NSH; ++sh)
-        for (uint32_t q = 0; q < R.S.n(OT_T5, sh); ++q) {
-            const size_t t = (size_t)sh * R.S.rc[OT_T5] + q;
-            const int32_t sl = R.slot[R.t5m[0][t]];
-            if (!R.clean[t] || sl < lo_slot || sl >= hi_slot) continue;
-            r[0] = LST_TC_T5; r[1] = -1;
-            pix_tuple(R, 10, (int32_t)t, &r[2]);
-            rows.push_back(r);
-        }
-    for (int32_t q = c->sd_off[event]; q < c->sd_off[event + 1]; ++q)
-        if (R.sk[q]) {
-            r[0] = LST_TC_PLS; r[1] = R.sloc[q];
-            for (int k = 0; k < 10; ++k) r[2 + k] = -1;
-            rows.push_back(r);
-        }
-    return put_rows(c, rows, 12, out, cap, n);
+    return pixel_rows(c, event, -1, 12, out, cap, n, stream);
 }
 
 int lst_get_pixel_candidates(lst_ctx *c, int32_t event, int32_t what, int32_t *out, int64_t cap,
@@ -1698,23 +1635,7 @@ int lst_get_pixel_candidates(lst_ctx *c, int32_t event, int32_t what, int32_t *o
     if (!c) return LST_E_INVALID;
     if (event < 0 || event >= c->n_events) return fail(c, LST_E_INVALID, "event %d", event);
     if (what != 0 && what != 1) return fail(c, LST_E_INVALID, "what %d (0 pT5, 1 pT3)", what);
-    PixRead R;
-    int rc = pix_read(c, stream, R);
-    if (rc) return rc;
-    const std::vector<int32_t> &sd = what ? R.s3 : R.s5, &ob = what ? R.o3 : R.o5;
-    const std::vector<float> &sc = what ? R.f3 : R.f5;
-    const std::vector<uint8_t> &kp = what ? R.k3 : R.k5;
-    std::vector<std::array<int32_t, 13>> rows;
-    std::array<int32_t, 13> r{};
-    for (size_t i = 0; i < sd.size(); ++i) {
-        if (R.sev[sd[i]] != event) continue;
-        r[0] = R.sloc[sd[i]];
-        pix_tuple(R, what ? 6 : 10, ob[i], &r[1]);
-        std::memcpy(&r[11], &sc[i], sizeof(float));
-        r[12] = kp[i];
-        rows.push_back(r);
-    }
-    return put_rows(c, rows, 13, out, cap, n);
+    return pixel_rows(c, event, what, 13, out, cap, n, stream);
 }
 
 int lst_get_t3_features(lst_ctx *c, int32_t event, float *out, int64_t cap, int64_t *n_out,

@@ -163,7 +163,9 @@ struct EvDev {
     // counters (zeroed at chain start)
     uint32_t *gc;                    // [GC_COUNT]
     uint32_t *bar;                   // persistent-chain barrier counters [33]
-    uint32_t *rd_cnt;                // [PACK_BLOCKS] rows per block of the result packing
+    uint32_t *rd_cnt;                // [PACK_BLOCKS + 1] rows per block of the result packing; all
+    uint64_t *rd_key;                // [2 cap_pxc + t5 span + cap_seeds] pixel rows: sort key
+    int2 *rd_src;                    // the same: source and index there
     uint64_t *rd_part;               // [count_part_size] per-block sums of the counts
 };
 
@@ -224,10 +226,15 @@ struct PackArgs {
     ReadHdr *hdr;
     void *out;
     uint32_t cap_rows;
+    // pixel rows: the event, track candidates (-1) or pT5 (0) or pT3 (1) link
+    // candidates, words of a row, type word of each source of track candidates
+    int32_t event, what, width;
+    int32_t type_of[4];
 };
 hipError_t launch_pack_tuples(const EvDev &E, int type, const PackArgs &A, hipStream_t s);
 // type OT_T3 or OT_T5; row_bytes 1, 4 or 160
 hipError_t launch_pack_field(const EvDev &E, int type, int row_bytes, const PackArgs &A, hipStream_t s);
+hipError_t launch_pack_pixel(const EvDev &E, const PackArgs &A, hipStream_t s);
 // the counts of every event: candidate and stored mini-doublets, candidate
 // segments; then number and candidates of the segments and of the triplets,
 // number, kept and cleaned of the quintuplets

@@ -196,6 +196,227 @@ hipError_t launch_pack_field(const EvDev &E, int type, int row_bytes, const Pack
     }
 }
 
+// ---------------------------------------------------------------- pixel rows
+// Track candidates (what < 0) or link candidates (0 pT5, 1 pT3) of one event
+// as rows in lexicographic order.  The sources are taken as one list: pT5
+// candidates, pT3 candidates, quintuplets, the event's seeds.  Three launches:
+// wanted entries per block, their sort keys (first words of the row) into a
+// list, and each row to the place its rank among the keys gives it.  The
+// rank counts the smaller keys, n per row.  A PU200-like event (2,300 rows):
+// 5.0, 6.6 and 24 us, 49 us from call to return; 1.3 ms with the pixel
+// stage's arrays copied to the host and sorted there.
+struct PxList {
+    uint32_t n5, n3, nt, total;
+    int32_t sd0;
+};
+
+// the list's lengths (every thread of the block calls it)
+__device__ __forceinline__ PxList px_list(const EvDev &E, const PackArgs &A, uint32_t *s_pre)
+{
+    PxList L{};
+    const uint32_t cap = (uint32_t)E.cap_pxc;
+    if (A.what != 1) L.n5 = min(E.gc[GC_PX5], cap);
+    if (A.what != 0) L.n3 = min(E.gc[GC_PX3], cap);
+    L.total = L.n5 + L.n3;
+    if (A.what < 0) {
+        L.nt = t5_prefix(E, s_pre);
+        L.sd0 = E.sd_off[A.event];
+        L.total += L.nt + (uint32_t)(E.sd_off[A.event + 1] - L.sd0);
+    }
+    return L;
+}
+
+// entry v of the list: its source (0 pT5, 1 pT3, 2 T5, 3 pLS) and index there
+struct PxEntry {
+    int32_t src, i;
+};
+
+__device__ __forceinline__ PxEntry px_entry(const EvDev &E, const PxList &L, const uint32_t *s_pre,
+                                            uint32_t v)
+{
+    if (v < L.n5) return PxEntry{0, (int32_t)v};
+    if ((v -= L.n5) < L.n3) return PxEntry{1, (int32_t)v};
+    if ((v -= L.n3) < L.nt) return PxEntry{2, t5_at(E, s_pre, v)};
+    return PxEntry{3, L.sd0 + (int32_t)(v - L.nt)};
+}
+
+__device__ __forceinline__ bool px_wanted(const EvDev &E, const PackArgs &A, const PxEntry &e)
+{
+    switch (e.src) {
+    case 0: return (A.what == 0 || E.c5_keep[e.i]) && E.sd_ev[E.c5_seed[e.i]] == A.event;
+    case 1: return (A.what == 1 || E.c3_keep[e.i]) && E.sd_ev[E.c3_seed[e.i]] == A.event;
+    case 2: {
+        if (!E.t5_clean[e.i]) return false;
+        const int32_t s = E.md_slot[E.t5_md0[e.i]];
+        return s >= A.lo_slot && s < A.hi_slot;
+    }
+    default: return E.sd_keep[e.i] != 0;
+    }
+}
+
+__device__ __forceinline__ int32_t px_seed(const EvDev &E, const PxEntry &e)
+{
+    return e.src == 0 ? E.sd_local[E.c5_seed[e.i]] : e.src == 1 ? E.sd_local[E.c3_seed[e.i]]
+         : e.src == 2 ? -1 : E.sd_local[e.i];
+}
+
+// outer hit j (0..9) of the entry's object, -1 past its end
+__device__ __forceinline__ int32_t px_hit(const EvDev &E, const PxEntry &e, int j)
+{
+    int32_t m;
+    if (e.src == 1) {
+        if (j >= 6) return -1;
+        const int32_t o = E.c3_obj[e.i];
+        m = j < 2 ? E.t3_a[o] : j < 4 ? E.t3_b[o] : E.t3_c[o];
+    } else if (e.src == 3) {
+        return -1;
+    } else {
+        m = t5_md(E, e.src == 0 ? E.c5_obj[e.i] : e.i, j >> 1);
+    }
+    return hit_orig(E, (j & 1) ? E.md_hup[m] : E.md_hlo[m]);
+}
+
+// word j of the entry's row: (type, seed, hits) or (seed, hits, score, kept)
+__device__ __forceinline__ int32_t px_word(const EvDev &E, const PackArgs &A, const PxEntry &e, int j)
+{
+    if (A.what < 0) {
+        // sources in the order of the track candidates' types
+        if (j == 0) return e.src == 0 ? A.type_of[0] : e.src == 1 ? A.type_of[1]
+                         : e.src == 2 ? A.type_of[2] : A.type_of[3];
+        return j == 1 ? px_seed(E, e) : px_hit(E, e, j - 2);
+    }
+    if (j == 0) return px_seed(E, e);
+    if (j < 11) return px_hit(E, e, j - 1);
+    if (j == 11) return __float_as_int(e.src == 0 ? E.c5_score[e.i] : E.c3_score[e.i]);
+    return e.src == 0 ? E.c5_keep[e.i] : E.c3_keep[e.i];
+}
+
+// the row's first words as an unsigned key in row order (every word is at
+// least -1; types fit two bits, seeds 30)
+__device__ __forceinline__ uint64_t px_key(const EvDev &E, const PackArgs &A, const PxEntry &e)
+{
+    const uint64_t seed = (uint64_t)(uint32_t)(px_seed(E, e) + 1);
+    const uint64_t hit = (uint64_t)((uint32_t)px_hit(E, e, 0) + 1u);
+    const uint64_t type = A.what < 0 ? (uint64_t)px_word(E, A, e, 0) : 0u;
+    return (type << 62) | (seed << 32) | hit;
+}
+
+__global__ __launch_bounds__(BLOCK) void k_px_count(EvDev E, PackArgs A)
+{
+    __shared__ uint32_t s_pre[NSH + 1], s_n;
+    if (upstream_overflow(E)) return;
+    if (threadIdx.x == 0) s_n = 0;
+    const PxList L = px_list(E, A, s_pre);
+    __syncthreads();
+    uint32_t first, last, mine = 0;
+    block_share(L.total, first, last);
+    for (uint32_t v0 = first; v0 < last; v0 += BLOCK) {
+        const uint32_t v = v0 + threadIdx.x;
+        const bool on = v < last && px_wanted(E, A, px_entry(E, L, s_pre, v));
+        mine += (uint32_t)__popcll(__ballot(on));
+    }
+    if (rd_lane() == 0 && mine) atomicAdd(&s_n, mine);
+    __syncthreads();
+    if (threadIdx.x == 0) E.rd_cnt[blockIdx.x] = s_n;
+}
+
+__global__ __launch_bounds__(BLOCK) void k_px_keys(EvDev E, PackArgs A)
+{
+    __shared__ uint32_t s_pre[NSH + 1], s_w[WAVES];
+    if (upstream_overflow(E)) return;
+    const PxList L = px_list(E, A, s_pre);
+    uint32_t mine = 0, before;
+    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += BLOCK) mine += E.rd_cnt[b];
+    (void)rd_block_scan(mine, s_w, before);
+    uint32_t first, last;
+    block_share(L.total, first, last);
+    for (uint32_t v0 = first; v0 < last; v0 += BLOCK) {
+        const uint32_t v = v0 + threadIdx.x;
+        PxEntry e{};
+        bool on = false;
+        if (v < last) {
+            e = px_entry(E, L, s_pre, v);
+            on = px_wanted(E, A, e);
+        }
+        uint32_t rows;
+        const uint32_t pos = before + rd_block_scan(on ? 1u : 0u, s_w, rows);
+        if (on) {
+            E.rd_key[pos] = px_key(E, A, e);
+            E.rd_src[pos] = make_int2(e.src, e.i);
+        }
+        before += rows;
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) E.rd_cnt[PACK_BLOCKS] = before;
+}
+
+// row order of entries with equal keys, other than themselves
+__device__ __forceinline__ bool px_less(const EvDev &E, const PackArgs &A, uint32_t a, uint32_t b)
+{
+    const int2 x = E.rd_src[a], y = E.rd_src[b];
+    const PxEntry ea{x.x, x.y}, eb{y.x, y.y};
+    for (int j = 0; j < A.width; ++j) {
+        const int32_t p = px_word(E, A, ea, j), q = px_word(E, A, eb, j);
+        if (p != q) return p < q;
+    }
+    return a < b;
+}
+
+// A wave ranks PX_RANK rows at a time: its lanes take the keys 64 at a time
+// and compare each with all of the wave's rows.  (One thread per row over
+// keys staged in LDS kept nine blocks busy: 197 us for 2,300 rows.)
+constexpr int PX_RANK = 4;
+
+__global__ __launch_bounds__(BLOCK) void k_px_rows(EvDev E, PackArgs A)
+{
+    if (blockIdx.x == 0) put_header(E, A.hdr);
+    const uint32_t n = upstream_overflow(E) ? 0u : E.rd_cnt[PACK_BLOCKS];
+    if (blockIdx.x == 0 && threadIdx.x == 0) A.hdr->rows = n;
+    if (n > A.cap_rows) return;   // the buffer grows and the rows are packed again
+    const uint32_t l = (uint32_t)rd_lane(), width = (uint32_t)A.width;
+    int32_t *out = (int32_t *)A.out;
+    for (uint32_t r0 = (blockIdx.x * WAVES + (threadIdx.x >> 6)) * PX_RANK; r0 < n;
+         r0 += gridDim.x * WAVES * PX_RANK) {
+        uint64_t key[PX_RANK];
+        uint32_t rank[PX_RANK];
+#pragma unroll
+        for (int i = 0; i < PX_RANK; ++i) {
+            key[i] = r0 + i < n ? E.rd_key[r0 + i] : 0;
+            rank[i] = 0;
+        }
+#pragma unroll 4
+        for (uint32_t c = l; c < n; c += 64) {
+            const uint64_t o = E.rd_key[c];
+#pragma unroll
+            for (int i = 0; i < PX_RANK; ++i) {
+                rank[i] += o < key[i];
+                if (o == key[i] && r0 + i < n && c != r0 + i && px_less(E, A, c, r0 + i)) ++rank[i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < PX_RANK; ++i)
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) rank[i] += __shfl_xor(rank[i], d, 64);
+        const uint32_t words = min(n - r0, (uint32_t)PX_RANK) * width;
+        for (uint32_t q = l; q < words; q += 64) {
+            const uint32_t i = q / width, j = q - i * width;
+            const uint32_t at = i == 0 ? rank[0] : i == 1 ? rank[1] : i == 2 ? rank[2] : rank[3];
+            const int2 x = E.rd_src[r0 + i];
+            out[(size_t)at * width + j] = px_word(E, A, PxEntry{x.x, x.y}, (int)j);
+        }
+    }
+}
+static_assert(PX_RANK == 4, "rank of the row in the loop above");
+
+hipError_t launch_pack_pixel(const EvDev &E, const PackArgs &A, hipStream_t s)
+{
+    const int64_t most = 2 * (int64_t)E.cap_pxc + (int64_t)E.rc[OT_T5] * NSH + E.cap_seeds;
+    const int grid = (int)std::min<int64_t>(PACK_BLOCKS, std::max<int64_t>(1, (most + BLOCK - 1) / BLOCK));
+    hipLaunchKernelGGL(k_px_count, dim3(grid), dim3(BLOCK), 0, s, E, A);
+    hipLaunchKernelGGL(k_px_keys, dim3(grid), dim3(BLOCK), 0, s, E, A);
+    hipLaunchKernelGGL(k_px_rows, dim3(grid), dim3(BLOCK), 0, s, E, A);
+    return hipGetLastError();
+}
+
 // ---------------------------------------------------------------- counts
 // Sums per event, stored per block and added up by a second kernel (no
 // atomics on device memory, no clearing).  The grid has a part for the module slots

@@ -79,3 +79,33 @@ def test_field_rows_follow_the_objects_and_outgrow_the_buffer():
         np.testing.assert_allclose(f[:, 5 * j + 1], ev.z[t3[:, 2 * j]] * np.float32(0.01), rtol=1e-6,
                                    atol=1e-9)
     np.testing.assert_array_equal(ctx.t3_features(0), f)
+
+
+@pytest.mark.parametrize("cid,tracks", [(2, (3000,)), (5, (400, 2, 700))])
+def test_pixel_rows_are_sorted(cid, tracks):
+    """track and link candidates come in lexicographic order, each event's
+    own (equal first words, i.e. one seed with several objects, included)"""
+    lst, ctx, orc = _ctx(cid)
+    evs = [E.generate(cid, 530 + i, n_tracks=n) for i, n in enumerate(tracks)]
+    pxs = [E.pixel_seeds(ev, cid, 530 + i) for i, ev in enumerate(evs)]
+    b = E.concat(evs)
+    cat = lambda a: np.concatenate([getattr(p, a) for p in pxs])
+    print(f"case read pixel cfg{cid} tracks {tracks}", flush=True)
+    ctx.reserve(lst.default_caps(len(evs), int(b.offsets[-1])))
+    ctx.pixel_caps(sum(p.n_hits for p in pxs), sum(p.n_seeds for p in pxs))
+    ctx.run_batch(b.offsets, b.x, b.y, b.z, b.module, b.sensor)
+    ctx.load_pixel(np.r_[0, np.cumsum([p.n_hits for p in pxs])], cat("x"), cat("y"), cat("z"),
+                   np.r_[0, np.cumsum([p.n_seeds for p in pxs])], cat("seeds"), PR.make_pixel())
+    ctx.run_pixel()
+    tied = 0
+    for e, (ev, px) in enumerate(zip(evs, pxs)):
+        orc.run_event(ev)
+        ref = orc.run_pixel(PR.make_pixel(), px)
+        for got, want in ((ctx.track_candidates(e), ref.tc), (ctx.pixel_candidates(e, 0), ref.pt5),
+                          (ctx.pixel_candidates(e, 1), ref.pt3)):
+            order = np.lexsort(got.T[::-1]) if len(got) else np.zeros(0, int)
+            np.testing.assert_array_equal(order, np.arange(len(got)))
+            same = set(map(tuple, got.tolist())) == set(map(tuple, np.asarray(want).tolist()))
+            assert same or ref.near > 0
+            tied += int((np.diff(got[:, :2], axis=0) == 0).all(axis=1).sum()) if len(got) > 1 else 0
+    assert tied > 0
