@@ -550,6 +550,177 @@ __global__ __launch_bounds__(SORT_EV_BLOCK) void k_scatter_ev(EvDev E, ModDev M)
     }
 }
 
+// One event: the whole grouping in one launch.  Its 2 x n_mod keys are split
+// in GROUP_PARTS ranges of whole modules, one block per range.  A block reads
+// the module and sensor ids of all hits, lists those of its range with their
+// bins counted in LDS, and counts the hits of earlier ranges as it goes, so it
+// knows its first position without waiting for any other block; then it scans
+// its bins and stores its hits.  Reading the ids once per range (275 KB per
+// block on a PU200-like event, from the L2s) costs less than the two
+// dependent launches it saves.  What bounds it is VALU issue (every block
+// looks at every hit) and the latency of four phases, so a hit takes four
+// instructions unless it is in the range: ids out of range are rare, and only
+// their presence is noted (largest module id, bits of the sensor ids); a block
+// that saw any counts again, leaving them out.
+// Several events would read ids of events that are not theirs to know how
+// many valid hits precede them: three stress events took 57 us, 46 us with
+// the three kernels above, which they keep.  Measured in the chain: 200
+// tracks 5.5 us for 4.0 + 5.8 + 3.7, PU200-like 15.7 us for 8.2 + 7.1 + 4.6
+// (128 ranges: 2.3 us more).
+constexpr int GROUP_BLOCK = 1024;
+constexpr int GROUP_WAVES = GROUP_BLOCK / 64;
+constexpr int GROUP_PARTS = 256;      // one block per CU
+constexpr int GROUP_LIST = 256;       // hits of its range a wave lists in LDS; more are found by a second read
+constexpr int GROUP_ILP = 8;          // groups of four hits whose ids a thread loads together
+
+__host__ __device__ __forceinline__ int group_mods(int n_mod) { return (n_mod + GROUP_PARTS - 1) / GROUP_PARTS; }
+
+// f(hit, module, sensor) for every hit: four consecutive hits per 16-byte
+// load of the module ids, the last one to three hits one per thread.  A
+// wave's active lanes are always its first ones.
+template <class F>
+__device__ __forceinline__ void each_hit_id(const EvDev &E, int n_hits, F &&f)
+{
+    const int4 *mods = reinterpret_cast<const int4 *>(E.module);
+    const uint32_t *sens = reinterpret_cast<const uint32_t *>(E.sensor);
+    const int n_g = n_hits >> 2, t = (int)threadIdx.x;
+    for (int g0 = 0; g0 < n_g; g0 += GROUP_ILP * GROUP_BLOCK) {
+        int4 m[GROUP_ILP];
+        uint32_t s[GROUP_ILP];
+#pragma unroll
+        for (int u = 0; u < GROUP_ILP; ++u) {
+            const int g = g0 + u * GROUP_BLOCK + t;
+            if (g < n_g) {
+                m[u] = mods[g];
+                s[u] = sens[g];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < GROUP_ILP; ++u) {
+            const int g = g0 + u * GROUP_BLOCK + t;
+            if (g < n_g) {
+                f(4 * g, m[u].x, s[u] & 0xffu);
+                f(4 * g + 1, m[u].y, (s[u] >> 8) & 0xffu);
+                f(4 * g + 2, m[u].z, (s[u] >> 16) & 0xffu);
+                f(4 * g + 3, m[u].w, s[u] >> 24);
+            }
+        }
+    }
+    const int h = 4 * n_g + t;
+    if (h < n_hits) f(h, E.module[h], (uint32_t)E.sensor[h]);
+}
+
+__global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
+{
+    extern __shared__ uint32_t s_dyn[];     // the waves' lists, then the bins [2 group_mods(n_mod)]
+    __shared__ uint32_t s_before, s_bad, s_full, s_w[GROUP_WAVES], s_own[GROUP_WAVES];
+    const int n_mod = M.n_mod, per_part = group_mods(n_mod), part = blockIdx.x;
+    const int w = wave_id(), l = lane_id();
+    int2 *s_list = reinterpret_cast<int2 *>(s_dyn) + w * GROUP_LIST;
+    uint32_t *s_bin = s_dyn + 2 * GROUP_LIST * GROUP_WAVES;
+    // the chain's counters; the two words this kernel itself reports through
+    // are stored by the last block alone
+    for (int i = blockIdx.x * GROUP_BLOCK + threadIdx.x; i < GC_COUNT; i += gridDim.x * GROUP_BLOCK)
+        if (i != GC_ERROR && i != GC_N_SORTED) E.gc[i] = 0u;
+    const int n_hits = E.desc[D_NHITS];
+    const uint32_t m0 = (uint32_t)min(part * per_part, n_mod);
+    const uint32_t n_m = (uint32_t)min(per_part, n_mod - (int)m0);   // modules of the range
+    const int n_bin = 2 * (int)n_m;
+    for (int k = threadIdx.x; k < n_bin; k += GROUP_BLOCK) s_bin[k] = 0u;
+    if (threadIdx.x == 0) s_before = s_bad = s_full = 0u;
+    __syncthreads();
+    uint32_t before = 0, own = 0;           // the wave's hits before the range, in it
+    auto mine = [&](int h, uint32_t dm, uint32_t s, bool in) {
+        const unsigned long long mk = __ballot(in);
+        if (!mk) return;
+        if (in) {
+            const int key = 2 * (int)dm + (int)s;
+            atomicAdd(&s_bin[key], 1u);
+            const uint32_t at = own + (uint32_t)__popcll(mk & lanes_below());
+            if (at < (uint32_t)GROUP_LIST) s_list[at] = make_int2(h, key);
+        }
+        own += (uint32_t)__popcll(mk);
+    };
+    uint32_t m_max = 0, s_bits = 0;
+    each_hit_id(E, n_hits, [&](int h, int32_t m, uint32_t s) {
+        const uint32_t um = (uint32_t)m;
+        m_max = um > m_max ? um : m_max;
+        s_bits |= s;
+        before += (uint32_t)__popcll(__ballot(um < m0));
+        mine(h, um - m0, s & 1u, um - m0 < n_m);
+    });
+    const bool odd = m_max >= (uint32_t)n_mod || s_bits > 1u;
+    uint32_t bad = 0;
+    if (__syncthreads_or(odd)) {
+        for (int k = threadIdx.x; k < n_bin; k += GROUP_BLOCK) s_bin[k] = 0u;
+        before = own = 0;
+        __syncthreads();
+        each_hit_id(E, n_hits, [&](int h, int32_t m, uint32_t s) {
+            const bool ok = (uint32_t)m < (uint32_t)n_mod && s <= 1u;
+            bad |= ok ? 0u : 1u;
+            before += (uint32_t)__popcll(__ballot(ok && (uint32_t)m < m0));
+            mine(h, (uint32_t)m - m0, s, ok && (uint32_t)m - m0 < n_m);
+        });
+    }
+    if (bad) s_bad = 1u;
+    // lanes past the hits of a last, partial group missed its counts
+    before = (uint32_t)__builtin_amdgcn_readfirstlane((int)before);
+    own = (uint32_t)__builtin_amdgcn_readfirstlane((int)own);
+    if (l == 0) {
+        atomicAdd(&s_before, before);
+        s_own[w] = own;
+        if (own > (uint32_t)GROUP_LIST) s_full = 1u;
+    }
+    __syncthreads();
+    // exclusive scan of the bins: consecutive bins per thread
+    const int per = (n_bin + GROUP_BLOCK - 1) / GROUP_BLOCK;
+    const int b0 = min((int)threadIdx.x * per, n_bin), b1 = min(b0 + per, n_bin);
+    uint32_t sum = 0;
+    for (int k = b0; k < b1; ++k) sum += s_bin[k];
+    const uint32_t incl = wave_incl_scan(sum);
+    if (l == 63) s_w[w] = incl;
+    __syncthreads();
+    uint32_t at = s_before + incl - sum;
+    for (int i = 0; i < w; ++i) at += s_w[i];
+    for (int k = b0; k < b1; ++k) {
+        const uint32_t c = s_bin[k];
+        E.boff[2 * m0 + k] = at;
+        s_bin[k] = at;      // next free position of the bin
+        at += c;
+    }
+    if (part == GROUP_PARTS - 1 && threadIdx.x == 0) {
+        uint32_t n = s_before;
+        for (int i = 0; i < GROUP_WAVES; ++i) n += s_own[i];
+        E.boff[2 * n_mod] = n;
+        E.gc[GC_N_SORTED] = n;
+        E.gc[GC_ERROR] = s_bad;
+    }
+    __syncthreads();
+    auto put = [&](int h, int key) {
+        const float x = E.x[h], y = E.y[h], z = E.z[h];
+        const uint32_t pos = atomicAdd(&s_bin[key], 1u);
+        if (E.half16)
+            E.hsort_h[pos] = half_hit(mod_frame(M, (int)m0 + (key >> 1)), x, y, z, h);
+        else
+            E.hsort[pos] = make_float4(x, y, z, __int_as_float(h));
+    };
+    if (!s_full) {
+        for (uint32_t i = l; i < own; i += 64) put(s_list[i].x, s_list[i].y);
+    } else {
+        each_hit_id(E, n_hits, [&](int h, int32_t m, uint32_t s) {
+            if ((uint32_t)m - m0 < n_m && s <= 1u) put(h, 2 * (m - (int)m0) + (int)s);
+        });
+    }
+}
+
+static size_t group_lds_bytes(int n_mod)
+{
+    return sizeof(int2) * GROUP_LIST * GROUP_WAVES + 2 * sizeof(uint32_t) * (size_t)group_mods(n_mod);
+}
+
+// no attribute call is needed up to here (one million modules)
+constexpr size_t GROUP_LDS_MAX = 64 * 1024;
+
 size_t sort_ev_lds_bytes(int n_mod)
 {
     return (size_t)((2 * n_mod + SORT_EV_PARTS - 1) / SORT_EV_PARTS) * sizeof(uint32_t);
@@ -576,6 +747,10 @@ hipError_t launch_sort(const EvDev &E, const ModDev &M, int grid, bool per_event
         hipLaunchKernelGGL(k_hist_ev, dim3(eg), dim3(SORT_EV_BLOCK), lds, s, E, M.n_mod);
         hipLaunchKernelGGL(k_scan, dim3(nb < 1024 ? nb : 1024), dim3(BLOCK), 0, s, E);
         hipLaunchKernelGGL(k_scatter_ev, dim3(eg), dim3(SORT_EV_BLOCK), lds, s, E, M);
+        return hipGetLastError();
+    }
+    if (E.cap_ev == 1 && group_lds_bytes(M.n_mod) <= GROUP_LDS_MAX) {
+        hipLaunchKernelGGL(k_group, dim3(GROUP_PARTS), dim3(GROUP_BLOCK), group_lds_bytes(M.n_mod), s, E, M);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_hist, dim3(grid), dim3(BLOCK), 0, s, E, M.n_mod);
