@@ -192,7 +192,7 @@ size_t carve(lst_ctx *c, char *base, const lst_caps &k, EvDev &E, void **zero_ba
     E.boff = cv.take<uint32_t>(keys + 1);
     E.hsort = cv.take<float4>(k.hits);
     E.hsort_h = cv.take<uint2>(k.hits);
-    E.hmin = cv.take<uint32_t>(k.hits);
+    E.hmin = cv.take<unsigned long long>(k.hits);
     E.htie = cv.take<int32_t>(k.hits);
     E.hslot = cv.take<int32_t>((size_t)k.hits * TIE_SLOTS);
     E.thead = cv.take<int32_t>(k.hits);

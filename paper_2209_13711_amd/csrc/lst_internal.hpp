@@ -91,9 +91,9 @@ struct EvDev {
     // (u, v) in binary16 (x: u | v << 16) and the per-event index (y)
     uint2 *hsort_h;
     int32_t half16;
-    uint32_t *hmin;          // dedup: smallest quintuplet score bits per sorted hit
-    int32_t *htie;           // dedup: how many quintuplets reach that score
-    int32_t *hslot;          // dedup: [n_hits][TIE_SLOTS] quintuplets reaching it
+    unsigned long long *hmin;  // dedup: smallest (quintuplet score bits, index) per sorted hit
+    int32_t *htie;           // dedup: entries of the hit's tie list
+    int32_t *hslot;          // dedup: [n_hits][TIE_SLOTS] the list's first entries
     int32_t *thead;          // dedup: per hit, 1 + first pool entry of further ties (0: none)
     int32_t *tpool_t5, *tpool_next;  // dedup tie pool: quintuplet, 1 + next entry
     uint32_t cap_tpool;

@@ -947,7 +947,7 @@ __device__ __forceinline__ void md_body(const EvDev &E, const ModDev &M, const C
             np = (up0 - lo0) * nup;
             // per-hit state of duplicate removal for this slot's hits (contiguous)
             for (uint32_t h = lo0 + gp.lane; h < up0 + nup; h += G) {
-                E.hmin[h] = 0xffffffffu;
+                E.hmin[h] = ~0ull;
                 E.htie[h] = 0;
                 E.thead[h] = 0;
             }
@@ -1697,15 +1697,40 @@ hipError_t launch_t5(const EvDev &E, const ModDev &M, const Consts &K, int grid,
 // ---------------------------------------------------------------- duplicate removal
 // A quintuplet survives iff for each of its hits it has the smallest key
 // (score, hit tuple) among the quintuplets using that hit.  Scores are
-// non-negative, so their bit patterns order like the floats.  Quintuplets
-// reaching a hit's minimum score are recorded in TIE_SLOTS per-hit slots:
-// exact score ties are common (two quintuplets that differ only in the
-// upper hit of one mini-doublet have the same anchors, hence the same
-// score) and are resolved by the hit tuple.  A quintuplet vetoed by the
-// learned scorer takes no part.
+// non-negative, so their bit patterns order like the floats.  Exact score
+// ties are common (two quintuplets that differ only in the upper hit of one
+// mini-doublet have the same anchors, hence the same score) and are resolved
+// by the hit tuple.  A quintuplet vetoed by the learned scorer takes no part.
+//
+// First pass: a 64-bit minimum per hit of (score, quintuplet index), whose
+// returned old value shows a tie with the minimum of the moment.  Whoever
+// sees one records itself in the hit's tie list, and the quintuplet it
+// displaces, if it does: so the list and the final minimum's index together
+// hold every quintuplet of the hit that reaches the final minimum.  (The first
+// to reach it recorded itself only if something tied with it was there, and is
+// the minimum's index until displaced.)  The list may also hold quintuplets
+// tied at an earlier, larger minimum, and some twice; the second pass looks at
+// the scores.  TIE_SLOTS entries are in the hit's own slots, further ones in a
+// pool.  One pass instead of two (minima, then ties against the final minima);
+// PU200-like event, all of duplicate removal, 7.2 + 5.1 + 5.2 -> 7.7 + 5.8 us;
+// 16 of them 36.5 + 19.8 + 24.5 -> 40.4 + 25.5 us.
 //
 // one thread per (quintuplet, hit); the hit indices are cached per
-// quintuplet ([t][10], sorted and per-event) for the two later passes
+// quintuplet ([t][10], sorted and per-event) for the later pass
+__device__ __forceinline__ void tie_record(const EvDev &E, int32_t h, int32_t t)
+{
+    const int k = atomicAdd(&E.htie[h], 1);
+    if (k < TIE_SLOTS) {
+        E.hslot[(size_t)h * TIE_SLOTS + k] = t;
+        return;
+    }
+    const uint32_t s = atomicAdd(&E.gc[GC_TIEPOOL], 1u);
+    if (s < E.cap_tpool) {
+        E.tpool_t5[s] = t;
+        E.tpool_next[s] = atomicExch(&E.thead[h], (int32_t)s + 1);
+    }
+}
+
 __device__ __forceinline__ void dedup_min_body(const EvDev &E, uint32_t *s_pre)
 {
     if (upstream_overflow(E)) return;
@@ -1714,33 +1739,16 @@ __device__ __forceinline__ void dedup_min_body(const EvDev &E, uint32_t *s_pre)
         const int32_t t = t5_at(E, s_pre, v / 10u);
         const int j = (int)(v % 10u);
         const int32_t h = t5_hit(E, t, j);
+        const uint32_t sc = __float_as_uint(E.t5_score[t]);
+        const bool veto = E.t5_veto[t] != 0;
+        unsigned long long old = ~0ull;
+        const unsigned long long key = ((unsigned long long)sc << 32) | (uint32_t)t;
+        if (!veto) old = atomicMin(&E.hmin[h], key);
         E.t5_hs[(size_t)t * 10 + j] = h;
         E.t5_ho[(size_t)t * 10 + j] = hit_orig(E, h);
-        if (E.t5_veto[t]) continue;
-        atomicMin(&E.hmin[h], __float_as_uint(E.t5_score[t]));
-    }
-}
-
-__device__ __forceinline__ void dedup_tie_body(const EvDev &E, uint32_t *s_pre)
-{
-    if (upstream_overflow(E)) return;
-    const uint32_t n = t5_prefix(E, s_pre) * 10u;
-    for (uint32_t v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-        const int32_t t = t5_at(E, s_pre, v / 10u);
-        if (E.t5_veto[t]) continue;
-        const int32_t h = E.t5_hs[(size_t)t * 10 + (v % 10u)];
-        if (E.hmin[h] == __float_as_uint(E.t5_score[t])) {
-            const int k = atomicAdd(&E.htie[h], 1);
-            if (k < TIE_SLOTS) {
-                E.hslot[(size_t)h * TIE_SLOTS + k] = t;
-            } else {
-                // further ties: push onto the hit's list in the pool
-                const uint32_t s = atomicAdd(&E.gc[GC_TIEPOOL], 1u);
-                if (s < E.cap_tpool) {
-                    E.tpool_t5[s] = t;
-                    E.tpool_next[s] = atomicExch(&E.thead[h], (int32_t)s + 1);
-                }
-            }
+        if (!veto && (uint32_t)(old >> 32) == sc && old != ~0ull) {
+            tie_record(E, h, t);
+            if (key < old) tie_record(E, h, (int32_t)(uint32_t)old);
         }
     }
 }
@@ -1756,10 +1764,10 @@ __device__ __forceinline__ bool tuple_less(const EvDev &E, int32_t u, const int3
         o[2 * k] = q.x;
         o[2 * k + 1] = q.y;
     }
+    bool less = false;   // decided from the last word to the first, without branches
 #pragma unroll
-    for (int j = 0; j < 10; ++j)
-        if (o[j] != own[j]) return o[j] < own[j];
-    return false;
+    for (int j = 9; j >= 0; --j) less = o[j] < own[j] || (o[j] == own[j] && less);
+    return less;
 }
 
 // one group of 16 lanes per quintuplet: lane j < 10 checks hit j, so the
@@ -1783,11 +1791,12 @@ __device__ __forceinline__ void dedup_keep_body(const EvDev &E, uint32_t *s_pre)
             veto = E.t5_veto[t] != 0;
         }
         if (v < n && gl < 10 && !veto) {
-            const float sc = E.t5_score[t];
+            const uint32_t sc = __float_as_uint(E.t5_score[t]);
             const int32_t h = E.t5_hs[(size_t)t * 10 + gl];
+            const unsigned long long mn = E.hmin[h];
             const int nt = E.htie[h];
-            bad = E.hmin[h] != __float_as_uint(sc);
-            if (!bad && nt > 1) {
+            bad = (uint32_t)(mn >> 32) != sc;
+            if (!bad && nt > 0) {
                 int32_t own[10];
                 const int2 *po = reinterpret_cast<const int2 *>(E.t5_ho + (size_t)t * 10);
 #pragma unroll
@@ -1796,26 +1805,49 @@ __device__ __forceinline__ void dedup_keep_body(const EvDev &E, uint32_t *s_pre)
                     own[2 * k] = b2.x;
                     own[2 * k + 1] = b2.y;
                 }
+                auto beats = [&](int32_t u) {
+                    return u != t && __float_as_uint(E.t5_score[u]) == sc && tuple_less(E, u, own);
+                };
+                // the minimum's own index, then the slots: indices, then
+                // scores in flight together
                 const int ns = nt < TIE_SLOTS ? nt : TIE_SLOTS;
-                int32_t us[TIE_SLOTS];
+                int32_t us[TIE_SLOTS + 1];
+                uint32_t su[TIE_SLOTS + 1];
+                us[TIE_SLOTS] = (int32_t)(uint32_t)mn;
 #pragma unroll
                 for (int k = 0; k < TIE_SLOTS; ++k)
                     us[k] = k < ns ? E.hslot[(size_t)h * TIE_SLOTS + k] : t;
 #pragma unroll
-                for (int k = 0; k < TIE_SLOTS; ++k)
-                    if (!bad && us[k] != t && tuple_less(E, us[k], own)) bad = true;
+                for (int k = 0; k <= TIE_SLOTS; ++k) su[k] = us[k] != t ? __float_as_uint(E.t5_score[us[k]]) : ~sc;
+                // the tied ones, each once; up to three are compared with
+                // their tuples in flight together (more are rare)
+                int32_t c0 = t, c1 = t, c2 = t;
+                int nc = 0;
+#pragma unroll
+                for (int k = TIE_SLOTS; k >= 0; --k)
+                    if (su[k] == sc && us[k] != c0 && us[k] != c1 && us[k] != c2) {
+                        c2 = c1;
+                        c1 = c0;
+                        c0 = us[k];
+                        ++nc;
+                    }
+                const int l0 = tuple_less(E, c0, own), l1 = tuple_less(E, c1, own), l2 = tuple_less(E, c2, own);
+                bad = (l0 | l1 | l2) != 0;
+                if (nc > 3) {
+#pragma unroll 1
+                    for (int k = 0; k < ns && !bad; ++k) bad = beats(E.hslot[(size_t)h * TIE_SLOTS + k]);
+                    if (!bad) bad = beats((int32_t)(uint32_t)mn);
+                }
                 if (!bad && nt > TIE_SLOTS) {
                     // further ties are chained in the pool
                     int listed = 0;
-                    for (int32_t e = E.thead[h]; e != 0 && !bad; e = E.tpool_next[e - 1], ++listed) {
-                        const int32_t u = E.tpool_t5[e - 1];
-                        if (u != t && tuple_less(E, u, own)) bad = true;
-                    }
+                    for (int32_t e = E.thead[h]; e != 0 && !bad; e = E.tpool_next[e - 1], ++listed)
+                        bad = beats(E.tpool_t5[e - 1]);
                     if (!bad && listed < nt - TIE_SLOTS) {
                         // the pool ran out: scan every quintuplet (correct, slow)
                         for (uint32_t q = 0; q < n && !bad; ++q) {
                             const int32_t u = t5_at(E, s_pre, q);
-                            if (u == t || E.t5_veto[u] || E.t5_score[u] != sc) continue;
+                            if (u == t || E.t5_veto[u] || __float_as_uint(E.t5_score[u]) != sc) continue;
                             bool uses = false;
                             for (int k = 0; k < 10; ++k) uses |= (E.t5_hs[(size_t)u * 10 + k] == h);
                             if (uses && tuple_less(E, u, own)) bad = true;
@@ -1836,12 +1868,6 @@ __global__ void k_dedup_min(EvDev E)
     dedup_min_body(E, s_pre);
 }
 
-__global__ void k_dedup_tie(EvDev E)
-{
-    __shared__ uint32_t s_pre[NSH + 1];
-    dedup_tie_body(E, s_pre);
-}
-
 __global__ void k_dedup_keep(EvDev E)
 {
     __shared__ uint32_t s_pre[NSH + 1];
@@ -1852,7 +1878,6 @@ hipError_t launch_dedup(const EvDev &E, const ModDev &M, int grid, hipStream_t s
 {
     (void)M;
     hipLaunchKernelGGL(k_dedup_min, dim3(grid), dim3(BLOCK), 0, s, E);
-    hipLaunchKernelGGL(k_dedup_tie, dim3(grid), dim3(BLOCK), 0, s, E);
     hipLaunchKernelGGL(k_dedup_keep, dim3(grid), dim3(BLOCK), 0, s, E);
     return hipGetLastError();
 }
@@ -2000,8 +2025,6 @@ __global__ __launch_bounds__(BLOCK) void k_chain(EvDev E, ModDev M, Consts K, ui
     if (stop == PERS_TO_T5) return;
     LST_SYNC();
     dedup_min_body(E, sm.pre);
-    LST_SYNC();
-    dedup_tie_body(E, sm.pre);
     LST_SYNC();
     dedup_keep_body(E, sm.pre);
 #undef LST_SYNC
