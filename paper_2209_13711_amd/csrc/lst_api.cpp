@@ -46,8 +46,9 @@ struct lst_ctx {
     // batch
     int n_events = 0;
     std::vector<int32_t> hit_off;
-    // pinned staging: batch descriptor, hit offsets, then (host inputs) x, y,
-    // z, module, sensor, so that every upload is a DMA from pinned memory
+    // pinned staging, laid out as the device's input region (descriptor, hit
+    // offsets, then x, y, z, module, sensor of host inputs), then room for a
+    // pixel batch: every upload is a DMA from pinned memory
     int32_t *stage_host = nullptr;
     size_t stage_cap = 0;   // bytes
     hipEvent_t stage_done = nullptr;
@@ -125,6 +126,24 @@ static void derive(const double *p, Consts &K)
 }
 
 // ---------------------------------------------------------------- arena
+// input region: [descriptor][offsets] then the hit arrays; the staging buffer
+// has the same layout, followed by room for a pixel batch
+static size_t stage_hits_offset(int64_t events)
+{
+    return ((sizeof(int32_t) * ((size_t)events + 1 + D_COUNT)) + 255) & ~(size_t)255;
+}
+
+static size_t stage_pixel_offset(const lst_caps &k)
+{
+    return (stage_hits_offset(k.events) + hits_bytes(k.hits) + 255) & ~(size_t)255;
+}
+
+static size_t stage_bytes(const lst_caps &k)
+{
+    return stage_pixel_offset(k) +
+           (k.seeds > 0 ? sizeof(int32_t) * px_pack_words(k.events, k.px_hits, k.seeds) : 0);
+}
+
 namespace {
 struct Carver {
     char *base;
@@ -160,7 +179,6 @@ size_t carve(lst_ctx *c, char *base, const lst_caps &k, EvDev &E, void **zero_ba
     E.cap_ev = k.events;
     E.cap_slots = (int32_t)slots;
     E.cap_keys = (int32_t)keys;
-    E.desc = cv.take<int32_t>(D_COUNT);
     E.bar = cv.take<uint32_t>(33 * 64);   // 33 barrier counters, one 256-byte line each
     E.rd_cnt = cv.take<uint32_t>(PACK_BLOCKS + 1);
     E.rd_part = cv.take<uint64_t>(count_part_size(c->n_mod, k.events));
@@ -180,13 +198,11 @@ size_t carve(lst_ctx *c, char *base, const lst_caps &k, EvDev &E, void **zero_ba
     size_t z1 = (cv.off + 255) & ~(size_t)255;
     if (zero_base) *zero_base = base ? base + z0 : nullptr;
     if (zero_bytes) *zero_bytes = z1 - z0;
-    // inputs
-    E.x = cv.take<float>(k.hits);
-    E.y = cv.take<float>(k.hits);
-    E.z = cv.take<float>(k.hits);
-    E.module = cv.take<int32_t>(k.hits);
-    E.sensor = cv.take<uint8_t>(k.hits);
-    E.hit_off = cv.take<int32_t>(k.events + 1);
+    // inputs: one region, as staged
+    char *in = cv.take<char>(stage_hits_offset(k.events) + hits_bytes(k.hits));
+    E.desc = (int32_t *)in;
+    E.hit_off = in ? (int32_t *)in + D_COUNT : nullptr;
+    E.hits = in ? in + stage_hits_offset(k.events) : nullptr;
     // grouping
     E.hrank = cv.take<uint32_t>(k.hits);
     E.boff = cv.take<uint32_t>(keys + 1);
@@ -255,6 +271,7 @@ size_t carve(lst_ctx *c, char *base, const lst_caps &k, EvDev &E, void **zero_ba
     E.cap_seeds = (int32_t)k.seeds;
     E.cap_pxc = (int32_t)k.px_cand;
     if (k.seeds > 0) {
+        E.px_pack = (char *)cv.take<int32_t>(px_pack_words(k.events, k.px_hits, k.seeds));
         E.px_x = cv.take<float>(k.px_hits);
         E.px_y = cv.take<float>(k.px_hits);
         E.px_z = cv.take<float>(k.px_hits);
@@ -327,17 +344,6 @@ static int sorted_orig(lst_ctx *c, std::vector<int32_t> &out, size_t n)
     if (rc) return rc;
     for (size_t i = 0; i < n; ++i) std::memcpy(&out[i], &h[i].w, sizeof(int32_t));
     return LST_OK;
-}
-
-// pinned staging layout: [descriptor][offsets] then the host hit arrays
-static size_t stage_hits_offset(int64_t events)
-{
-    return ((sizeof(int32_t) * ((size_t)events + 1 + D_COUNT)) + 255) & ~(size_t)255;
-}
-
-static size_t stage_bytes(int64_t events, int64_t hits)
-{
-    return stage_hits_offset(events) + (size_t)hits * (3 * sizeof(float) + sizeof(int32_t) + 1);
 }
 
 extern "C" {
@@ -592,7 +598,7 @@ int lst_attach_arena(lst_ctx *c, void *dev_ptr, size_t bytes, const lst_caps *ca
         HIPCHK(c, hipEventSynchronize(c->stage_done));
         c->stage_pending = false;
     }
-    const size_t want = stage_bytes(caps->events, caps->hits);
+    const size_t want = stage_bytes(*caps);
     if (c->stage_cap < want) {
         if (c->stage_host) HIPCHK(c, hipHostFree(c->stage_host));
         c->stage_host = nullptr;
@@ -625,6 +631,9 @@ int lst_attach_arena(lst_ctx *c, void *dev_ptr, size_t bytes, const lst_caps *ca
     return LST_OK;
 }
 
+// batches up to here go to the device as one copy (its host copy is short)
+constexpr size_t STAGE_WHOLE = 2 << 20;
+
 int lst_load_hits(lst_ctx *c, int32_t n_events, const int32_t *hit_offsets, const float *x,
                   const float *y, const float *z, const int32_t *module, const uint8_t *sensor,
                   int on_device, void *stream)
@@ -647,30 +656,6 @@ int lst_load_hits(lst_ctx *c, int32_t n_events, const int32_t *hit_offsets, cons
     EvDev &E = c->E;
     // the pinned buffer is reused: wait until the previous batch's copies have left it
     if (c->stage_pending) HIPCHK(c, hipEventSynchronize(c->stage_done));
-    if (n > 0 && on_device) {
-        HIPCHK(c, hipMemcpyAsync(E.x, x, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
-        HIPCHK(c, hipMemcpyAsync(E.y, y, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
-        HIPCHK(c, hipMemcpyAsync(E.z, z, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
-        HIPCHK(c, hipMemcpyAsync(E.module, module, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
-        HIPCHK(c, hipMemcpyAsync(E.sensor, sensor, n, hipMemcpyDeviceToDevice, s));
-    } else if (n > 0) {
-        // host arrays: one host copy into pinned memory, then DMA (a copy from
-        // pageable memory goes through the runtime's own staging, several
-        // times slower)
-        char *hp = (char *)c->stage_host + stage_hits_offset(c->caps.events);
-        const size_t nb = sizeof(float) * n;
-        char *px = hp, *py = px + nb, *pz = py + nb, *pm = pz + nb, *ps = pm + nb;
-        std::memcpy(px, x, nb);
-        std::memcpy(py, y, nb);
-        std::memcpy(pz, z, nb);
-        std::memcpy(pm, module, sizeof(int32_t) * n);
-        std::memcpy(ps, sensor, n);
-        HIPCHK(c, hipMemcpyAsync(E.x, px, nb, hipMemcpyHostToDevice, s));
-        HIPCHK(c, hipMemcpyAsync(E.y, py, nb, hipMemcpyHostToDevice, s));
-        HIPCHK(c, hipMemcpyAsync(E.z, pz, nb, hipMemcpyHostToDevice, s));
-        HIPCHK(c, hipMemcpyAsync(E.module, pm, sizeof(int32_t) * n, hipMemcpyHostToDevice, s));
-        HIPCHK(c, hipMemcpyAsync(E.sensor, ps, n, hipMemcpyHostToDevice, s));
-    }
     c->hit_off.assign(hit_offsets, hit_offsets + n_events + 1);
     int32_t *st = c->stage_host;
     st[D_NEV] = n_events;
@@ -681,9 +666,37 @@ int lst_load_hits(lst_ctx *c, int32_t n_events, const int32_t *hit_offsets, cons
     st[D_NSEEDS] = 0;
     c->px_loaded = false;
     std::memcpy(st + D_COUNT, hit_offsets, sizeof(int32_t) * (n_events + 1));
-    HIPCHK(c, hipMemcpyAsync((void *)E.desc, st, sizeof(int32_t) * D_COUNT, hipMemcpyHostToDevice, s));
-    HIPCHK(c, hipMemcpyAsync(E.hit_off, st + D_COUNT, sizeof(int32_t) * (n_events + 1),
-                             hipMemcpyHostToDevice, s));
+    const size_t head = stage_hits_offset(c->caps.events), head_used = sizeof(int32_t) * (D_COUNT + n_events + 1);
+    const HitsIn d = hits_at(E.hits, n);
+    if (n > 0 && !on_device) {
+        // host arrays: one host copy into pinned memory, then DMA (a copy from
+        // pageable memory goes through the runtime's own staging, several
+        // times slower).  A small batch goes as one DMA, a larger one array
+        // by array, each on its way while the next is copied here.
+        char *hp = (char *)st;
+        const HitsIn h = hits_at(hp + head, n);
+        const struct { void *to; const void *from; size_t bytes; } part[5] = {
+            {h.x, x, sizeof(float) * n}, {h.y, y, sizeof(float) * n}, {h.z, z, sizeof(float) * n},
+            {h.module, module, sizeof(int32_t) * n}, {h.sensor, sensor, (size_t)n}};
+        const bool whole = hits_bytes(n) <= STAGE_WHOLE;
+        size_t sent = 0;
+        for (int i = 0; i < 5; ++i) {
+            std::memcpy(part[i].to, part[i].from, part[i].bytes);
+            if (whole && i < 4) continue;
+            const size_t end = (char *)part[i].to + part[i].bytes - hp;
+            HIPCHK(c, hipMemcpyAsync((char *)E.desc + sent, hp + sent, end - sent, hipMemcpyHostToDevice, s));
+            sent = end;
+        }
+    } else {
+        if (n > 0) {
+            HIPCHK(c, hipMemcpyAsync(d.x, x, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
+            HIPCHK(c, hipMemcpyAsync(d.y, y, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
+            HIPCHK(c, hipMemcpyAsync(d.z, z, sizeof(float) * n, hipMemcpyDeviceToDevice, s));
+            HIPCHK(c, hipMemcpyAsync(d.module, module, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
+            HIPCHK(c, hipMemcpyAsync(d.sensor, sensor, n, hipMemcpyDeviceToDevice, s));
+        }
+        HIPCHK(c, hipMemcpyAsync((void *)E.desc, st, head_used, hipMemcpyHostToDevice, s));
+    }
     HIPCHK(c, hipEventRecord(c->stage_done, s));
     c->stage_pending = true;
     c->n_events = n_events;
@@ -716,40 +729,36 @@ int lst_load_pixel(lst_ctx *c, int32_t n_events, const int32_t *px_offsets, cons
                     (long long)c->caps.seeds);
     if ((n_px > 0 && (!x || !y || !z)) || (n_sd > 0 && !seeds))
         return fail(c, LST_E_INVALID, "null pixel array");
-    std::vector<int32_t> hits((size_t)n_sd * 4), ev((size_t)n_sd), loc((size_t)n_sd);
-    for (int e = 0; e < n_events; ++e)
-        for (int32_t q = seed_offsets[e]; q < seed_offsets[e + 1]; ++q) {
-            const int32_t n_e = px_offsets[e + 1] - px_offsets[e];
-            for (int k = 0; k < 4; ++k) {
-                const int32_t h = seeds[4 * (size_t)q + k];
-                if (h < 0 || h >= n_e)
-                    return fail(c, LST_E_INVALID, "seed %d of event %d: pixel hit %d outside 0..%d",
-                                q - seed_offsets[e], e, h, n_e - 1);
-                hits[4 * (size_t)q + k] = px_offsets[e] + h;
-            }
-            ev[q] = e;
-            loc[q] = q - seed_offsets[e];
-        }
+    for (int e = 0; e < n_events; ++e) {
+        const uint32_t n_e = (uint32_t)(px_offsets[e + 1] - px_offsets[e]);
+        for (int64_t k = 4 * (int64_t)seed_offsets[e]; k < 4 * (int64_t)seed_offsets[e + 1]; ++k)
+            if ((uint32_t)seeds[k] >= n_e)
+                return fail(c, LST_E_INVALID, "seed %lld of event %d: pixel hit %d outside 0..%d",
+                            (long long)(k / 4 - seed_offsets[e]), e, seeds[k], (int)n_e - 1);
+    }
     HIPCHK(c, hipSetDevice(c->device));
-    // the stream may still read the previous pixel batch: copy after it
-    HIPCHK(c, hipStreamSynchronize((hipStream_t)stream));
+    // packed into pinned memory, one copy, then a kernel lays the arrays out;
+    // both follow the stream's earlier work on the previous pixel batch
+    hipStream_t s = (hipStream_t)stream;
     const EvDev &E = c->E;
-    if (n_px > 0) {
-        HIPCHK(c, hipMemcpy(E.px_x, x, sizeof(float) * n_px, hipMemcpyHostToDevice));
-        HIPCHK(c, hipMemcpy(E.px_y, y, sizeof(float) * n_px, hipMemcpyHostToDevice));
-        HIPCHK(c, hipMemcpy(E.px_z, z, sizeof(float) * n_px, hipMemcpyHostToDevice));
-    }
-    if (n_sd > 0) {
-        HIPCHK(c, hipMemcpy(E.sd_hits, hits.data(), sizeof(int32_t) * hits.size(), hipMemcpyHostToDevice));
-        HIPCHK(c, hipMemcpy(E.sd_ev, ev.data(), sizeof(int32_t) * ev.size(), hipMemcpyHostToDevice));
-        HIPCHK(c, hipMemcpy(E.sd_local, loc.data(), sizeof(int32_t) * loc.size(), hipMemcpyHostToDevice));
-    }
-    if (E.px_off) {
-        HIPCHK(c, hipMemcpy(E.px_off, px_offsets, sizeof(int32_t) * (n_events + 1), hipMemcpyHostToDevice));
-        HIPCHK(c, hipMemcpy(E.sd_off, seed_offsets, sizeof(int32_t) * (n_events + 1), hipMemcpyHostToDevice));
-    }
-    const int32_t d[2] = {(int32_t)n_px, (int32_t)n_sd};
-    HIPCHK(c, hipMemcpy((void *)(E.desc + D_NPX), d, sizeof(d), hipMemcpyHostToDevice));
+    int32_t *const pack = (int32_t *)((char *)c->stage_host + stage_pixel_offset(c->caps));
+    int32_t *p = pack;
+    auto put = [&p](const void *from, size_t words) {
+        if (words) std::memcpy(p, from, words * sizeof(int32_t));
+        p += words;
+    };
+    *p++ = (int32_t)n_px;
+    *p++ = (int32_t)n_sd;
+    put(px_offsets, (size_t)n_events + 1);
+    put(seed_offsets, (size_t)n_events + 1);
+    put(x, (size_t)n_px);
+    put(y, (size_t)n_px);
+    put(z, (size_t)n_px);
+    put(seeds, (size_t)n_sd * 4);
+    HIPCHK(c, hipMemcpyAsync(E.px_pack, pack, (p - pack) * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    HIPCHK(c, launch_px_take(E, n_events, n_px, n_sd, s));
+    // complete on return: the pixel stage may run on another stream
+    HIPCHK(c, hipStreamSynchronize(s));
     c->px_off.assign(px_offsets, px_offsets + n_events + 1);
     c->sd_off.assign(seed_offsets, seed_offsets + n_events + 1);
     // pixel constants, each rounded once from the double parameters

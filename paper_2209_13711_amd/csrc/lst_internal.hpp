@@ -76,11 +76,11 @@ struct EvDev {
     int32_t cap_ev, cap_slots, cap_keys;
     int64_t cap_hits;
     uint32_t rc[OT_COUNT];           // region capacity per shard, per object type
-    // inputs as loaded
-    float *x, *y, *z;
-    int32_t *module;
-    uint8_t *sensor;
+    // inputs as loaded: descriptor, offsets and hit arrays are one region in
+    // the order of the host's staging buffer, so one copy brings a batch; the
+    // hit arrays follow each other at the batch's own size (hits_in)
     int32_t *hit_off;        // [n_ev + 1]
+    char *hits;
     // grouping of hits by key = 2 * slot + sensor
     uint32_t *bcnt;          // [n_keys]     (zero between chains: the scan clears what it reads)
     uint32_t *hrank;         // [cap_hits]   each input hit's rank in its bin (histogram atomics)
@@ -136,6 +136,7 @@ struct EvDev {
     // pixel objects: pixel hits and seeds of the batch (pLS), object
     // directions, per-event lists, link candidates, cross-cleaning state
     int32_t cap_px, cap_seeds, cap_pxc;
+    char *px_pack;                   // a pixel batch as the host sends it (k_px_take unpacks it)
     float *px_x, *px_y, *px_z;       // [cap_px]
     int32_t *px_off, *sd_off;        // [cap_ev + 1] first pixel hit / seed of each event
     int32_t *sd_hits;                // [cap_seeds][4] batch-wide pixel hit indices, inner to outer
@@ -168,6 +169,22 @@ struct EvDev {
     int2 *rd_src;                    // the same: source and index there
     uint64_t *rd_part;               // [count_part_size] per-block sums of the counts
 };
+
+// x, y, z, module, sensor of a batch of n hits in E.hits: each array starts
+// at a multiple of 64 elements (256 bytes)
+struct HitsIn {
+    float *x, *y, *z;
+    int32_t *module;
+    uint8_t *sensor;
+};
+__host__ __device__ inline size_t hits_stride(int64_t n) { return ((size_t)n + 63) & ~(size_t)63; }
+__host__ __device__ inline size_t hits_bytes(int64_t n) { return hits_stride(n) * 17; }
+__host__ __device__ inline HitsIn hits_at(char *base, int64_t n)
+{
+    const size_t r = hits_stride(n);
+    float *f = (float *)base;
+    return HitsIn{f, f + r, f + 2 * r, (int32_t *)(f + 3 * r), (uint8_t *)(f + 4 * r)};
+}
 
 constexpr int TIE_SLOTS = 8;
 constexpr int BLOCK = 256;           // 4 waves of 64
@@ -206,6 +223,13 @@ struct PixConsts {
     float wphi;   // azimuth half-range of the link window plus a margin (>= pi: all bins)
     float wdr;    // the same for the cross-cleaning closeness
 };
+// A pixel batch as it is sent: n_px, n_seeds, px_off[n_ev + 1], sd_off[n_ev + 1],
+// x, y, z [n_px], seeds [n_seeds][4], 4 bytes each
+inline size_t px_pack_words(int64_t n_ev, int64_t n_px, int64_t n_seeds)
+{
+    return 2 + 2 * ((size_t)n_ev + 1) + 3 * (size_t)n_px + 4 * (size_t)n_seeds;
+}
+hipError_t launch_px_take(const EvDev &E, int n_ev, int64_t n_px, int64_t n_seeds, hipStream_t s);
 hipError_t launch_pixel(const EvDev &E, const Consts &K, const PixConsts &P, hipStream_t s);
 // per-module capacity `cap` of object type `type` (lst_cap.hip): objects of
 // a module beyond it removed, the type's arrays compacted in place

@@ -265,11 +265,12 @@ __device__ __forceinline__ int event_of(const int32_t *off, int n_ev, int32_t h)
     return lo;
 }
 
-__device__ __forceinline__ int hit_key(const EvDev &E, int n_mod, int n_ev, int32_t h, int &ev)
+__device__ __forceinline__ int hit_key(const EvDev &E, const HitsIn &in, int n_mod, int n_ev, int32_t h,
+                                       int &ev)
 {
     ev = event_of(E.hit_off, n_ev, h);
-    int32_t m = E.module[h];
-    uint8_t s = E.sensor[h];
+    int32_t m = in.module[h];
+    uint8_t s = in.sensor[h];
     if (m < 0 || m >= n_mod || s > 1) return -1;
     return 2 * (ev * n_mod + m) + s;
 }
@@ -282,13 +283,14 @@ __device__ __forceinline__ int hit_key(const EvDev &E, int n_mod, int n_ev, int3
 __device__ __forceinline__ void hist_body(const EvDev &E, int n_mod)
 {
     const int n_ev = E.desc[D_NEV], n_hits = E.desc[D_NHITS];
+    const HitsIn in = hits_at(E.hits, n_hits);
     const int t0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
     for (int i = t0; i < GC_COUNT; i += stride) E.gc[i] = 0u;
     const int n_tiles = (E.cap_keys + 1 + SCAN_TILE - 1) / SCAN_TILE;
     for (int i = t0; i < n_tiles; i += stride) E.scan_st[i] = 0ull;
     for (int32_t h = t0; h < n_hits; h += stride) {
         int ev;
-        const int key = hit_key(E, n_mod, n_ev, h, ev);
+        const int key = hit_key(E, in, n_mod, n_ev, h, ev);
         if (key >= 0) E.hrank[h] = atomicAdd(&E.bcnt[key], 1u);
     }
 }
@@ -419,10 +421,11 @@ __device__ __forceinline__ void scatter_body(const EvDev &E, const ModDev &M)
 {
     const int n_mod = M.n_mod;
     const int n_ev = E.desc[D_NEV], n_hits = E.desc[D_NHITS];
+    const HitsIn in = hits_at(E.hits, n_hits);
     for (int32_t h = blockIdx.x * blockDim.x + threadIdx.x; h < n_hits;
          h += gridDim.x * blockDim.x) {
         int ev;
-        const int key = hit_key(E, n_mod, n_ev, h, ev);
+        const int key = hit_key(E, in, n_mod, n_ev, h, ev);
         if (key < 0) {
             atomicOr(&E.gc[GC_ERROR], 1u);
             continue;
@@ -435,9 +438,9 @@ __device__ __forceinline__ void scatter_body(const EvDev &E, const ModDev &M)
         // one 16-byte store per hit (scattered 4-byte stores cost a line each),
         // or one 8-byte record in half-precision storage
         if (E.half16)
-            E.hsort_h[pos] = half_hit(mod_frame(M, E.module[h]), E.x[h], E.y[h], E.z[h], h - E.hit_off[ev]);
+            E.hsort_h[pos] = half_hit(mod_frame(M, in.module[h]), in.x[h], in.y[h], in.z[h], h - E.hit_off[ev]);
         else
-            E.hsort[pos] = make_float4(E.x[h], E.y[h], E.z[h], __int_as_float(h - E.hit_off[ev]));
+            E.hsort[pos] = make_float4(in.x[h], in.y[h], in.z[h], __int_as_float(h - E.hit_off[ev]));
     }
 }
 
@@ -461,6 +464,7 @@ __device__ __forceinline__ int sort_ev_span(int nk) { return (nk + SORT_EV_PARTS
 __global__ __launch_bounds__(SORT_EV_BLOCK) void k_hist_ev(EvDev E, int n_mod)
 {
     extern __shared__ uint32_t s_bin[];     // [sort_ev_span(2 n_mod)]
+    const HitsIn in = hits_at(E.hits, E.desc[D_NHITS]);
     const int n_ev = E.desc[D_NEV], nk = 2 * n_mod, kp = sort_ev_span(nk);
     const int t0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
     for (int i = t0; i < GC_COUNT; i += stride) E.gc[i] = 0u;
@@ -479,8 +483,8 @@ __global__ __launch_bounds__(SORT_EV_BLOCK) void k_hist_ev(EvDev E, int n_mod)
 #pragma unroll
             for (int u = 0; u < SORT_EV_ILP; ++u) {
                 const int h = hb + u * (int)blockDim.x;
-                m[u] = h < h1 ? E.module[h] : -1;
-                sn[u] = h < h1 ? E.sensor[h] : 0;
+                m[u] = h < h1 ? in.module[h] : -1;
+                sn[u] = h < h1 ? in.sensor[h] : 0;
             }
 #pragma unroll
             for (int u = 0; u < SORT_EV_ILP; ++u) {
@@ -500,6 +504,7 @@ __global__ __launch_bounds__(SORT_EV_BLOCK) void k_scatter_ev(EvDev E, ModDev M)
 {
     const int n_mod = M.n_mod;
     extern __shared__ uint32_t s_cur[];     // next free slot of each bin of the range
+    const HitsIn in = hits_at(E.hits, E.desc[D_NHITS]);
     const int n_ev = E.desc[D_NEV], nk = 2 * n_mod, kp = sort_ev_span(nk);
     for (int item = blockIdx.x; item < n_ev * SORT_EV_PARTS; item += gridDim.x) {
         const int ev = item / SORT_EV_PARTS, part = item - ev * SORT_EV_PARTS, k0 = part * kp;
@@ -515,8 +520,8 @@ __global__ __launch_bounds__(SORT_EV_BLOCK) void k_scatter_ev(EvDev E, ModDev M)
                 const int h = hb + u * (int)blockDim.x;
                 key[u] = -1;
                 if (h < h1) {
-                    const int32_t m = E.module[h];
-                    const uint8_t sn = E.sensor[h];
+                    const int32_t m = in.module[h];
+                    const uint8_t sn = in.sensor[h];
                     if (m < 0 || m >= n_mod || sn > 1) {
                         if (part == 0) atomicOr(&E.gc[GC_ERROR], 1u);
                     } else {
@@ -529,7 +534,7 @@ __global__ __launch_bounds__(SORT_EV_BLOCK) void k_scatter_ev(EvDev E, ModDev M)
             for (int u = 0; u < SORT_EV_ILP; ++u) {
                 const int h = hb + u * (int)blockDim.x;
                 if (key[u] >= k0 && key[u] < k1)
-                    v[u] = make_float4(E.x[h], E.y[h], E.z[h], __int_as_float(h - h0));
+                    v[u] = make_float4(in.x[h], in.y[h], in.z[h], __int_as_float(h - h0));
             }
 #pragma unroll
             for (int u = 0; u < SORT_EV_ILP; ++u) {
@@ -579,10 +584,10 @@ __host__ __device__ __forceinline__ int group_mods(int n_mod) { return (n_mod + 
 // load of the module ids, the last one to three hits one per thread.  A
 // wave's active lanes are always its first ones.
 template <class F>
-__device__ __forceinline__ void each_hit_id(const EvDev &E, int n_hits, F &&f)
+__device__ __forceinline__ void each_hit_id(const HitsIn &in, int n_hits, F &&f)
 {
-    const int4 *mods = reinterpret_cast<const int4 *>(E.module);
-    const uint32_t *sens = reinterpret_cast<const uint32_t *>(E.sensor);
+    const int4 *mods = reinterpret_cast<const int4 *>(in.module);
+    const uint32_t *sens = reinterpret_cast<const uint32_t *>(in.sensor);
     const int n_g = n_hits >> 2, t = (int)threadIdx.x;
     for (int g0 = 0; g0 < n_g; g0 += GROUP_ILP * GROUP_BLOCK) {
         int4 m[GROUP_ILP];
@@ -607,7 +612,7 @@ __device__ __forceinline__ void each_hit_id(const EvDev &E, int n_hits, F &&f)
         }
     }
     const int h = 4 * n_g + t;
-    if (h < n_hits) f(h, E.module[h], (uint32_t)E.sensor[h]);
+    if (h < n_hits) f(h, in.module[h], (uint32_t)in.sensor[h]);
 }
 
 __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
@@ -623,6 +628,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
     for (int i = blockIdx.x * GROUP_BLOCK + threadIdx.x; i < GC_COUNT; i += gridDim.x * GROUP_BLOCK)
         if (i != GC_ERROR && i != GC_N_SORTED) E.gc[i] = 0u;
     const int n_hits = E.desc[D_NHITS];
+    const HitsIn in = hits_at(E.hits, n_hits);
     const uint32_t m0 = (uint32_t)min(part * per_part, n_mod);
     const uint32_t n_m = (uint32_t)min(per_part, n_mod - (int)m0);   // modules of the range
     const int n_bin = 2 * (int)n_m;
@@ -642,7 +648,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
         own += (uint32_t)__popcll(mk);
     };
     uint32_t m_max = 0, s_bits = 0;
-    each_hit_id(E, n_hits, [&](int h, int32_t m, uint32_t s) {
+    each_hit_id(in, n_hits, [&](int h, int32_t m, uint32_t s) {
         const uint32_t um = (uint32_t)m;
         m_max = um > m_max ? um : m_max;
         s_bits |= s;
@@ -655,7 +661,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
         for (int k = threadIdx.x; k < n_bin; k += GROUP_BLOCK) s_bin[k] = 0u;
         before = own = 0;
         __syncthreads();
-        each_hit_id(E, n_hits, [&](int h, int32_t m, uint32_t s) {
+        each_hit_id(in, n_hits, [&](int h, int32_t m, uint32_t s) {
             const bool ok = (uint32_t)m < (uint32_t)n_mod && s <= 1u;
             bad |= ok ? 0u : 1u;
             before += (uint32_t)__popcll(__ballot(ok && (uint32_t)m < m0));
@@ -697,7 +703,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
     }
     __syncthreads();
     auto put = [&](int h, int key) {
-        const float x = E.x[h], y = E.y[h], z = E.z[h];
+        const float x = in.x[h], y = in.y[h], z = in.z[h];
         const uint32_t pos = atomicAdd(&s_bin[key], 1u);
         if (E.half16)
             E.hsort_h[pos] = half_hit(mod_frame(M, (int)m0 + (key >> 1)), x, y, z, h);
@@ -707,7 +713,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
     if (!s_full) {
         for (uint32_t i = l; i < own; i += 64) put(s_list[i].x, s_list[i].y);
     } else {
-        each_hit_id(E, n_hits, [&](int h, int32_t m, uint32_t s) {
+        each_hit_id(in, n_hits, [&](int h, int32_t m, uint32_t s) {
             if ((uint32_t)m - m0 < n_m && s <= 1u) put(h, 2 * (m - (int)m0) + (int)s);
         });
     }

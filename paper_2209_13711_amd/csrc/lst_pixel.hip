@@ -142,6 +142,42 @@ struct EvRun {
     }
 };
 
+// ---------------------------------------------------------------- input
+// A pixel batch as sent (px_pack_words) into its arrays: hit indices made
+// batch-wide, each seed's event and its index there.
+__global__ __launch_bounds__(BLOCK) void k_px_take(EvDev E, int n_ev)
+{
+    const int32_t *p = (const int32_t *)E.px_pack;
+    const int n_px = p[0], n_sd = p[1];
+    const int32_t *px_off = p + 2, *sd_off = px_off + n_ev + 1;
+    const float *x = (const float *)(sd_off + n_ev + 1), *y = x + n_px, *z = y + n_px;
+    const int32_t *seeds = (const int32_t *)(z + n_px);
+    const int t0 = blockIdx.x * BLOCK + threadIdx.x, st = gridDim.x * BLOCK;
+    if (t0 == 0) {
+        ((int32_t *)E.desc)[D_NPX] = n_px;
+        ((int32_t *)E.desc)[D_NSEEDS] = n_sd;
+    }
+    for (int i = t0; i <= n_ev; i += st) {
+        E.px_off[i] = px_off[i];
+        E.sd_off[i] = sd_off[i];
+    }
+    for (int i = t0; i < n_px; i += st) {
+        E.px_x[i] = x[i];
+        E.px_y[i] = y[i];
+        E.px_z[i] = z[i];
+    }
+    for (int q = t0; q < n_sd; q += st) {
+        int lo = 0, hi = n_ev - 1;   // last event whose first seed is at or before q
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (sd_off[mid] <= q) lo = mid; else hi = mid - 1;
+        }
+        for (int k = 0; k < 4; ++k) E.sd_hits[4 * q + k] = px_off[lo] + seeds[4 * q + k];
+        E.sd_ev[q] = lo;
+        E.sd_local[q] = q - sd_off[lo];
+    }
+}
+
 // ---------------------------------------------------------------- setup
 // every per-event list count, the per-hit minima and flags, seed state and
 // direction
@@ -781,6 +817,13 @@ static int px_grid(int64_t work, int per_block)
     if (g < 1) g = 1;
     if (g > GRID_MAX) g = GRID_MAX;
     return (int)g;
+}
+
+hipError_t launch_px_take(const EvDev &E, int n_ev, int64_t n_px, int64_t n_seeds, hipStream_t s)
+{
+    const int grid = px_grid(std::max<int64_t>(std::max(n_px, n_seeds), n_ev + 1), BLOCK);
+    hipLaunchKernelGGL(k_px_take, dim3(grid), dim3(BLOCK), 0, s, E, n_ev);
+    return hipGetLastError();
 }
 
 hipError_t launch_pixel(const EvDev &E, const Consts &K, const PixConsts &P, hipStream_t s)

@@ -47,9 +47,12 @@ class lst_counts(ctypes.Structure):
                [("mlp_fallback", ctypes.c_int32)]
 
     def as_dict(self):
-        d = {n: getattr(self, n) for n, _ in self._fields_}
+        d = {n: getattr(self, n) for n in self._names}
         d["dropped"] = list(self.dropped)
         return d
+
+
+lst_counts._names = tuple(n for n, _ in lst_counts._fields_)
 
 
 class LSTError(RuntimeError):
@@ -60,6 +63,15 @@ class LSTError(RuntimeError):
 
 _lib = None
 _P = ctypes.c_void_p
+
+
+def _current_stream(device):
+    """handle of torch's current stream on `device`"""
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+# the same without building a Stream object, where torch offers it
+_current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _current_stream)
 _SIGS = {
     "lst_create": (ctypes.c_int, [ctypes.POINTER(_P), ctypes.c_int, _P, ctypes.c_int32]),
     "lst_destroy": (None, [_P]),
@@ -147,7 +159,8 @@ def load_library():
 
 
 def _np_ptr(a):
-    return a.ctypes.data_as(ctypes.c_void_p)
+    """address of an array's data (the caller keeps the array)"""
+    return a.__array_interface__["data"][0]
 
 
 def lst_build_map(params, geo_f32, geo_i32):
@@ -208,6 +221,7 @@ class Context:
         self.caps = None
         self.n_events = 0
         self._keep = []
+        self._rows_seen = {}   # per output: rows of the last read (sizes the next buffer)
 
     def __del__(self):
         if getattr(self, "h", None) is not None and self.lib is not None:
@@ -222,8 +236,8 @@ class Context:
     @staticmethod
     def _stream(stream):
         if stream is None:
-            stream = torch.cuda.current_stream()
-        return ctypes.c_void_p(stream.cuda_stream)
+            return _current_stream(torch.cuda.current_device())
+        return stream.cuda_stream
 
     # -- memory -------------------------------------------------------------
     def arena_bytes(self, caps: dict) -> int:
@@ -393,13 +407,9 @@ class Context:
         self._check(self.lib.lst_run_pixel(self.h, self._stream(stream)))
 
     def _rows(self, fn, width, *args, stream=None):
-        n = ctypes.c_int64(0)
-        rc = fn(self.h, *args, None, 0, ctypes.byref(n), self._stream(stream))
-        if rc not in (LST_OK, LST_E_CAPACITY):
-            self._check(rc)
-        out = np.zeros((max(n.value, 1), width), np.int32)
-        self._check(fn(self.h, *args, _np_ptr(out), n.value, ctypes.byref(n), self._stream(stream)))
-        return out[:n.value]
+        st = self._stream(stream)
+        return self._fetch((fn.__name__, args[1:]), lambda o, cap, n: fn(
+            self.h, *args, _np_ptr(o), cap, n, st), (width,), np.int32)
 
     def track_candidates(self, event, stream=None) -> np.ndarray:
         """[n, 12]: type, seed (-1 for T5), outer hits (-1 padded)"""
@@ -425,56 +435,49 @@ class Context:
         """test hook: OR error bits 1/2 into the device error word (lst_raise_error_flags)"""
         self._check(self.lib.lst_raise_error_flags(self.h, int(bits), self._stream(stream)))
 
-    def _hint(self, kind):
-        """rows an output of `kind` can hold at most: the arena's capacity"""
-        key = {LST_MD: "md", LST_SEG: "seg", LST_T3: "t3", LST_T5: "t5", LST_T5_KEPT: "t5"}[kind]
-        return int(self.caps.get(key, 0)) if self.caps else 0
-
-    def _fetch(self, call, shape, dtype, hint):
-        """One getter call into a buffer of `hint` rows (the getters copy the
-        device arrays on every call); a second call only when they do not
-        fit.  `call(out_ptr, cap, n)` returns the status."""
+    def _fetch(self, what, call, shape, dtype):
+        """One getter call into a buffer somewhat larger than the output was at
+        the last read of `what`; a second call only when the rows do not fit
+        (every call selects the rows again).  `call(out, cap, n)` returns the
+        status."""
         n = ctypes.c_int64(0)
-        out = np.empty((max(hint, 1),) + shape, dtype)
-        rc = call(_np_ptr(out), hint, n)
-        if rc == LST_E_CAPACITY and n.value > hint:
-            out = np.empty((n.value,) + shape, dtype)
-            rc = call(_np_ptr(out), n.value, n)
+        room = max(1024, self._rows_seen.get(what, 0) * 5 // 4)
+        out = np.empty((room,) + shape, dtype)
+        rc = call(out, room, ctypes.byref(n))
+        if rc == LST_E_CAPACITY and n.value > room:
+            room = n.value
+            out = np.empty((room,) + shape, dtype)
+            rc = call(out, room, ctypes.byref(n))
         self._check(rc)
+        self._rows_seen[what] = n.value
         return out[:n.value]
 
     def objects(self, event, kind, stream=None) -> np.ndarray:
         st = self._stream(stream)
-        return self._fetch(lambda o, cap, n: self.lib.lst_get_objects(
-            self.h, event, kind, o, cap, ctypes.byref(n), st), (WIDTH[kind],), np.int32,
-            self._hint(kind))
+        return self._fetch(kind, lambda o, cap, n: self.lib.lst_get_objects(
+            self.h, event, kind, _np_ptr(o), cap, n, st), (WIDTH[kind],), np.int32)
 
     def run_t5_features(self, stream=None):
         self._check(self.lib.lst_run_t5_features(self.h, self._stream(stream)))
 
-    def _features(self, fn, event, stream, kind):
+    def _features(self, fn, event, stream):
         st = self._stream(stream)
-        return self._fetch(lambda o, cap, n: fn(self.h, event, o, cap, ctypes.byref(n), st),
-                           (40,), np.float32, self._hint(kind))
+        return self._fetch(fn.__name__, lambda o, cap, n: fn(self.h, event, _np_ptr(o), cap, n, st),
+                           (40,), np.float32)
 
     def t5_features(self, event, stream=None) -> np.ndarray:
-        return self._features(self.lib.lst_get_t5_features, event, stream, LST_T5)
+        return self._features(self.lib.lst_get_t5_features, event, stream)
 
     def run_t3_features(self, stream=None):
         self._check(self.lib.lst_run_t3_features(self.h, self._stream(stream)))
 
     def t3_features(self, event, stream=None) -> np.ndarray:
-        return self._features(self.lib.lst_get_t3_features, event, stream, LST_T3)
+        return self._features(self.lib.lst_get_t3_features, event, stream)
 
     def t5_scores(self, event, stream=None) -> np.ndarray:
-        n = ctypes.c_int64(0)
-        rc = self.lib.lst_get_t5_scores(self.h, event, None, 0, ctypes.byref(n), self._stream(stream))
-        if rc not in (LST_OK, LST_E_CAPACITY):
-            self._check(rc)
-        out = np.zeros(max(n.value, 1), np.float32)
-        self._check(self.lib.lst_get_t5_scores(self.h, event, _np_ptr(out), n.value,
-                                               ctypes.byref(n), self._stream(stream)))
-        return out[:n.value]
+        st = self._stream(stream)
+        return self._fetch("t5_scores", lambda o, cap, n: self.lib.lst_get_t5_scores(
+            self.h, event, _np_ptr(o), cap, n, st), (), np.float32)
 
     # -- learned scorer -----------------------------------------------------
     def mlp_load(self, params, mean, istd, threshold=0.0, kind=LST_T5):
@@ -495,15 +498,14 @@ class Context:
         self._check(self.lib.lst_run_t3_score(self.h, self._stream(stream)))
 
     def _logits(self, fn, event, stream):
-        n = ctypes.c_int64(0)
-        rc = fn(self.h, event, None, None, 0, ctypes.byref(n), self._stream(stream))
-        if rc not in (LST_OK, LST_E_CAPACITY):
-            self._check(rc)
-        lg = np.zeros(max(n.value, 1), np.float32)
-        vt = np.zeros(max(n.value, 1), np.uint8)
-        self._check(fn(self.h, event, _np_ptr(lg), _np_ptr(vt), n.value, ctypes.byref(n),
-                       self._stream(stream)))
-        return lg[:n.value], vt[:n.value].astype(bool)
+        st = self._stream(stream)
+        veto = [np.empty(0, np.uint8)]
+
+        def call(o, cap, n):
+            veto[0] = np.empty(cap, np.uint8)
+            return fn(self.h, event, _np_ptr(o), _np_ptr(veto[0]), cap, n, st)
+        logits = self._fetch(fn.__name__, call, (), np.float32)
+        return logits, veto[0][:len(logits)].astype(bool)
 
     def t5_logits(self, event, stream=None):
         """(logits float32, veto bool) in lst_get_objects(LST_T5) order"""
@@ -517,7 +519,7 @@ class Context:
     @staticmethod
     def _dev(t, dtype):
         assert t.is_cuda and t.is_contiguous() and t.dtype == dtype, (t.dtype, dtype)
-        return ctypes.c_void_p(t.data_ptr())
+        return t.data_ptr()
 
     def mlp_workspace_bytes(self, n):
         return int(self.lib.lst_mlp_workspace_bytes(int(n)))
