@@ -429,8 +429,8 @@ int lst_get_t3_logits(lst_ctx *ctx, int32_t event, float *logits_host, uint8_t *
  * roundings unchanged.  Every sum runs in a fixed order, so results are
  * bit-for-bit reproducible. */
 
-/* device workspace lst_mlp_backward needs for n rows: 4 (n + 64 x
- * LST_MLP_NPARAM) bytes (per-row losses, partial gradients of up to 64 row
+/* device workspace lst_mlp_backward needs for n rows: 4 (n + 128 x
+ * LST_MLP_NPARAM) bytes (per-row losses, partial gradients of up to 128 row
  * chunks) */
 size_t lst_mlp_workspace_bytes(int64_t n);
 
@@ -454,7 +454,7 @@ int lst_mlp_backward(lst_ctx *ctx, const float *params, const uint16_t *x, const
 /* lst_mlp_backward without a workspace argument, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving or
  * training loops, harnesses that forbid allocation).  The workspace is a
- * fixed device array inside the library, one per GPU, 1.8 MB, held from the
+ * fixed device array inside the library, one per GPU, 3.5 MB, held from the
  * first lst_create on that GPU until the process ends; n at most 8192 rows
  * (else LST_E_CAPACITY, nothing launched).  The call allocates nothing and
  * gives the same results as lst_mlp_backward.  Every call on one GPU shares

@@ -295,11 +295,13 @@ hipError_t mlp_adam(float *P, const float *grad, float *m, float *v, float lr, f
 hipError_t mlp_train_step(float *P, const uint16_t *X, const uint8_t *y, int64_t n, float *work,
                           float *grad, float *loss, float *m, float *v, float lr, float b1, float b2,
                           float eps, float c1, float c2, hipStream_t s);
+// row chunks of the gradient sums at most: one 64-row batch each up to 8192 rows
+constexpr int MLP_GRAD_CHUNKS = 128;
 // fixed backward workspace (no allocation): rows it holds, its size in floats
-// (n loss rows + 64 chunks x MLP_NPARAM at n = MLP_FIXED_MAX_ROWS), and its
+// (n loss rows + the chunks x MLP_NPARAM at n = MLP_FIXED_MAX_ROWS), and its
 // device address on `device` (looked up once per device, then cached)
 constexpr int64_t MLP_FIXED_MAX_ROWS = 8192;
-constexpr size_t MLP_FIXED_SCRATCH_FLOATS = (size_t)MLP_FIXED_MAX_ROWS + (size_t)64 * MLP_NPARAM;
+constexpr size_t MLP_FIXED_SCRATCH_FLOATS = (size_t)MLP_FIXED_MAX_ROWS + (size_t)MLP_GRAD_CHUNKS * MLP_NPARAM;
 constexpr int MLP_FIXED_MAX_DEVICES = 64;
 hipError_t mlp_fixed_scratch(int device, void **out);
 // kind: OT_T3 or OT_T5

@@ -33,7 +33,7 @@ constexpr int LD = KP + 8;   // LDS row stride in BF16 elements (144 B: conflict
 constexpr int OFF_W1 = 0, OFF_B1 = NH * NIN, OFF_W2 = OFF_B1 + NH, OFF_B2 = OFF_W2 + NH * NH;
 constexpr int OFF_W3 = OFF_B2 + NH, OFF_B3 = OFF_W3 + NH, NPARAM = OFF_B3 + 1;
 static_assert(NPARAM == MLP_NPARAM, "parameter layout");
-constexpr int GRAD_CHUNKS = 64;   // row chunks of the gradient sums
+constexpr int GRAD_CHUNKS = MLP_GRAD_CHUNKS;   // most row chunks of the gradient sums
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -63,24 +63,24 @@ struct MlpW {
     float b3;
 };
 
-// Every kernel that stages the weights runs BLOCK threads: each thread loads
-// its WPT elements of each matrix before it converts them, so the loads are
-// in flight together rather than one after the other.
-constexpr int WPT = NH * KP / BLOCK;
-static_assert(NH * KP % BLOCK == 0 && NH * NH == NH * KP, "weight staging");
-
+// The weights staged by the block's NT threads: each thread loads its
+// elements of each matrix before it converts them, so the loads are in flight
+// together rather than one after the other.
+template <int NT>
 __device__ __forceinline__ void load_weights(const float *P, MlpW &w)
 {
+    static_assert(NH * KP % NT == 0 && NH * NH == NH * KP, "weight staging");
+    constexpr int WPT = NH * KP / NT;
     float a[WPT], b[WPT];
 #pragma unroll
     for (int u = 0; u < WPT; ++u) {
-        const int i = threadIdx.x + u * BLOCK, o = i / KP, k = i % KP;
+        const int i = threadIdx.x + u * NT, o = i / KP, k = i % KP;
         a[u] = k < NIN ? P[OFF_W1 + o * NIN + k] : 0.0f;
         b[u] = P[OFF_W2 + o * NH + k];
     }
 #pragma unroll
     for (int u = 0; u < WPT; ++u) {
-        const int i = threadIdx.x + u * BLOCK, o = i / KP, k = i % KP;
+        const int i = threadIdx.x + u * NT, o = i / KP, k = i % KP;
         w.w1[o][k] = k < NIN ? f2bf(a[u]) : (uint16_t)0;
         w.w2[o][k] = f2bf(b[u]);
     }
@@ -128,12 +128,10 @@ __device__ __forceinline__ void mfma_layer(const uint16_t (*A)[LD], const uint16
 // scratch tile.  Lanes with l%16 == 0 return the logits of rows
 // 4 (l/16) + r in logit[r].  If h1_out / h2_out are given, rows row0 + i < n
 // of the first (BF16, stride KP) and second (FP32, stride NH) hidden layers
-// are stored.  A and H are the calling wave's own tiles.  If h2v is given,
-// lane l receives the second hidden layer's units 16 nt + l%16 of rows
-// 4 (l/16) + r in h2v[nt][r], and every lane the logits of its rows.
+// are stored.  A and H are the calling wave's own tiles.
 __device__ __forceinline__ void mlp_tile(const MlpW &w, const uint16_t (*A)[LD], uint16_t (*H)[LD],
                                          float logit[4], uint16_t *h1_out, float *h2_out,
-                                         int64_t row0, int64_t n, float (*h2v)[4] = nullptr)
+                                         int64_t row0, int64_t n)
 {
     const int l = threadIdx.x & 63;
     const int col = l & 15, rq = 4 * (l >> 4);
@@ -160,7 +158,6 @@ __device__ __forceinline__ void mlp_tile(const MlpW &w, const uint16_t (*A)[LD],
             const float z = acc[nt][r] + w.b2[j];
             const float h2 = z > 0.0f ? z : 0.0f;
             if (h2_out && row0 + rq + r < n) h2_out[(row0 + rq + r) * NH + j] = h2;
-            if (h2v) h2v[nt][r] = h2;
             part[r] += h2 * w.w3[j];
         }
     // sum over the 16 lanes that hold one row's hidden units
@@ -188,7 +185,7 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_forward(const float *P, const uin
                                                        float *logits, uint16_t *h1, float *h2)
 {
     __shared__ SmFwd sm;
-    load_weights(P, sm.w);
+    load_weights<BLOCK>(P, sm.w);
     __syncthreads();   // weights staged
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     const int64_t tiles = (n + 15) / 16;
@@ -235,37 +232,53 @@ __global__ void k_mlp_prepare(const float *F, const float *mean, const float *is
 //   dW1 = dz1^T X, db1 = sum dz1, dW2 = dz2^T h1, db2 = sum dz2,
 //   dw3 = h2^T g, db3 = sum g.
 // The rows split into at most GRAD_CHUNKS chunks of whole 64-row batches,
-// one block per chunk.  In each batch a wave takes 16 rows: their forward
-// (FWD) or the stored logits and hidden layers, the row terms into LDS, and
-// dz1 as a 16 x 64 x 64 FP32 matrix product.  The block's waves then share
-// the 28 16 x 16 tiles of dW1 (64 x 48, inputs zero padded) and dW2
-// (64 x 64), each a product over the batch's 64 rows; their accumulators
-// stay in registers over the chunk's batches.  Products are FP32 matrix-core
-// steps (v_mfma_f32_16x16x4_f32: lane l supplies A[l%16][l/16] and
-// B[l/16][l%16], receives D rows 4 (l/16) + r, column l%16).  The vector
-// sums are kept per lane over its rows and combined in a fixed order at the
-// end.  A block writes its chunk's partial gradient; k_mlp_reduce adds the
-// chunks in chunk order.  Every sum runs in an order fixed by n alone, so the
-// gradient is bit-for-bit reproducible, and the forward-fused and the
-// stored-activation variants give the same bits.
-constexpr int RB = WAVES * 16;     // rows per batch of a block
-// row stride of the FP32 row-term tiles: the gradient products read 16
-// consecutive columns of 4 consecutive rows per instruction, which a stride
-// of 16 banks (mod 64) spreads over distinct banks
-constexpr int DS = NH + 16;
-constexpr int GT = 28;             // gradient tiles: 12 of dW1, 16 of dW2
-constexpr int GT_W = GT / WAVES;   // per wave
-static_assert(GT % WAVES == 0 && NIN <= 48, "gradient tiles");
+// one block of eight waves per chunk.  In each batch two waves share 16 rows,
+// each taking half of the hidden units: their forward (FWD) or the stored
+// logits and hidden layers, the row terms into LDS, and dz1 as 16 x 32 x 64
+// FP32 matrix products.  The waves then share the 28 16 x 16 tiles of dW1
+// (64 x 48, inputs zero padded) and dW2 (64 x 64), each a product over the
+// batch's 64 rows; their accumulators stay in registers over the chunk's
+// batches.  Products are FP32 matrix-core steps (v_mfma_f32_16x16x4_f32: lane
+// l supplies A[l%16][l/16] and B[l/16][l%16], receives D rows 4 (l/16) + r,
+// column l%16).  The vector sums are kept per lane over its rows and combined
+// in a fixed order at the end.  A block writes its chunk's partial gradient;
+// k_mlp_reduce adds the chunks in chunk order.  Every sum runs in an order
+// fixed by n alone, so the gradient is bit-for-bit reproducible, and the
+// forward-fused and the stored-activation variants give the same bits.
+//
+// Bounded by latency: at 4096 rows 64 blocks run one batch each, a chain of
+// loads, small products and barriers.  So eight waves rather than four (two
+// per SIMD: the products' and the tiles' chains halve), the batch's rows and
+// labels are loaded before the weights, and a row's sigmoid and loss are
+// computed once, by one lane.  4096 rows 17.7 -> 13.4 us, 5000 rows (79 blocks
+// of one batch instead of 40 of two) 29.0 -> 11.8 us.  Of the 13.4 us, weights
+// and rows to LDS take 2.7, the forward 2.1, the row terms 0.9, dz1 1.5, the
+// tiles 2.8 (their products alone 1.5), the partial sums 1.4.  Step-ordered
+// copies of the operands for 16-byte LDS reads made the tiles slower (5.8 us:
+// each BF16 operand converted right before its product).
+constexpr int GW = 8, GB = GW * 64;    // waves and threads of a block
+constexpr int RB = 64;                 // rows per batch of a block: 16 for each pair of waves
+constexpr int HT = 2;                  // 16-column tiles of the hidden layer per wave
+constexpr int GT = 28;                 // gradient tiles: 12 of dW1, 16 of dW2
+constexpr int GT_W = (GT + GW - 1) / GW;   // per wave at most
+// row strides of the FP32 row-term tiles: the gradient products read 16
+// consecutive columns of 4 consecutive rows per instruction, which a stride of
+// 16 banks (mod 64) spreads over distinct banks; dz1 reads 4 consecutive
+// columns of 16 rows, which takes a stride of 4 banks, so dz2 is kept in both
+constexpr int DS = NH + 16, DR = NH + 4;
+static_assert(NIN <= 48 && GB * 8 == RB * KP, "gradient tiles; one 16-byte load per thread stages a batch");
 
 struct SmGrad {
     MlpW w;
-    uint16_t x[WAVES][16][LD];     // inputs (BF16)
-    uint16_t h[WAVES][16][LD];     // first hidden layer (BF16)
-    float d2[WAVES][16][DS];       // dz2
-    float d1[WAVES][16][DS];       // dz1
-    float vs[WAVES][3][NH];        // the waves' db1, db2, dw3
-    float gs[WAVES];               // the waves' db3
+    uint16_t x[RB][LD];            // inputs (BF16)
+    uint16_t h[RB][LD];            // first hidden layer (BF16)
+    float d2[RB][DS], d2r[RB][DR]; // dz2
+    float d1[RB][DS];              // dz1; before that, logit terms of the upper hidden half
+    float g[RB], y[RB];            // row terms, labels
+    float vs[4][3][NH];            // the row groups' db1, db2, dw3
+    float gs[4];                   // the row groups' db3
 };
+static_assert(sizeof(float) * 4 * HT * 4 * 64 <= sizeof(float) * RB * DS, "logit terms fit d1");
 
 __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c)
 {
@@ -277,114 +290,196 @@ static void grad_chunks(int64_t n, int &nch, int64_t &clen)
 {
     int64_t b = (n + RB - 1) / RB;
     if (b < 1) b = 1;
-    nch = (int)(b < GRAD_CHUNKS ? b : GRAD_CHUNKS);
-    clen = (b + nch - 1) / nch * RB;
+    const int64_t per = (b + GRAD_CHUNKS - 1) / GRAD_CHUNKS;   // batches of a chunk
+    nch = (int)((b + per - 1) / per);
+    clen = per * RB;
+}
+
+// acc[i] = A(16 x 64) * W(16 columns from 16 (2 half + i))^T (mfma_layer's
+// products for one half of the hidden units)
+__device__ __forceinline__ void mfma_half(const uint16_t (*A)[LD], const uint16_t (*W)[LD], int half,
+                                          f32x4 acc[HT])
+{
+    const int l = threadIdx.x & 63;
+    const int row = l & 15, kq = 8 * (l >> 4);
+#pragma unroll
+    for (int i = 0; i < HT; ++i) acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int ks = 0; ks < KP / 32; ++ks) {
+        const bf16x8 a = load8(&A[row][32 * ks + kq]);
+#pragma unroll
+        for (int i = 0; i < HT; ++i) {
+            const bf16x8 b = load8(&W[16 * (HT * half + i) + row][32 * ks + kq]);
+            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[i], 0, 0, 0);
+        }
+    }
 }
 
 template <bool FWD>
-__global__ __launch_bounds__(BLOCK) void k_mlp_grad(const float *P, const uint16_t *X,
-                                                    const uint8_t *y, int64_t n, int64_t clen,
-                                                    const float *logits, const uint16_t *h1,
-                                                    const float *h2, float *loss_rows, float *part)
+__global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t *X, const uint8_t *y,
+                                                 int64_t n, int64_t clen, const float *logits,
+                                                 const uint16_t *h1, const float *h2, float *loss_rows,
+                                                 float *part)
 {
     __shared__ SmGrad sm;
-    load_weights(P, sm.w);
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int col = l & 15, q = l >> 4, rq = 4 * q;
+    const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+    const int rg = w & 3, half = w >> 2;             // 16-row group, half of the hidden units
+    const int col = l & 15, q = l >> 4, rq = 16 * rg + 4 * q;
     const int64_t r0 = (int64_t)blockIdx.x * clen;
     const int64_t r1 = r0 + clen < n ? r0 + clen : n;
+    // the batch's inputs (and stored first hidden layer), 16 bytes per thread,
+    // zero past the chunk; labels and stored logits one per thread
+    const int xr = tid >> 3, xc = (tid & 7) * 8;
+    uint4 xv, hv;
+    float yv = 0.0f, zv = 0.0f;
+    auto fetch = [&](int64_t b0) {
+        xv = hv = make_uint4(0u, 0u, 0u, 0u);
+        if (b0 + xr < r1) {
+            xv = *reinterpret_cast<const uint4 *>(&X[(b0 + xr) * KP + xc]);
+            if (!FWD) hv = *reinterpret_cast<const uint4 *>(&h1[(b0 + xr) * KP + xc]);
+        }
+        if (tid < RB) {
+            const bool live = b0 + tid < r1;
+            yv = live && y[b0 + tid] ? 1.0f : 0.0f;
+            if (!FWD) zv = live ? logits[b0 + tid] : 0.0f;
+        }
+    };
+    fetch(r0);
+    load_weights<GB>(P, sm.w);
     f32x4 acc[GT_W];
 #pragma unroll
     for (int i = 0; i < GT_W; ++i) acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    float sb1[4] = {0.0f, 0.0f, 0.0f, 0.0f}, sb2[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    float sw3[4] = {0.0f, 0.0f, 0.0f, 0.0f}, sg = 0.0f;
+    float sb1[HT] = {0.0f, 0.0f}, sb2[HT] = {0.0f, 0.0f}, sw3[HT] = {0.0f, 0.0f}, sg = 0.0f;
     // operands of the wave's gradient tiles: column 16 jt + l%16 of dz1 (dW1)
     // or dz2 (dW2) and column 16 kt + l%16 of the inputs or h1, at row 0
     const float *ta[GT_W];
     const uint16_t *tb[GT_W];
 #pragma unroll
     for (int i = 0; i < GT_W; ++i) {
-        const int t = w + WAVES * i;
+        const int t = w + GW * i < GT ? w + GW * i : GT - 1;
         const bool first = t < 12;
         const int jt = first ? t / 3 : (t - 12) / 4, kt = first ? t % 3 : (t - 12) % 4;
-        ta[i] = (first ? &sm.d1[0][0][0] : &sm.d2[0][0][0]) + 16 * jt + col;
-        tb[i] = (first ? &sm.x[0][0][0] : &sm.h[0][0][0]) + 16 * kt + col;
+        ta[i] = (first ? &sm.d1[0][0] : &sm.d2[0][0]) + 16 * jt + col;
+        tb[i] = (first ? &sm.x[0][0] : &sm.h[0][0]) + 16 * kt + col;
     }
-    __syncthreads();   // weights staged
+    float(*sp)[HT][4][64] = reinterpret_cast<float(*)[HT][4][64]>(&sm.d1[0][0]);
     for (int64_t b0 = r0; b0 < r1; b0 += RB) {
-        const int64_t row0 = b0 + 16 * w;
-        // the wave's 16 input rows (and stored first hidden layer), zero past the chunk
-        for (int i = l; i < 16 * (KP / 8); i += 64) {
-            const int r = i / (KP / 8), c8 = (i % (KP / 8)) * 8;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u), u = v;
-            if (row0 + r < r1) {
-                v = *reinterpret_cast<const uint4 *>(&X[(row0 + r) * KP + c8]);
-                if (!FWD) u = *reinterpret_cast<const uint4 *>(&h1[(row0 + r) * KP + c8]);
-            }
-            *reinterpret_cast<uint4 *>(&sm.x[w][r][c8]) = v;
-            if (!FWD) *reinterpret_cast<uint4 *>(&sm.h[w][r][c8]) = u;
+        *reinterpret_cast<uint4 *>(&sm.x[xr][xc]) = xv;
+        if (!FWD) *reinterpret_cast<uint4 *>(&sm.h[xr][xc]) = hv;
+        if (tid < RB) {
+            sm.y[tid] = yv;
+            if (!FWD) sm.g[tid] = zv;     // the row's logit until its row term replaces it
         }
-        wave_tile_sync();
-        float lg[4], h2v[4][4];
-        if (FWD) {
-            mlp_tile(sm.w, sm.x[w], sm.h[w], lg, nullptr, nullptr, row0, r1, h2v);
-        } else {
+        float h2v[HT][4];
+        if (!FWD) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int64_t row = row0 + rq + r;
-                const bool live = row < r1;
-                lg[r] = live ? logits[row] : 0.0f;
+                const int64_t row = b0 + rq + r;
 #pragma unroll
-                for (int nt = 0; nt < 4; ++nt) h2v[nt][r] = live ? h2[row * NH + 16 * nt + col] : 0.0f;
+                for (int i = 0; i < HT; ++i)
+                    h2v[i][r] = row < r1 ? h2[row * NH + 16 * (HT * half + i) + col] : 0.0f;
             }
         }
-        // row terms: g, the loss per row, dz2 (lane: units 16 nt + col of rows rq + r)
+        fetch(b0 + RB);                   // the next batch's rows arrive during this one
+        __syncthreads();                  // batch (and, first, weights) in LDS
+        float lg[4];
+        if (FWD) {
+            // the wave's hidden units; the lower half then adds both halves'
+            // terms of the logits in unit-tile order
+            f32x4 a[HT];
+            mfma_half(&sm.x[16 * rg], sm.w.w1, half, a);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t row = row0 + rq + r;
-            const bool live = row < r1;
-            const float z = lg[r];
-            const float yv = live && y[row] ? 1.0f : 0.0f;
-            const float gr = live ? (1.0f / (1.0f + expf(-z)) - yv) / (float)n : 0.0f;
-            if (live && col == 0)
-                loss_rows[row] = (z > 0.0f ? z : 0.0f) - z * yv + log1pf(expf(-fabsf(z)));
-            if (col == 0) sg += gr;
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const int j = 16 * nt + col;
-                const float dj = h2v[nt][r] > 0.0f ? gr * sm.w.w3[j] : 0.0f;
-                sm.d2[w][rq + r][j] = dj;
-                sb2[nt] += dj;
-                sw3[nt] += gr * h2v[nt][r];
-            }
-        }
-        wave_tile_sync();
-        // dz1 (16 x 64) = dz2 (16 x 64) W2 (64 x 64), masked where h1 is zero
-        {
-            f32x4 d[4];
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) d[nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int ks = 0; ks < NH / 4; ++ks) {
-                const float a = sm.d2[w][col][4 * ks + q];
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt)
-                    d[nt] = mfma_f32(a, bf2f(sm.w.w2[4 * ks + q][16 * nt + col]), d[nt]);
-            }
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
+            for (int i = 0; i < HT; ++i)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int j = 16 * nt + col;
-                    const float v = sm.h[w][rq + r][j] != 0 ? d[nt][r] : 0.0f;
-                    sm.d1[w][rq + r][j] = v;
-                    sb1[nt] += v;
+                    const int j = 16 * (HT * half + i) + col;
+                    const float z = a[i][r] + sm.w.b1[j];
+                    sm.h[rq + r][j] = f2bf(z > 0.0f ? z : 0.0f);
+                }
+            __syncthreads();              // both halves of the hidden layer
+            mfma_half(&sm.h[16 * rg], sm.w.w2, half, a);
+            float p[HT][4];
+#pragma unroll
+            for (int i = 0; i < HT; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int j = 16 * (HT * half + i) + col;
+                    const float z = a[i][r] + sm.w.b2[j];
+                    h2v[i][r] = z > 0.0f ? z : 0.0f;
+                    p[i][r] = h2v[i][r] * sm.w.w3[j];
+                    if (half) sp[rg][i][r][l] = p[i][r];
+                }
+            __syncthreads();              // the upper half's terms
+            if (!half) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float v = 0.0f;
+#pragma unroll
+                    for (int i = 0; i < HT; ++i) v += p[i][r];
+#pragma unroll
+                    for (int i = 0; i < HT; ++i) v += sp[rg][i][r][l];
+                    v += __shfl_xor(v, 8, 16);
+                    v += __shfl_xor(v, 4, 16);
+                    v += __shfl_xor(v, 2, 16);
+                    v += __shfl_xor(v, 1, 16);
+                    lg[r] = v + sm.w.b3;
+                }
+            }
+        }
+        // row terms: lane (q, r < 4) of the lower half takes row 4 q + r of
+        // the group: its loss and g
+        if (!half && col < 4) {
+            const int rl = rq + col;
+            const int64_t row = b0 + rl;
+            const float z = FWD ? (col == 0 ? lg[0] : col == 1 ? lg[1] : col == 2 ? lg[2] : lg[3]) : sm.g[rl];
+            const float t = sm.y[rl];
+            const bool live = row < r1;
+            sm.g[rl] = live ? (1.0f / (1.0f + expf(-z)) - t) / (float)n : 0.0f;
+            if (live) loss_rows[row] = (z > 0.0f ? z : 0.0f) - z * t + log1pf(expf(-fabsf(z)));
+        }
+        __syncthreads();                  // g
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float gr = sm.g[rq + r];
+            if (!half && col == 0) sg += gr;
+#pragma unroll
+            for (int i = 0; i < HT; ++i) {
+                const int j = 16 * (HT * half + i) + col;
+                const float dj = h2v[i][r] > 0.0f ? gr * sm.w.w3[j] : 0.0f;
+                sm.d2[rq + r][j] = dj;
+                sm.d2r[rq + r][j] = dj;
+                sb2[i] += dj;
+                sw3[i] += gr * h2v[i][r];
+            }
+        }
+        __syncthreads();                  // dz2 of both halves
+        // dz1 (16 x 32) = dz2 (16 x 64) W2 (64 x 32), masked where h1 is zero
+        {
+            f32x4 d[HT];
+#pragma unroll
+            for (int i = 0; i < HT; ++i) d[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int ks = 0; ks < NH / 4; ++ks) {
+                const float a = sm.d2r[16 * rg + col][4 * ks + q];
+#pragma unroll
+                for (int i = 0; i < HT; ++i)
+                    d[i] = mfma_f32(a, bf2f(sm.w.w2[4 * ks + q][16 * (HT * half + i) + col]), d[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < HT; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int j = 16 * (HT * half + i) + col;
+                    const float v = sm.h[rq + r][j] != 0 ? d[i][r] : 0.0f;
+                    sm.d1[rq + r][j] = v;
+                    sb1[i] += v;
                 }
         }
         __syncthreads();   // every wave's rows in LDS
-        // the wave's gradient tiles t = w + WAVES i over the batch's 64 rows,
+        // the wave's gradient tiles t = w + GW i over the batch's 64 rows,
         // four rows per step; the tiles' products of one step are independent
-#pragma unroll 2
+        // (the last waves' fourth tile is not stored)
+#pragma unroll 4
         for (int s = 0; s < RB / 4; ++s) {
             const int row = 4 * s + q;
 #pragma unroll
@@ -397,13 +492,14 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_grad(const float *P, const uint16
     float *pc = part + (int64_t)blockIdx.x * NPARAM;
 #pragma unroll
     for (int i = 0; i < GT_W; ++i) {
-        const int t = w + WAVES * i;
+        const int t = w + GW * i;
+        if (t >= GT) break;
         const bool first = t < 12;
         const int jt = first ? t / 3 : (t - 12) / 4, kt = first ? t % 3 : (t - 12) % 4;
         const int k = 16 * kt + col;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int j = 16 * jt + rq + r;
+            const int j = 16 * jt + 4 * q + r;
             if (first) {
                 if (k < NIN) pc[OFF_W1 + j * NIN + k] = acc[i][r];
             } else {
@@ -411,10 +507,10 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_grad(const float *P, const uint16
             }
         }
     }
-    // vector sums: the four row quarters of the wave, then the waves in order
+    // vector sums: the four row quarters of the group, then the groups in order
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        float a = sb1[nt], b = sb2[nt], c = sw3[nt];
+    for (int i = 0; i < HT; ++i) {
+        float a = sb1[i], b = sb2[i], c = sw3[i];
         a += __shfl_xor(a, 16, 64);
         b += __shfl_xor(b, 16, 64);
         c += __shfl_xor(c, 16, 64);
@@ -422,26 +518,26 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_grad(const float *P, const uint16
         b += __shfl_xor(b, 32, 64);
         c += __shfl_xor(c, 32, 64);
         if (q == 0) {
-            sm.vs[w][0][16 * nt + col] = a;
-            sm.vs[w][1][16 * nt + col] = b;
-            sm.vs[w][2][16 * nt + col] = c;
+            const int j = 16 * (HT * half + i) + col;
+            sm.vs[rg][0][j] = a;
+            sm.vs[rg][1][j] = b;
+            sm.vs[rg][2][j] = c;
         }
     }
     sg += __shfl_xor(sg, 16, 64);
     sg += __shfl_xor(sg, 32, 64);
-    if (l == 0) sm.gs[w] = sg;
+    if (!half && l == 0) sm.gs[rg] = sg;
     __syncthreads();
-    const int tid = threadIdx.x;
     if (tid < 3 * NH) {
         const int v = tid / NH, j = tid % NH;
         float a = 0.0f;
 #pragma unroll
-        for (int ww = 0; ww < WAVES; ++ww) a += sm.vs[ww][v][j];
+        for (int ww = 0; ww < 4; ++ww) a += sm.vs[ww][v][j];
         pc[(v == 0 ? OFF_B1 : v == 1 ? OFF_B2 : OFF_W3) + j] = a;
     } else if (tid == 3 * NH) {
         float a = 0.0f;
 #pragma unroll
-        for (int ww = 0; ww < WAVES; ++ww) a += sm.gs[ww];
+        for (int ww = 0; ww < 4; ++ww) a += sm.gs[ww];
         pc[OFF_B3] = a;
     }
 }
@@ -482,45 +578,73 @@ struct AdamArgs {
     float lr, b1, b2, eps, c1, c2;
 };
 
-__device__ __forceinline__ void adam_one(float *P, int p, float gr, const AdamArgs &a)
+__device__ __forceinline__ void adam_update(float &p, float &m, float &v, float gr, const AdamArgs &a)
 {
-    const float mp = a.b1 * a.m[p] + (1.0f - a.b1) * gr;
-    const float vp = a.b2 * a.v[p] + (1.0f - a.b2) * gr * gr;
-    a.m[p] = mp;
-    a.v[p] = vp;
-    P[p] -= a.lr * (mp / a.c1) / (sqrtf(vp / a.c2) + a.eps);
+    m = a.b1 * m + (1.0f - a.b1) * gr;
+    v = a.b2 * v + (1.0f - a.b2) * gr * gr;
+    p -= a.lr * (m / a.c1) / (sqrtf(v / a.c2) + a.eps);
 }
 
 __global__ void k_mlp_adam(float *P, const float *grad, AdamArgs a)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= NPARAM) return;
-    adam_one(P, p, grad[p], a);
+    float q = P[p], m = a.m[p], v = a.v[p];
+    adam_update(q, m, v, grad[p], a);
+    a.m[p] = m;
+    a.v[p] = v;
+    P[p] = q;
 }
 
 // The end of a backward pass in one launch: grad[p] is the sum of the
 // chunks' partials in chunk order, followed (ADAM) by the Adam update of
 // parameter p with the same operations as k_mlp_adam; the block past the
-// parameters takes the mean loss (loss_body).
+// parameters takes the mean loss (loss_body).  A block takes RD_P parameters:
+// its waves load a share of the chunks each, all in flight, into LDS, and one
+// wave adds them in order, its optimiser state loaded meanwhile.  Latency
+// bound (two loads deep): 4.1 us for 64 chunks, 4.6 us with one thread loading
+// all chunks of a parameter on 28 blocks and the optimiser state after the sum.
+constexpr int RD_P = 64;
+
 template <bool ADAM>
-__global__ void k_mlp_reduce(const float *part, int nch, float *grad, const float *loss_rows,
-                             int64_t n, float *loss, float *P, AdamArgs a)
+__global__ __launch_bounds__(BLOCK) void k_mlp_reduce(const float *part, int nch, float *grad,
+                                                      const float *loss_rows, int64_t n, float *loss,
+                                                      float *P, AdamArgs a)
 {
     if (blockIdx.x == gridDim.x - 1) {
         loss_body(loss_rows, n, loss);
         return;
     }
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= NPARAM) return;
-    float v[GRAD_CHUNKS];   // all chunks' partials in flight, then added in chunk order
+    __shared__ float s_v[GRAD_CHUNKS][RD_P];
+    constexpr int PER = GRAD_CHUNKS / WAVES;
+    const int w = threadIdx.x >> 6, l = threadIdx.x & 63, p = blockIdx.x * RD_P + l;
+    const bool live = p < NPARAM;
+    float m = 0.0f, v = 0.0f, q = 0.0f;
+    if (ADAM && w == 0 && live) {
+        m = a.m[p];
+        v = a.v[p];
+        q = P[p];
+    }
+    float t[PER];
 #pragma unroll
-    for (int c = 0; c < GRAD_CHUNKS; ++c) v[c] = c < nch ? part[c * NPARAM + p] : 0.0f;
+    for (int u = 0; u < PER; ++u) {
+        const int c = w + WAVES * u;
+        t[u] = live && c < nch ? part[(int64_t)c * NPARAM + p] : 0.0f;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) s_v[w + WAVES * u][l] = t[u];
+    __syncthreads();
+    if (w > 0 || !live) return;
     float acc = 0.0f;
-#pragma unroll
-    for (int c = 0; c < GRAD_CHUNKS; ++c)
-        if (c < nch) acc += v[c];
+#pragma unroll 8
+    for (int c = 0; c < nch; ++c) acc += s_v[c][l];
     grad[p] = acc;
-    if (ADAM) adam_one(P, p, acc, a);
+    if (ADAM) {
+        adam_update(q, m, v, acc, a);
+        a.m[p] = m;
+        a.v[p] = v;
+        P[p] = q;
+    }
 }
 
 // ---------------------------------------------------------------- scoring in the chain
@@ -547,7 +671,7 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_score(EvDev E, Consts K, const fl
     if (upstream_overflow(E)) return;
     const uint32_t n = obj_prefix(E, KIND, sm.pre);
     if (blockIdx.x * (WAVES * 64) >= n) return;   // no rows for this block
-    load_weights(P, sm.w);
+    load_weights<BLOCK>(P, sm.w);
     for (int i = threadIdx.x; i < NIN; i += blockDim.x) {
         sm.mean[i] = mean[i];
         sm.istd[i] = istd[i];
@@ -649,10 +773,10 @@ hipError_t mlp_backward(const float *P, const uint16_t *X, const uint8_t *y, int
     int nch;
     int64_t clen;
     grad_chunks(n, nch, clen);
-    hipLaunchKernelGGL(k_mlp_grad<false>, dim3(nch), dim3(BLOCK), 0, s, P, X, y, n, clen, logits, h1,
+    hipLaunchKernelGGL(k_mlp_grad<false>, dim3(nch), dim3(GB), 0, s, P, X, y, n, clen, logits, h1,
                        h2, lrow, part);
     // the chunk sums and the mean loss in one launch (the loss in the last block)
-    hipLaunchKernelGGL(k_mlp_reduce<false>, dim3((NPARAM + BLOCK - 1) / BLOCK + 1), dim3(BLOCK), 0, s,
+    hipLaunchKernelGGL(k_mlp_reduce<false>, dim3((NPARAM + RD_P - 1) / RD_P + 1), dim3(BLOCK), 0, s,
                        part, nch, grad, lrow, n, loss, nullptr, AdamArgs{});
     return hipGetLastError();
 }
@@ -669,9 +793,9 @@ hipError_t mlp_train_step(float *P, const uint16_t *X, const uint8_t *y, int64_t
     int nch;
     int64_t clen;
     grad_chunks(n, nch, clen);
-    hipLaunchKernelGGL(k_mlp_grad<true>, dim3(nch), dim3(BLOCK), 0, s, P, X, y, n, clen, nullptr,
+    hipLaunchKernelGGL(k_mlp_grad<true>, dim3(nch), dim3(GB), 0, s, P, X, y, n, clen, nullptr,
                        nullptr, nullptr, lrow, part);
-    hipLaunchKernelGGL(k_mlp_reduce<true>, dim3((NPARAM + BLOCK - 1) / BLOCK + 1), dim3(BLOCK), 0, s,
+    hipLaunchKernelGGL(k_mlp_reduce<true>, dim3((NPARAM + RD_P - 1) / RD_P + 1), dim3(BLOCK), 0, s,
                        part, nch, grad, lrow, n, loss, P, AdamArgs{m, v, lr, b1, b2, eps, c1, c2});
     return hipGetLastError();
 }
