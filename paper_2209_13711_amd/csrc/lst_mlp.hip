@@ -6,7 +6,10 @@
 // products (BF16 operands, FP32 accumulation), the first hidden layer is
 // rounded to BF16 (nearest, ties to even) before it feeds the second, and
 // the last layer is an FP32 dot product on the vector ALUs (N = 1 would
-// waste a matrix tile).  In the chain the 40 features of a quintuplet are
+// waste a matrix tile).  The products are taken as weights x candidates, so
+// a lane receives consecutive hidden units of one candidate, which is the
+// operand the next layer takes: nothing passes through LDS between layers.
+// In the chain the 40 features of a quintuplet are
 // computed in registers by the lane that owns it, standardised and written
 // straight into the LDS operand tile, so they never travel through HBM.
 //
@@ -21,7 +24,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "lst_access.hpp"
 #include "lst_cuts.hpp"
@@ -37,6 +42,10 @@ constexpr int GRAD_CHUNKS = MLP_GRAD_CHUNKS;   // most row chunks of the gradien
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// the caller's hidden-layer arrays are only aligned to their elements: wide
+// global accesses that the hardware takes at any address
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 
 // float -> BF16 bits, round to nearest even (a NaN stays a quiet NaN)
 __device__ __forceinline__ uint16_t f2bf(float f)
@@ -56,7 +65,7 @@ __device__ __forceinline__ bf16x8 load8(const uint16_t *p)
 }
 
 // Weights in LDS as BF16 [output unit][k] (K zero padded), the rest FP32.
-struct MlpW {
+struct alignas(16) MlpW {
     uint16_t w1[NH][LD];
     uint16_t w2[NH][LD];
     float b1[NH], b2[NH], w3[NH];
@@ -102,113 +111,146 @@ __device__ __forceinline__ void wave_tile_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// acc[nt] = A(16 x 64) * W(rows 16 nt .. 16 nt + 15)^T.  Operand layouts of
-// v_mfma_f32_16x16x32_bf16 on a wave64: lane l supplies row l%16 of A and
-// column l%16 of B, each with the eight k values 8 (l/16) .. +7 of the
-// 32-wide k step; lane l receives D rows 4 (l/16) + r, column l%16.
-__device__ __forceinline__ void mfma_layer(const uint16_t (*A)[LD], const uint16_t (*W)[LD],
-                                           f32x4 acc[4])
+// Operand layouts of v_mfma_f32_16x16x32_bf16 on a wave64: lane l supplies row
+// l%16 of A and column l%16 of B, each with the eight k values 8 (l/16) .. +7
+// of the 32-wide k step; lane l receives D rows 4 (l/16) + r, column l%16.
+// With A the weights (row = hidden unit) and B the candidates (column =
+// candidate), lane l receives units 16 nt + 4 (l/16) + r of candidate l%16.
+//
+// The second layer takes those units where they are: its k step ks holds the
+// units 32 ks .. 32 ks + 31, of which quarter q = l/16 supplies 4 q + j (j < 4)
+// and 16 + 4 q + j - 4 (j >= 4).  The order of k inside a step is free as long
+// as both operands agree, so its weights are read in that order.
+__device__ __forceinline__ bf16x8 layer2_k(const uint16_t *row, int ks, int q)
 {
-    const int l = threadIdx.x & 63;
-    const int row = l & 15, kq = 8 * (l >> 4);
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int ks = 0; ks < KP / 32; ++ks) {
-        const bf16x8 a = load8(&A[row][32 * ks + kq]);
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            const bf16x8 b = load8(&W[16 * nt + row][32 * ks + kq]);
-            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[nt], 0, 0, 0);
-        }
-    }
+    const uint2 a = *reinterpret_cast<const uint2 *>(row + 32 * ks + 4 * q);
+    const uint2 b = *reinterpret_cast<const uint2 *>(row + 32 * ks + 16 + 4 * q);
+    return __builtin_bit_cast(bf16x8, make_uint4(a.x, a.y, b.x, b.y));
 }
 
-// Forward of the 16 rows in A (wave-private), H a wave-private 16-row
-// scratch tile.  Lanes with l%16 == 0 return the logits of rows
-// 4 (l/16) + r in logit[r].  If h1_out / h2_out are given, rows row0 + i < n
-// of the first (BF16, stride KP) and second (FP32, stride NH) hidden layers
-// are stored.  A and H are the calling wave's own tiles.
-__device__ __forceinline__ void mlp_tile(const MlpW &w, const uint16_t (*A)[LD], uint16_t (*H)[LD],
-                                         float logit[4], uint16_t *h1_out, float *h2_out,
-                                         int64_t row0, int64_t n)
+// the weights as a wave's operands, kept over its tiles
+struct MlpOps {
+    bf16x8 w1[4][KP / 32], w2[4][KP / 32];
+};
+
+__device__ __forceinline__ MlpOps mlp_ops(const MlpW &w)
 {
-    const int l = threadIdx.x & 63;
-    const int col = l & 15, rq = 4 * (l >> 4);
+    const int l = threadIdx.x & 63, c = l & 15, q = l >> 4;
+    MlpOps o;
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+        for (int ks = 0; ks < KP / 32; ++ks) {
+            o.w1[nt][ks] = load8(&w.w1[16 * nt + c][32 * ks + 8 * q]);
+            o.w2[nt][ks] = layer2_k(w.w2[16 * nt + c], ks, q);
+        }
+    return o;
+}
+
+// ReLU of four hidden units as BF16 (8 bytes)
+__device__ __forceinline__ uint2 relu4(const f32x4 &a, const float4 &b)
+{
+    const float z[4] = {a[0] + b.x, a[1] + b.y, a[2] + b.z, a[3] + b.w};
+    uint32_t h[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) h[r] = f2bf(z[r] > 0.0f ? z[r] : 0.0f);
+    return make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+}
+
+// Forward of 16 candidates: x[ks] = inputs 32 ks + 8 q .. +7 of candidate l%16.
+// Every lane returns the logit of its candidate.  save(nt, h1, h2), when
+// given, receives the lane's units 16 nt + 4 q .. +3 of both hidden layers.
+// The logit adds a lane's 16 terms in order, then the four quarters'.
+template <class F>
+__device__ __forceinline__ float mlp_tile(const MlpW &w, const MlpOps &o, const bf16x8 x[KP / 32], F &&save)
+{
+    const int q = (threadIdx.x & 63) >> 4;
     f32x4 acc[4];
-    mfma_layer(A, w.w1, acc);
+    uint2 h[4];
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
+    for (int nt = 0; nt < 4; ++nt) {
+        acc[nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = 16 * nt + col;
-            const float z = acc[nt][r] + w.b1[j];
-            const uint16_t hb = f2bf(z > 0.0f ? z : 0.0f);
-            H[rq + r][j] = hb;
-            if (h1_out && row0 + rq + r < n) h1_out[(row0 + rq + r) * KP + j] = hb;
-        }
-    wave_tile_sync();
-    mfma_layer(H, w.w2, acc);
-    float part[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = 16 * nt + col;
-            const float z = acc[nt][r] + w.b2[j];
-            const float h2 = z > 0.0f ? z : 0.0f;
-            if (h2_out && row0 + rq + r < n) h2_out[(row0 + rq + r) * NH + j] = h2;
-            part[r] += h2 * w.w3[j];
-        }
-    // sum over the 16 lanes that hold one row's hidden units
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        float v = part[r];
-        v += __shfl_xor(v, 8, 16);
-        v += __shfl_xor(v, 4, 16);
-        v += __shfl_xor(v, 2, 16);
-        v += __shfl_xor(v, 1, 16);
-        logit[r] = v + w.b3;
+        for (int ks = 0; ks < KP / 32; ++ks)
+            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.w1[nt][ks], x[ks], acc[nt], 0, 0, 0);
     }
-    wave_tile_sync();   // H is reused by the next tile
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+        h[nt] = relu4(acc[nt], *reinterpret_cast<const float4 *>(&w.b1[16 * nt + 4 * q]));
+    bf16x8 hk[KP / 32];
+#pragma unroll
+    for (int ks = 0; ks < KP / 32; ++ks)
+        hk[ks] = __builtin_bit_cast(bf16x8, make_uint4(h[2 * ks].x, h[2 * ks].y, h[2 * ks + 1].x, h[2 * ks + 1].y));
+    float v = 0.0f;
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        acc[nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int ks = 0; ks < KP / 32; ++ks)
+            acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(o.w2[nt][ks], hk[ks], acc[nt], 0, 0, 0);
+    }
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+        const float4 b = *reinterpret_cast<const float4 *>(&w.b2[16 * nt + 4 * q]);
+        const float4 c = *reinterpret_cast<const float4 *>(&w.w3[16 * nt + 4 * q]);
+        const float z[4] = {acc[nt][0] + b.x, acc[nt][1] + b.y, acc[nt][2] + b.z, acc[nt][3] + b.w};
+        const float w3[4] = {c.x, c.y, c.z, c.w};
+        float h2[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            h2[r] = z[r] > 0.0f ? z[r] : 0.0f;
+            v += h2[r] * w3[r];
+        }
+        save(nt, h[nt], make_float4(h2[0], h2[1], h2[2], h2[3]));
+    }
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    return v + w.b3;
 }
 
 // ---------------------------------------------------------------- training forward
-struct SmFwd {
-    MlpW w;
-    uint16_t x[WAVES][16][LD];
-    uint16_t h[WAVES][16][LD];
-};
+// X: [n][KP] BF16 rows (features standardised, zero padded).  A wave takes
+// tiles of 16 rows, its operands straight from memory (a row is 128 bytes) and
+// the next tile's on their way; few blocks, so that staging the weights (27 KB
+// a block) is spread over many tiles.  FWD_TIMES
+constexpr int FWD_BLOCKS = 512;   // two per CU: what its registers allow
 
-// X: [n][KP] BF16 rows (features standardised, zero padded).
+template <bool SAVE>
 __global__ __launch_bounds__(BLOCK) void k_mlp_forward(const float *P, const uint16_t *X, int64_t n,
                                                        float *logits, uint16_t *h1, float *h2)
 {
-    __shared__ SmFwd sm;
-    load_weights<BLOCK>(P, sm.w);
-    __syncthreads();   // weights staged
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int64_t tiles = (n + 15) / 16;
-    for (int64_t base = (int64_t)blockIdx.x * WAVES; base < tiles; base += (int64_t)gridDim.x * WAVES) {
-        const int64_t tile = base + w;
-        const int64_t row0 = tile * 16;
-        const bool live = tile < tiles;
-        // stage the tile, 16 bytes per lane and step (rows beyond n are zero)
-        for (int i = l; i < 16 * (KP / 8); i += 64) {
-            const int r = i / (KP / 8), c8 = (i % (KP / 8)) * 8;
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (live && row0 + r < n) v = *reinterpret_cast<const uint4 *>(&X[(row0 + r) * KP + c8]);
-            *reinterpret_cast<uint4 *>(&sm.x[w][r][c8]) = v;
-        }
-        wave_tile_sync();
-        float lg[4];
-        mlp_tile(sm.w, sm.x[w], sm.h[w], lg, live ? h1 : nullptr, live ? h2 : nullptr, row0, n);
-        if ((l & 15) == 0 && live)
+    __shared__ MlpW w;
+    const int l = threadIdx.x & 63, c = l & 15, q = l >> 4;
+    const int64_t tiles = (n + 15) / 16, step = (int64_t)gridDim.x * WAVES;
+    const int64_t first = (int64_t)blockIdx.x * WAVES + (threadIdx.x >> 6);
+    bf16x8 next[KP / 32];
+    auto fetch = [&](int64_t tile) {
+        const int64_t row = tile * 16 + c;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t gr = row0 + 4 * (l >> 4) + r;
-                if (gr < n) logits[gr] = lg[r];
-            }
+        for (int ks = 0; ks < KP / 32; ++ks) {
+            uint4 v = make_uint4(0u, 0u, 0u, 0u);
+            if (row < n) v = *reinterpret_cast<const uint4 *>(&X[row * KP + 32 * ks + 8 * q]);
+            next[ks] = __builtin_bit_cast(bf16x8, v);
+        }
+    };
+    fetch(first);
+    load_weights<BLOCK>(P, w);
+    __syncthreads();   // weights staged
+    const MlpOps o = mlp_ops(w);
+    for (int64_t tile = first; tile < tiles; tile += step) {
+        bf16x8 x[KP / 32];
+#pragma unroll
+        for (int ks = 0; ks < KP / 32; ++ks) x[ks] = next[ks];
+        fetch(tile + step);
+        const int64_t row = tile * 16 + c;
+        const float z = mlp_tile(w, o, x, [&](int nt, const uint2 &a, const float4 &b) {
+            if (!SAVE || row >= n) return;
+            uint16_t *pa = h1 + row * KP + 16 * nt + 4 * q;
+            float *pb = h2 + row * NH + 16 * nt + 4 * q;
+            *reinterpret_cast<u32x2_any *>(pa) = u32x2_any{a.x, a.y};
+            *reinterpret_cast<f32x4_any *>(pb) = f32x4_any{b.x, b.y, b.z, b.w};
+        });
+        if (q == 0 && row < n) logits[row] = z;
     }
 }
 
@@ -222,6 +264,35 @@ __global__ void k_mlp_prepare(const float *F, const float *mean, const float *is
         const int64_t r = i / KP;
         const int k = (int)(i % KP);
         X[i] = k < NIN ? f2bf((F[r * NIN + k] - mean[k]) * istd[k]) : (uint16_t)0;
+    }
+}
+
+// the same for 16-byte aligned F and X: eight features per thread, always the
+// same eight (the grid's stride is a whole number of rows), so their constants
+// are read once.  Bounded by memory: PREP_TIMES
+__global__ __launch_bounds__(BLOCK) void k_mlp_prepare8(const float *F, const float *mean, const float *istd,
+                                                        int64_t n, uint16_t *X)
+{
+    const int k = (threadIdx.x & 7) * 8;
+    float m[8], s[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        m[i] = k < NIN ? mean[k + i] : 0.0f;
+        s[i] = k < NIN ? istd[k + i] : 0.0f;
+    }
+    const int64_t stride = (int64_t)gridDim.x * (BLOCK / 8);
+    for (int64_t r = (int64_t)blockIdx.x * (BLOCK / 8) + (threadIdx.x >> 3); r < n; r += stride) {
+        uint4 out = make_uint4(0u, 0u, 0u, 0u);
+        if (k < NIN) {
+            const float4 *p = reinterpret_cast<const float4 *>(&F[r * NIN + k]);
+            const float4 a = p[0], b = p[1];
+            const float f[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+            uint32_t u[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) u[i] = f2bf((f[i] - m[i]) * s[i]);
+            out = make_uint4(u[0] | (u[1] << 16), u[2] | (u[3] << 16), u[4] | (u[5] << 16), u[6] | (u[7] << 16));
+        }
+        *reinterpret_cast<uint4 *>(&X[r * KP + k]) = out;
     }
 }
 
@@ -268,7 +339,7 @@ constexpr int GT_W = (GT + GW - 1) / GW;   // per wave at most
 constexpr int DS = NH + 16, DR = NH + 4;
 static_assert(NIN <= 48 && GB * 8 == RB * KP, "gradient tiles; one 16-byte load per thread stages a batch");
 
-struct SmGrad {
+struct alignas(16) SmGrad {
     MlpW w;
     uint16_t x[RB][LD];            // inputs (BF16)
     uint16_t h[RB][LD];            // first hidden layer (BF16)
@@ -285,6 +356,20 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c)
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// lane 15 of each row of 16 lanes: the row's sum (DPP row_shr:1,2,4,8; lanes
+// outside a shift add zero)
+__device__ __forceinline__ float row_sum16(float v)
+{
+    auto shr = [](float x, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    v += shr(v, std::integral_constant<int, 0x111>{});
+    v += shr(v, std::integral_constant<int, 0x112>{});
+    v += shr(v, std::integral_constant<int, 0x114>{});
+    v += shr(v, std::integral_constant<int, 0x118>{});
+    return v;
+}
+
 // rows of the chunk c: [c clen, min((c + 1) clen, n)), clen a multiple of RB
 static void grad_chunks(int64_t n, int &nch, int64_t &clen)
 {
@@ -293,26 +378,6 @@ static void grad_chunks(int64_t n, int &nch, int64_t &clen)
     const int64_t per = (b + GRAD_CHUNKS - 1) / GRAD_CHUNKS;   // batches of a chunk
     nch = (int)((b + per - 1) / per);
     clen = per * RB;
-}
-
-// acc[i] = A(16 x 64) * W(16 columns from 16 (2 half + i))^T (mfma_layer's
-// products for one half of the hidden units)
-__device__ __forceinline__ void mfma_half(const uint16_t (*A)[LD], const uint16_t (*W)[LD], int half,
-                                          f32x4 acc[HT])
-{
-    const int l = threadIdx.x & 63;
-    const int row = l & 15, kq = 8 * (l >> 4);
-#pragma unroll
-    for (int i = 0; i < HT; ++i) acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int ks = 0; ks < KP / 32; ++ks) {
-        const bf16x8 a = load8(&A[row][32 * ks + kq]);
-#pragma unroll
-        for (int i = 0; i < HT; ++i) {
-            const bf16x8 b = load8(&W[16 * (HT * half + i) + row][32 * ks + kq]);
-            acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[i], 0, 0, 0);
-        }
-    }
 }
 
 template <bool FWD>
@@ -324,7 +389,7 @@ __global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t 
     __shared__ SmGrad sm;
     const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
     const int rg = w & 3, half = w >> 2;             // 16-row group, half of the hidden units
-    const int col = l & 15, q = l >> 4, rq = 16 * rg + 4 * q;
+    const int col = l & 15, q = l >> 4, rl = 16 * rg + col;   // the lane's row of the batch
     const int64_t r0 = (int64_t)blockIdx.x * clen;
     const int64_t r1 = r0 + clen < n ? r0 + clen : n;
     // the batch's inputs (and stored first hidden layer), 16 bytes per thread,
@@ -332,6 +397,8 @@ __global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t 
     const int xr = tid >> 3, xc = (tid & 7) * 8;
     uint4 xv, hv;
     float yv = 0.0f, zv = 0.0f;
+    f32x4 h2n[HT];                                   // the lane's row and units of the stored second layer
+    const int u0 = 16 * HT * half + 4 * q;           // the lane's first unit
     auto fetch = [&](int64_t b0) {
         xv = hv = make_uint4(0u, 0u, 0u, 0u);
         if (b0 + xr < r1) {
@@ -343,13 +410,22 @@ __global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t 
             yv = live && y[b0 + tid] ? 1.0f : 0.0f;
             if (!FWD) zv = live ? logits[b0 + tid] : 0.0f;
         }
+        if (!FWD)
+#pragma unroll
+            for (int i = 0; i < HT; ++i) {
+                h2n[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                if (b0 + rl < r1)
+                    h2n[i] = *reinterpret_cast<const f32x4_any *>(h2 + (b0 + rl) * NH + u0 + 16 * i);
+            }
     };
     fetch(r0);
     load_weights<GB>(P, sm.w);
     f32x4 acc[GT_W];
 #pragma unroll
     for (int i = 0; i < GT_W; ++i) acc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    float sb1[HT] = {0.0f, 0.0f}, sb2[HT] = {0.0f, 0.0f}, sw3[HT] = {0.0f, 0.0f}, sg = 0.0f;
+    // sums over rows: db1 of the lane's unit 16 (2 half + i) + l%16 (its dz1
+    // rows), db2 and dw3 of its units 16 (2 half + i) + 4 q + r (its row), db3
+    float sb1[HT] = {0.0f, 0.0f}, sb2[HT][4] = {}, sw3[HT][4] = {}, sg = 0.0f;
     // operands of the wave's gradient tiles: column 16 jt + l%16 of dz1 (dW1)
     // or dz2 (dW2) and column 16 kt + l%16 of the inputs or h1, at row 0
     const float *ta[GT_W];
@@ -362,7 +438,7 @@ __global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t 
         ta[i] = (first ? &sm.d1[0][0] : &sm.d2[0][0]) + 16 * jt + col;
         tb[i] = (first ? &sm.x[0][0] : &sm.h[0][0]) + 16 * kt + col;
     }
-    float(*sp)[HT][4][64] = reinterpret_cast<float(*)[HT][4][64]>(&sm.d1[0][0]);
+    float4(*sp)[HT][64] = reinterpret_cast<float4(*)[HT][64]>(&sm.d1[0][0]);
     for (int64_t b0 = r0; b0 < r1; b0 += RB) {
         *reinterpret_cast<uint4 *>(&sm.x[xr][xc]) = xv;
         if (!FWD) *reinterpret_cast<uint4 *>(&sm.h[xr][xc]) = hv;
@@ -371,85 +447,97 @@ __global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t 
             if (!FWD) sm.g[tid] = zv;     // the row's logit until its row term replaces it
         }
         float h2v[HT][4];
-        if (!FWD) {
+        if (!FWD)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int64_t row = b0 + rq + r;
+            for (int i = 0; i < HT; ++i)
 #pragma unroll
-                for (int i = 0; i < HT; ++i)
-                    h2v[i][r] = row < r1 ? h2[row * NH + 16 * (HT * half + i) + col] : 0.0f;
-            }
-        }
+                for (int r = 0; r < 4; ++r) h2v[i][r] = h2n[i][r];
         fetch(b0 + RB);                   // the next batch's rows arrive during this one
         __syncthreads();                  // batch (and, first, weights) in LDS
-        float lg[4];
+        float z = 0.0f;
         if (FWD) {
-            // the wave's hidden units; the lower half then adds both halves'
-            // terms of the logits in unit-tile order
+            // mlp_tile's products, each wave its half of the units; the lower
+            // half then adds both halves' terms of the logits in its order
             f32x4 a[HT];
-            mfma_half(&sm.x[16 * rg], sm.w.w1, half, a);
+#pragma unroll
+            for (int i = 0; i < HT; ++i) {
+                a[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int ks = 0; ks < KP / 32; ++ks)
+                    a[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        load8(&sm.w.w1[16 * (HT * half + i) + col][32 * ks + 8 * q]),
+                        load8(&sm.x[rl][32 * ks + 8 * q]), a[i], 0, 0, 0);
+            }
 #pragma unroll
             for (int i = 0; i < HT; ++i)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int j = 16 * (HT * half + i) + col;
-                    const float z = a[i][r] + sm.w.b1[j];
-                    sm.h[rq + r][j] = f2bf(z > 0.0f ? z : 0.0f);
-                }
+                *reinterpret_cast<uint2 *>(&sm.h[rl][u0 + 16 * i]) =
+                    relu4(a[i], *reinterpret_cast<const float4 *>(&sm.w.b1[u0 + 16 * i]));
             __syncthreads();              // both halves of the hidden layer
-            mfma_half(&sm.h[16 * rg], sm.w.w2, half, a);
             float p[HT][4];
 #pragma unroll
-            for (int i = 0; i < HT; ++i)
+            for (int i = 0; i < HT; ++i) {
+                a[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int ks = 0; ks < KP / 32; ++ks)
+                    a[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        layer2_k(sm.w.w2[16 * (HT * half + i) + col], ks, q), layer2_k(sm.h[rl], ks, q), a[i],
+                        0, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < HT; ++i) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int j = 16 * (HT * half + i) + col;
-                    const float z = a[i][r] + sm.w.b2[j];
-                    h2v[i][r] = z > 0.0f ? z : 0.0f;
-                    p[i][r] = h2v[i][r] * sm.w.w3[j];
-                    if (half) sp[rg][i][r][l] = p[i][r];
+                    const float s = a[i][r] + sm.w.b2[u0 + 16 * i + r];
+                    h2v[i][r] = s > 0.0f ? s : 0.0f;
+                    p[i][r] = h2v[i][r] * sm.w.w3[u0 + 16 * i + r];
                 }
+                if (half) sp[rg][i][l] = make_float4(p[i][0], p[i][1], p[i][2], p[i][3]);
+            }
             __syncthreads();              // the upper half's terms
             if (!half) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    float v = 0.0f;
+                for (int i = 0; i < HT; ++i)
 #pragma unroll
-                    for (int i = 0; i < HT; ++i) v += p[i][r];
+                    for (int r = 0; r < 4; ++r) z += p[i][r];
 #pragma unroll
-                    for (int i = 0; i < HT; ++i) v += sp[rg][i][r][l];
-                    v += __shfl_xor(v, 8, 16);
-                    v += __shfl_xor(v, 4, 16);
-                    v += __shfl_xor(v, 2, 16);
-                    v += __shfl_xor(v, 1, 16);
-                    lg[r] = v + sm.w.b3;
+                for (int i = 0; i < HT; ++i) {
+                    const float4 v = sp[rg][i][l];
+                    z += v.x;
+                    z += v.y;
+                    z += v.z;
+                    z += v.w;
                 }
+                z += __shfl_xor(z, 16, 64);
+                z += __shfl_xor(z, 32, 64);
+                z += sm.w.b3;
             }
         }
-        // row terms: lane (q, r < 4) of the lower half takes row 4 q + r of
-        // the group: its loss and g
-        if (!half && col < 4) {
-            const int rl = rq + col;
+        // row terms: the first quarter of the lower half takes the group's rows
+        if (!half && q == 0) {
             const int64_t row = b0 + rl;
-            const float z = FWD ? (col == 0 ? lg[0] : col == 1 ? lg[1] : col == 2 ? lg[2] : lg[3]) : sm.g[rl];
+            if (!FWD) z = sm.g[rl];
             const float t = sm.y[rl];
             const bool live = row < r1;
-            sm.g[rl] = live ? (1.0f / (1.0f + expf(-z)) - t) / (float)n : 0.0f;
+            const float gr = live ? (1.0f / (1.0f + expf(-z)) - t) / (float)n : 0.0f;
+            sm.g[rl] = gr;
+            sg += gr;
             if (live) loss_rows[row] = (z > 0.0f ? z : 0.0f) - z * t + log1pf(expf(-fabsf(z)));
         }
         __syncthreads();                  // g
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float gr = sm.g[rq + r];
-            if (!half && col == 0) sg += gr;
+        {
+            const float gr = sm.g[rl];
 #pragma unroll
             for (int i = 0; i < HT; ++i) {
-                const int j = 16 * (HT * half + i) + col;
-                const float dj = h2v[i][r] > 0.0f ? gr * sm.w.w3[j] : 0.0f;
-                sm.d2[rq + r][j] = dj;
-                sm.d2r[rq + r][j] = dj;
-                sb2[i] += dj;
-                sw3[i] += gr * h2v[i][r];
+                float dj[4];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    dj[r] = h2v[i][r] > 0.0f ? gr * sm.w.w3[u0 + 16 * i + r] : 0.0f;
+                    sb2[i][r] += dj[r];
+                    sw3[i][r] += gr * h2v[i][r];
+                }
+                const float4 v = make_float4(dj[0], dj[1], dj[2], dj[3]);
+                *reinterpret_cast<float4 *>(&sm.d2[rl][u0 + 16 * i]) = v;
+                *reinterpret_cast<float4 *>(&sm.d2r[rl][u0 + 16 * i]) = v;
             }
         }
         __syncthreads();                  // dz2 of both halves
@@ -460,7 +548,7 @@ __global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t 
             for (int i = 0; i < HT; ++i) d[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int ks = 0; ks < NH / 4; ++ks) {
-                const float a = sm.d2r[16 * rg + col][4 * ks + q];
+                const float a = sm.d2r[rl][4 * ks + q];
 #pragma unroll
                 for (int i = 0; i < HT; ++i)
                     d[i] = mfma_f32(a, bf2f(sm.w.w2[4 * ks + q][16 * (HT * half + i) + col]), d[i]);
@@ -469,9 +557,9 @@ __global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t 
             for (int i = 0; i < HT; ++i)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int j = 16 * (HT * half + i) + col;
-                    const float v = sm.h[rq + r][j] != 0 ? d[i][r] : 0.0f;
-                    sm.d1[rq + r][j] = v;
+                    const int j = 16 * (HT * half + i) + col, row = 16 * rg + 4 * q + r;
+                    const float v = sm.h[row][j] != 0 ? d[i][r] : 0.0f;
+                    sm.d1[row][j] = v;
                     sb1[i] += v;
                 }
         }
@@ -507,26 +595,24 @@ __global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t 
             }
         }
     }
-    // vector sums: the four row quarters of the group, then the groups in order
+    // vector sums: the group's 16 rows, then the groups in order
 #pragma unroll
     for (int i = 0; i < HT; ++i) {
-        float a = sb1[i], b = sb2[i], c = sw3[i];
+        float a = sb1[i];
         a += __shfl_xor(a, 16, 64);
-        b += __shfl_xor(b, 16, 64);
-        c += __shfl_xor(c, 16, 64);
         a += __shfl_xor(a, 32, 64);
-        b += __shfl_xor(b, 32, 64);
-        c += __shfl_xor(c, 32, 64);
-        if (q == 0) {
-            const int j = 16 * (HT * half + i) + col;
-            sm.vs[rg][0][j] = a;
-            sm.vs[rg][1][j] = b;
-            sm.vs[rg][2][j] = c;
+        if (q == 0) sm.vs[rg][0][16 * (HT * half + i) + col] = a;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float b = row_sum16(sb2[i][r]), c = row_sum16(sw3[i][r]);
+            if (col == 15) {
+                sm.vs[rg][1][u0 + 16 * i + r] = b;
+                sm.vs[rg][2][u0 + 16 * i + r] = c;
+            }
         }
     }
-    sg += __shfl_xor(sg, 16, 64);
-    sg += __shfl_xor(sg, 32, 64);
-    if (!half && l == 0) sm.gs[rg] = sg;
+    sg = row_sum16(sg);
+    if (!half && l == 15) sm.gs[rg] = sg;
     __syncthreads();
     if (tid < 3 * NH) {
         const int v = tid / NH, j = tid % NH;
@@ -648,11 +734,10 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_reduce(const float *part, int nch
 }
 
 // ---------------------------------------------------------------- scoring in the chain
-struct SmScore {
+struct alignas(16) SmScore {
     MlpW w;
     float mean[NIN], istd[NIN];
     uint16_t x[WAVES][64][LD];
-    uint16_t h[WAVES][16][LD];
     float logit[WAVES][64];
     uint32_t pre[NSH + 1];
 };
@@ -677,8 +762,11 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_score(EvDev E, Consts K, const fl
         sm.istd[i] = istd[i];
     }
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    for (int k = NIN; k < KP; ++k) sm.x[w][l][k] = 0;   // K padding, never rewritten
+#pragma unroll
+    for (int k = NIN; k < KP; k += 8)                   // K padding, never rewritten
+        *reinterpret_cast<uint4 *>(&sm.x[w][l][k]) = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
+    const MlpOps ops = mlp_ops(sm.w);
     for (uint32_t base = blockIdx.x * (WAVES * 64); base < n; base += gridDim.x * (WAVES * 64)) {
         const uint32_t v = base + w * 64 + l;
         const bool live = v < n;
@@ -705,19 +793,22 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_score(EvDev E, Consts K, const fl
             for (int k = 0; k < 40; ++k) f[k] = 0.0f;
         }
 #pragma unroll
-        for (int k = 0; k < NIN; k += 2) {
-            const uint32_t lo = f2bf((f[k] - sm.mean[k]) * sm.istd[k]);
-            const uint32_t hi = f2bf((f[k + 1] - sm.mean[k + 1]) * sm.istd[k + 1]);
-            *reinterpret_cast<uint32_t *>(&sm.x[w][l][k]) = lo | (hi << 16);
+        for (int k = 0; k < NIN; k += 8) {
+            uint32_t u[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) u[i] = f2bf((f[k + i] - sm.mean[k + i]) * sm.istd[k + i]);
+            *reinterpret_cast<uint4 *>(&sm.x[w][l][k]) = make_uint4(u[0] | (u[1] << 16), u[2] | (u[3] << 16),
+                                                                    u[4] | (u[5] << 16), u[6] | (u[7] << 16));
         }
         wave_tile_sync();
 #pragma unroll 1
         for (int sub = 0; sub < 4; ++sub) {
-            float lg[4];
-            mlp_tile(sm.w, &sm.x[w][16 * sub], sm.h[w], lg, nullptr, nullptr, 0, 0);
-            if ((l & 15) == 0)
+            bf16x8 x[KP / 32];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) sm.logit[w][16 * sub + 4 * (l >> 4) + r] = lg[r];
+            for (int ks = 0; ks < KP / 32; ++ks)
+                x[ks] = load8(&sm.x[w][16 * sub + (l & 15)][32 * ks + 8 * (l >> 4)]);
+            const float z = mlp_tile(sm.w, ops, x, [](int, const uint2 &, const float4 &) {});
+            if (l < 16) sm.logit[w][16 * sub + l] = z;
         }
         wave_tile_sync();
         if (live) {
@@ -752,16 +843,22 @@ size_t mlp_workspace_bytes(int64_t n)
 hipError_t mlp_prepare(const float *F, const float *mean, const float *istd, int64_t n, uint16_t *X,
                        hipStream_t s)
 {
-    hipLaunchKernelGGL(k_mlp_prepare, dim3(grid_of(n * KP, BLOCK)), dim3(BLOCK), 0, s, F, mean,
-                       istd, n, X);
+    if ((((uintptr_t)F | (uintptr_t)X) & 15) == 0)
+        hipLaunchKernelGGL(k_mlp_prepare8, dim3(grid_of(n * 8, BLOCK)), dim3(BLOCK), 0, s, F, mean, istd, n, X);
+    else
+        hipLaunchKernelGGL(k_mlp_prepare, dim3(grid_of(n * KP, BLOCK)), dim3(BLOCK), 0, s, F, mean,
+                           istd, n, X);
     return hipGetLastError();
 }
 
 hipError_t mlp_forward(const float *P, const uint16_t *X, int64_t n, float *logits, uint16_t *h1,
                        float *h2, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_mlp_forward, dim3(grid_of((n + 15) / 16, WAVES)), dim3(BLOCK), 0, s, P, X,
-                       n, logits, h1, h2);
+    const int grid = std::min(grid_of((n + 15) / 16, WAVES), FWD_BLOCKS);
+    if (h1)
+        hipLaunchKernelGGL(k_mlp_forward<true>, dim3(grid), dim3(BLOCK), 0, s, P, X, n, logits, h1, h2);
+    else
+        hipLaunchKernelGGL(k_mlp_forward<false>, dim3(grid), dim3(BLOCK), 0, s, P, X, n, logits, h1, h2);
     return hipGetLastError();
 }
 
