@@ -1372,11 +1372,11 @@ static int compute_counts(lst_ctx *c, hipStream_t stream)
 {
     const EvDev &E = c->E;
     const int n_ev = c->n_events;
-    int rc = res_reserve(c, std::max(n_ev * sizeof(EventSums), RES_FIRST));
+    int rc = res_reserve(c, std::max(read_counts_bytes(c->M, n_ev), RES_FIRST));
     if (rc) return rc;
     ReadHdr *h = (ReadHdr *)c->res_host;
-    const EventSums *sums = (const EventSums *)(c->res_host + RES_BODY);
-    HIPCHK(c, launch_read_counts(E, c->M, n_ev, c->stage, h, (EventSums *)sums, stream));
+    EventSums *sums = (EventSums *)(c->res_host + RES_BODY);
+    HIPCHK(c, launch_read_counts(E, c->M, n_ev, c->stage, h, sums, stream));
     if ((rc = sync_stream(c, stream))) return rc;
     c->counts.assign(n_ev, lst_counts{});
     for (int e = 0; e < n_ev; ++e) {
@@ -1408,6 +1408,7 @@ static int compute_counts(lst_ctx *c, hipStream_t stream)
         c->counts_valid = true;
         return LST_OK;
     }
+    finish_counts(c->M, n_ev, c->stage, sums);
     for (int e = 0; e < n_ev; ++e) {
         lst_counts &k = c->counts[e];
         const auto &q = sums[e].sum;

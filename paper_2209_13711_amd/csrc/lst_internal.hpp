@@ -266,8 +266,11 @@ struct EventSums {
     uint64_t sum[4][3];
 };
 size_t count_part_size(int n_mod, int n_events);
+size_t read_counts_bytes(const ModDev &M, int n_events);   // host room needed from `out` on
 hipError_t launch_read_counts(const EvDev &E, const ModDev &M, int n_events, int stage, ReadHdr *hdr,
                               EventSums *out, hipStream_t s);
+// once the stream is synchronised: the last addition, where the host does it
+void finish_counts(const ModDev &M, int n_events, int stage, EventSums *out);
 // stop: PERS_FULL runs every stage; PERS_TO_T5 ends after the quintuplets,
 // PERS_TO_T3 after the triplets (learned scoring follows as its own
 // launches); lanes: group width of its four object stages

@@ -13,8 +13,10 @@
 // What bounds them is latency.  One PU200-like event: its kept quintuplets
 // take 29 us from call to return (two launches of 5 and 7 us, the rest is
 // launching, waiting and the host's copy), 830 us with the arrays copied to
-// the host; its counts 30 us (7.5 and 6.8 us), 1,070 us before.  The kept
-// quintuplets of 16 such events: 0.73 ms, 365 ms before.
+// the host; its counts 24 us (9.1 us), 1,070 us before.  The kept quintuplets
+// of 16 such events: 0.42 ms, 365 ms before.  One launch for the rows, each
+// block waiting for the counts of those before it, took 10.2 us and gained
+// nothing over the two.
 #include <algorithm>
 
 #include "lst_access.hpp"
@@ -418,8 +420,10 @@ hipError_t launch_pack_pixel(const EvDev &E, const PackArgs &A, hipStream_t s)
 }
 
 // ---------------------------------------------------------------- counts
-// Sums per event, stored per block and added up by a second kernel (no
-// atomics on device memory, no clearing).  The grid has a part for the module slots
+// Sums per event, stored per block (no atomics on device memory, no clearing)
+// and added up by a second kernel, or, for one event, by the host (23 KB: 2.5
+// us less than the launch; 0.3 MB for 16 events: 100 us more).  The grid has a
+// part for the module slots
 // (candidates and number of mini-doublets, candidate segments: four threads
 // per slot share its map edges) and one for each kind of stored object, one
 // thread per object: its event, and the candidates it is the first half of
@@ -520,9 +524,10 @@ __device__ __forceinline__ void obj_counts(const EvDev &E, int n_mod, int n_ev, 
 }
 
 __global__ __launch_bounds__(BLOCK) void k_read_counts(EvDev E, ModDev M, int n_ev, int stage,
-                                                       uint32_t n_slot_blocks, uint32_t n_obj_blocks)
+                                                       uint32_t n_slot_blocks, uint32_t n_obj_blocks,
+                                                       ReadHdr *hdr, uint64_t *part)
 {
-    uint64_t *part = E.rd_part;
+    if (hdr && blockIdx.x == 0 && blockIdx.y == 0) put_header(E, hdr);
     if (upstream_overflow(E)) return;
     if (blockIdx.x < n_slot_blocks) {
         if (blockIdx.y == 0) slot_counts(E, M, stage, part);
@@ -588,17 +593,39 @@ size_t count_part_size(int n_mod, int n_events)
     return (slots + 3 * std::max<size_t>(4096, 32 * (size_t)n_events)) * RC_OBJ;
 }
 
+static int counted_kinds(int stage) { return stage >= 6 ? 3 : stage >= 5 ? 2 : stage >= 4 ? 1 : 0; }
+
 hipError_t launch_read_counts(const EvDev &E, const ModDev &M, int n_events, int stage, ReadHdr *hdr,
                               EventSums *out, hipStream_t s)
 {
     const uint32_t slots = (uint32_t)n_events * ((M.n_mod + RC_SLOTS - 1) / RC_SLOTS);
     const uint32_t obj = count_obj_blocks(n_events);
-    const int kinds = stage >= 6 ? 3 : stage >= 5 ? 2 : stage >= 4 ? 1 : 0;
+    const int kinds = counted_kinds(stage);
     const dim3 grid(slots + kinds * obj, (n_events + RC_EVENTS - 1) / RC_EVENTS);
-    hipLaunchKernelGGL(k_read_counts, grid, dim3(BLOCK), 0, s, E, M, n_events, stage, slots, obj);
-    hipLaunchKernelGGL(k_add_counts, dim3(n_events), dim3(BLOCK), 0, s, E, n_events, kinds, slots, obj,
-                       hdr, out);
+    const bool one = n_events == 1;   // the blocks' sums follow the event's in the host buffer
+    hipLaunchKernelGGL(k_read_counts, grid, dim3(BLOCK), 0, s, E, M, n_events, stage, slots, obj,
+                       one ? hdr : nullptr, one ? (uint64_t *)(out + 1) : E.rd_part);
+    if (!one)
+        hipLaunchKernelGGL(k_add_counts, dim3(n_events), dim3(BLOCK), 0, s, E, n_events, kinds, slots, obj,
+                           hdr, out);
     return hipGetLastError();
+}
+
+void finish_counts(const ModDev &M, int n_events, int stage, EventSums *out)
+{
+    if (n_events != 1) return;
+    const uint32_t slots = (M.n_mod + RC_SLOTS - 1) / RC_SLOTS, obj = count_obj_blocks(1);
+    const uint64_t *part = (const uint64_t *)(out + 1);
+    *out = EventSums{};
+    for (int k = 0; k <= counted_kinds(stage); ++k)
+        for (uint32_t b = 0; b < (k ? obj : slots); ++b, part += RC_OBJ)
+            for (int j = 0; j < RC_OBJ; ++j) out->sum[k][j] += part[j];
+}
+
+size_t read_counts_bytes(const ModDev &M, int n_events)
+{
+    return n_events * sizeof(EventSums) +
+           (n_events == 1 ? sizeof(uint64_t) * count_part_size(M.n_mod, 1) : 0);
 }
 
 }  // namespace lst
