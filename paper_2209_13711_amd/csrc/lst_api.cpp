@@ -537,8 +537,15 @@ int lst_get_map(lst_ctx *c, int32_t *row_ptr, int32_t *col, int64_t cap_col, int
 
 static int clamp_grid(int64_t g) { return (int)std::max<int64_t>(1, std::min<int64_t>(g, 65535)); }
 
-// Launch shapes before tuning: one wave per work item up to 2048 blocks.
-// launch shape before tuning: the best measured on a PU200-like event
+// Launch shape before tuning.  One event: the best measured on a PU200-like
+// event (no other shape gained more than 3 us on 30 to 4000 tracks).  Several
+// events: twice to four times the blocks and narrower groups, since a wave of
+// few blocks takes many inner objects in turn and the waves with the dense
+// modules finish last.  Chain of 16 PU200-like events 578 -> 447 us, 24 uneven
+// ones 827 -> 704, three stress events 664 -> 489 (triplets 221 -> 98), ten
+// small uneven ones 119 -> 101, two of 100 tracks 59 -> 56.  Groups of 8 lanes
+// gain more on some (segments of the uneven batch) and lose on others
+// (mini-doublets there: 193 us more).
 static void default_tuning(lst_ctx *c)
 {
     Tuning &t = c->tune;
@@ -553,6 +560,13 @@ static void default_tuning(lst_ctx *c)
     t.lanes[ST_SEG] = 32;
     t.lanes[ST_T3] = 32;
     t.lanes[ST_T5] = 16;
+    if (c->caps.events > 1) {
+        t.grid[ST_MD] = 2 * GRID_MAX;
+        t.grid[ST_SEG] = 4 * GRID_MAX;
+        t.grid[ST_T3] = 4 * GRID_MAX;
+        t.grid[ST_DEDUP] = GRID_MAX;
+        t.lanes[ST_MD] = t.lanes[ST_SEG] = t.lanes[ST_T3] = 16;
+    }
     t.persistent = 0;
     t.blocks_per_cu = std::max(1, std::min(2, persistent_blocks_per_cu(t.lanes[ST_SEG])));
 }
