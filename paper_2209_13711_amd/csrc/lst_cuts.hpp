@@ -73,7 +73,7 @@ __device__ __forceinline__ float4 stored_hit(const EvDev &E, const ModF &m, uint
 }
 
 struct MdOut {
-    float r, a, ca, bend, sv;
+    float r, a, ca;
 };
 
 // radius of the lower hit and the sine / cosine of the threshold track's
@@ -85,51 +85,85 @@ __device__ __forceinline__ void md_anchor(const Consts &K, float xL, float yL, M
     o.ca = sqrtf(1.0f - (o.a * o.a));
 }
 
-// Mini-doublet (stub) window for lower hit L and upper hit U of a module.
-__device__ __forceinline__ bool md_accept(const Consts &K, const ModF &m, float xL, float yL,
-                                          float zL, float xU, float yU, float zU, MdOut &o)
+// Mini-doublet (stub) window for lower hit L and upper hit U of a module, in
+// two parts: what the lower hit alone decides (its projections, the window of
+// the precise step and the coarse window's terms), and the pair's test.  Each
+// quantity comes from the same operations as if it were computed per pair.
+struct MdLo {
+    float u, v;        // the hit along the module's axes
+    float c0, h0;      // precise step: centre and half-width
+    float q0, q1;      // coarse step: barrel z/r and z0max/r (per unit of transverse step),
+                       // endcap centre and half-width
+};
+
+// the hit along the module's precise axis
+__device__ __forceinline__ float md_along(const ModF &m, float xL, float yL, float zL)
 {
-    float uL = (((xL - m.cx) * m.ux) + ((yL - m.cy) * m.uy)) + ((zL - m.cz) * m.uz);
-    float vL = (((xL - m.cx) * m.vx) + ((yL - m.cy) * m.vy)) + ((zL - m.cz) * m.vz);
-    float uU = (((xU - m.cx) * m.ux) + ((yU - m.cy) * m.uy)) + ((zU - m.cz) * m.uz);
-    float vU = (((xU - m.cx) * m.vx) + ((yU - m.cy) * m.vy)) + ((zU - m.cz) * m.vz);
-    float du = uU - uL;
-    float dv = vU - vL;
+    return (((xL - m.cx) * m.ux) + ((yL - m.cy) * m.uy)) + ((zL - m.cz) * m.uz);
+}
+
+// the same over the hit's radius in the endcaps, 0 in the barrel
+__device__ __forceinline__ float md_step(const ModF &m, float xL, float yL, float zL, float rL)
+{
+    return m.barrel ? 0.0f : md_along(m, xL, yL, zL) / rL;
+}
+
+__device__ __forceinline__ MdLo md_lower(const Consts &K, const ModF &m, float xL, float yL, float zL)
+{
+    MdLo t;
+    t.u = md_along(m, xL, yL, zL);
+    t.v = (((xL - m.cx) * m.vx) + ((yL - m.cy) * m.vy)) + ((zL - m.cz) * m.vz);
+    MdOut o;
     md_anchor(K, xL, yL, o);
     const float rL = o.r, a = o.a, ca = o.ca;
     float g = m.g;
-    float hi, lo, zc, hz, sv;
+    float hi, lo;
     if (m.barrel) {
         // bend along u over the gap: g tan(psi +- alpha)
         float ta = a / ca;
-        float tp = uL / m.rl;
+        float tp = t.u / m.rl;
         hi = g * ((tp + ta) / (1.0f - (tp * ta)));
         lo = g * ((tp - ta) / (1.0f + (tp * ta)));
-        float dxy = sqrtf((du * du) + (g * g));
-        zc = dxy * (zL / rL);
-        hz = (dxy * (K.z0max / rL)) + K.tolv;
-        sv = 0.0f;
+        t.q0 = zL / rL;
+        t.q1 = K.z0max / rL;
     } else {
         // transverse step between the sensors, precise component sin(delta +- alpha)
         float sz = fabsf(zL);
         float Dlo = g * (rL / (sz + K.z0max));
         float Dhi = g * ((rL * asinx(a * a)) / (sz - K.z0max));
-        float sp = uL / rL;
+        float sp = t.u / rL;
         float cp = ((xL * m.vx) + (yL * m.vy)) / rL;
         float Sp = (sp * ca) + (cp * a);
         float Sm = (sp * ca) - (cp * a);
         hi = mx(Dlo * Sp, Dhi * Sp);
         lo = mn(Dlo * Sm, Dhi * Sm);
         // the step's coarse (radial) component lies between Dlo cp and Dhi cp
-        zc = (0.5f * (Dlo + Dhi)) * cp;
-        hz = ((0.5f * (Dhi - Dlo)) * cp) + K.tolv;
-        sv = sp;
+        t.q0 = (0.5f * (Dlo + Dhi)) * cp;
+        t.q1 = ((0.5f * (Dhi - Dlo)) * cp) + K.tolv;
     }
-    float c0 = 0.5f * (hi + lo);
-    float h0 = (0.5f * (hi - lo)) + K.tolu;
-    o.bend = (du - c0) / h0;
-    o.sv = sv;
-    return (fabsf(du - c0) <= K.w * h0) && (fabsf(dv - zc) <= K.w * hz);
+    t.c0 = 0.5f * (hi + lo);
+    t.h0 = (0.5f * (hi - lo)) + K.tolu;
+    return t;
+}
+
+// the pair's decision; bend: the precise step's pull (of an accepted pair)
+__device__ __forceinline__ bool md_pair(const Consts &K, const ModF &m, const MdLo &t, float xU, float yU,
+                                        float zU, float &bend)
+{
+    float uU = (((xU - m.cx) * m.ux) + ((yU - m.cy) * m.uy)) + ((zU - m.cz) * m.uz);
+    float du = uU - t.u;
+    bend = 0.0f;
+    if (!(fabsf(du - t.c0) <= K.w * t.h0)) return false;
+    float vU = (((xU - m.cx) * m.vx) + ((yU - m.cy) * m.vy)) + ((zU - m.cz) * m.vz);
+    float dv = vU - t.v;
+    float zc = t.q0, hz = t.q1;
+    if (m.barrel) {
+        float dxy = sqrtf((du * du) + (m.g * m.g));
+        zc = dxy * t.q0;
+        hz = (dxy * t.q1) + K.tolv;
+    }
+    bend = (du - t.c0) / t.h0;
+    return fabsf(dv - zc) <= K.w * hz;
 }
 
 // A mini-doublet as the later stages see it (anchor = lower hit).

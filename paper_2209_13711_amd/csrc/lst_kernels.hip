@@ -788,11 +788,14 @@ struct ModL {
 };
 struct SmMD {
     uint32_t lo[WAVES][STAGE], up[WAVES][STAGE];
-    float bend[WAVES][STAGE], sv[WAVES][STAGE];
+    float bend[WAVES][STAGE];
     ModL mod[WAVES][MAXP];            // module frame of each group's slot
     int4 sl[WAVES][MAXP];             // slot, first lower hit, first upper hit, upper hits
     int4 nb[WAVES][MAXP];             // the slot's map row and its event's first slot
     uint32_t cnt[WAVES][MAXP];
+    float4 t0[WAVES][64];             // terms of 64 lower hits (MdLo)
+    float2 t1[WAVES][64];
+    int32_t mark[WAVES][64];          // chunk_src
     uint8_t g[WAVES][STAGE];
 };
 struct SmSeg {
@@ -836,11 +839,14 @@ struct SmChain {
 
 // ---------------------------------------------------------------- mini-doublets
 __device__ __forceinline__ void write_md(const EvDev &E, const Consts &K, uint32_t i, int slot,
-                                         uint32_t hl, uint32_t hu, const MdOut &o,
+                                         uint32_t hl, uint32_t hu, float bend,
                                          const ModF &mod, const int4 &nbr)
 {
     const float4 L = stored_hit(E, mod, hl, 0), U = stored_hit(E, mod, hu, 1);
     const float xL = L.x, yL = L.y;
+    MdOut o;
+    md_anchor(K, xL, yL, o);
+    const float sv = md_step(mod, xL, yL, L.z, o.r);
     E.md_hlo[i] = (int32_t)hl;
     E.md_hup[i] = (int32_t)hu;
     E.md_slot[i] = slot;
@@ -848,11 +854,11 @@ __device__ __forceinline__ void write_md(const EvDev &E, const Consts &K, uint32
     const float dx = U.x - xL, dy = U.y - yL;
     E.md_p0[i] = make_float4(xL, yL, L.z, o.r);
     // the segment window's per-MD terms, rounded exactly as it would round them
-    E.md_p1[i] = make_float4(o.a, o.ca, 1.0f / o.r, fabsf(o.sv) / o.r);
+    E.md_p1[i] = make_float4(o.a, o.ca, 1.0f / o.r, fabsf(sv) / o.r);
     const float dn = sqrtf((dx * dx) + (dy * dy));
-    E.md_p2[i] = make_float4(dx, dy, dn, o.sv);
+    E.md_p2[i] = make_float4(dx, dy, dn, sv);
     E.md_atol[i] = seg_angle_bound(K, dn);
-    E.md_bend[i] = o.bend;
+    E.md_bend[i] = bend;
     E.md_bar[i] = (uint8_t)(mod.barrel | (mod.is2s << 1));
 }
 
@@ -870,52 +876,82 @@ __device__ __forceinline__ ModF mod_from(const ModL &r)
 }
 
 // Every lower x upper hit pair of the wave's P module slots (one per group,
-// its frame and hit ranges in the LDS table), walked as one list 64 pairs at
-// a time, so a slot with many hits is shared by all lanes of the wave.  The
-// list is in slot order, so each slot's accepted pairs are consecutive in
-// the wave's output, in lower-major pair order.
-// sink(ok, g, hl, hu, o, pos): g = group of the slot, pos = rank among the
-// wave's accepted pairs, o the window's outputs for the pair.
+// its frame and hit ranges in the LDS table).  The slots' lower hits are taken
+// 64 at a time, one per lane, which computes what the hit alone decides (most
+// of the window's arithmetic: seven divisions and square roots, once per hit
+// and not once per pair); their pairs are then walked as one list 64 at a
+// time, so a slot with many hits is shared by all lanes of the wave.  The list
+// is in slot order, so each slot's accepted pairs are consecutive in the
+// wave's output, in lower-major pair order.  Against the whole window per
+// pair: 16 PU200 events 72 -> 70 us, 16 uneven ones 185 -> 144, the stress
+// configuration in binary16 storage 89 -> 59; one PU200 event (few hits per
+// slot: bound by the chain of loads) 12.6 -> 13.7, within the runs' spread at
+// the chain's end (81.2 -> 81.8).
+// The staging without the lower hit's step (write_md computes it again) leaves
+// LDS for six blocks per CU instead of four; half the staging would be a
+// little faster on one event (12.8) and sends the dense modules of the uneven
+// batch through the second enumeration (248).
+// sink(ok, g, hl, hu, bend, pos): g = group of the slot, pos = rank among
+// the wave's accepted pairs.
 template <int G, class F>
-__device__ __forceinline__ uint32_t enum_md(const EvDev &E, const Consts &K, const SmMD &sm, int w,
-                                            uint32_t np, F &&sink)
+__device__ __forceinline__ uint32_t enum_md(const EvDev &E, const Consts &K, SmMD &sm, int w,
+                                            uint32_t nlo, F &&sink)
 {
     constexpr int P = Grp<G>::P;
+    const Grp<64> gw;
     const uint32_t l = (uint32_t)lane_id();
     const unsigned long long below = lanes_below();
-    uint32_t pre[P + 1];
+    uint32_t pre[P + 1];   // lower hits (of slots with pairs) before group p's
     pre[0] = 0;
 #pragma unroll
     for (int p = 0; p < P; ++p)
-        pre[p + 1] = pre[p] + (uint32_t)__builtin_amdgcn_readlane((int)np, p * G);
-    const uint32_t tot = pre[P];
+        pre[p + 1] = pre[p] + (uint32_t)__builtin_amdgcn_readlane((int)nlo, p * G);
     uint32_t acc = 0;
-    for (uint32_t jc = 0; jc < tot; jc += 64) {
-        const uint32_t j = jc + l;
-        int g = 0;
+    for (uint32_t fc = 0; fc < pre[P]; fc += 64) {
+        const uint32_t f = fc + l;
+        int gl = 0;
         uint32_t gpre = 0;
 #pragma unroll
         for (int p = 1; p < P; ++p)
-            if (j >= pre[p]) {
-                g = p;
+            if (f >= pre[p]) {
+                gl = p;
                 gpre = pre[p];
             }
-        bool ok = false;
-        uint32_t hl = 0, hu = 0;
-        MdOut o = {};
-        if (j < tot) {
-            const int4 sl = sm.sl[w][g];
-            const uint32_t p = j - gpre, nup = (uint32_t)sl.w;
-            const uint32_t il = p / nup, iu = p - il * nup;
-            hl = (uint32_t)sl.y + il;
-            hu = (uint32_t)sl.z + iu;
-            const ModF mf = mod_from(sm.mod[w][g]);
-            const float4 L = stored_hit(E, mf, hl, 0), U = stored_hit(E, mf, hu, 1);
-            ok = md_accept(K, mf, L.x, L.y, L.z, U.x, U.y, U.z, o);
+        uint32_t nup = 0, hlow = 0;
+        if (f < pre[P]) {
+            const int4 sl = sm.sl[w][gl];
+            nup = (uint32_t)sl.w;
+            hlow = (uint32_t)sl.y + (f - gpre);
+            const ModF mf = mod_from(sm.mod[w][gl]);
+            const float4 L = stored_hit(E, mf, hlow, 0);
+            const MdLo t = md_lower(K, mf, L.x, L.y, L.z);
+            sm.t0[w][l] = make_float4(t.u, t.v, t.c0, t.h0);
+            sm.t1[w][l] = make_float2(t.q0, t.q1);
         }
-        const unsigned long long m = __ballot(ok);
-        sink(ok, g, hl, hu, o, acc + (uint32_t)__popcll(m & below));
-        acc += (uint32_t)__popcll(m);
+        const uint32_t incl = wave_incl_scan(nup);
+        const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        for (uint32_t jc = 0; jc < tot; jc += 64) {
+            const uint32_t j = jc + l;
+            const int src = chunk_src(incl, nup, jc, sm.mark[w]);
+            const uint32_t ex = gw.bcast(incl, src) - gw.bcast(nup, src);
+            const int g = gw.bcast(gl, src);
+            const uint32_t hl = gw.bcast(hlow, src);
+            bool ok = false;
+            uint32_t hu = 0;
+            float bend = 0.0f;
+            if (j < tot) {
+                hu = (uint32_t)sm.sl[w][g].z + (j - ex);
+                const ModF mf = mod_from(sm.mod[w][g]);
+                const float4 U = stored_hit(E, mf, hu, 1), a = sm.t0[w][src];
+                const float2 b = sm.t1[w][src];
+                const MdLo t{a.x, a.y, a.z, a.w, b.x, b.y};
+                ok = md_pair(K, mf, t, U.x, U.y, U.z, bend);
+            }
+            const unsigned long long m = __ballot(ok);
+            sink(ok, g, hl, hu, bend, acc + (uint32_t)__popcll(m & below));
+            acc += (uint32_t)__popcll(m);
+        }
+        wave_lds_sync();   // the terms are rewritten by the next lower hits
     }
     return acc;
 }
@@ -942,7 +978,7 @@ __device__ __forceinline__ void md_body(const EvDev &E, const ModDev &M, const C
         const int k = spread ? gp.g * nslot + u : u * P + gp.g;
         const bool act = u < nslot && k < items;
         int slot = 0;
-        uint32_t lo0 = 0, up0 = 0, nup = 0, np = 0;
+        uint32_t lo0 = 0, up0 = 0, nup = 0, nlo = 0;   // nlo: lower hits that have pairs
         if (act) {
             const int ev = k / n_x;
             const int m = M.xorder[M.sec_off[xb.x] + (k - ev * n_x)];
@@ -950,7 +986,7 @@ __device__ __forceinline__ void md_body(const EvDev &E, const ModDev &M, const C
             lo0 = E.boff[2 * slot];
             up0 = E.boff[2 * slot + 1];
             nup = E.boff[2 * slot + 2] - up0;
-            np = (up0 - lo0) * nup;
+            nlo = nup ? up0 - lo0 : 0u;
             // per-hit state of duplicate removal for this slot's hits (contiguous)
             for (uint32_t h = lo0 + gp.lane; h < up0 + nup; h += G) {
                 E.hmin[h] = ~0ull;
@@ -961,7 +997,7 @@ __device__ __forceinline__ void md_body(const EvDev &E, const ModDev &M, const C
                 sm.sl[w][gp.g] = make_int4(slot, (int)lo0, (int)up0, (int)nup);
                 const int e0 = M.map_ptr[m];
                 sm.nb[w][gp.g] = make_int4(e0, M.map_ptr[m + 1] - e0, ev * M.n_mod, 0);
-                if (np) {
+                if (nlo) {
                     ModL r;
                     r.c = make_float4(M.cx[m], M.cy[m], M.cz[m], M.g[m]);
                     r.u = make_float4(M.ux[m], M.uy[m], M.uz[m], M.rl[m]);
@@ -974,16 +1010,15 @@ __device__ __forceinline__ void md_body(const EvDev &E, const ModDev &M, const C
         }
         if (l < (uint32_t)MAXP) sm.cnt[w][l] = 0u;
         wave_lds_sync();
-        const uint32_t tot = enum_md<G>(E, K, sm, w, np,
-                                        [&](bool ok, int g, uint32_t hl, uint32_t hu, const MdOut &o,
+        const uint32_t tot = enum_md<G>(E, K, sm, w, nlo,
+                                        [&](bool ok, int g, uint32_t hl, uint32_t hu, float bend,
                                             uint32_t pos) {
             if (ok) {
                 atomicAdd(&sm.cnt[w][g], 1u);
                 if (pos < STAGE) {
                     sm.lo[w][pos] = hl;
                     sm.up[w][pos] = hu;
-                    sm.bend[w][pos] = o.bend;
-                    sm.sv[w][pos] = o.sv;
+                    sm.bend[w][pos] = bend;
                     sm.g[w][pos] = (uint8_t)g;
                 }
             }
@@ -1002,20 +1037,16 @@ __device__ __forceinline__ void md_body(const EvDev &E, const ModDev &M, const C
         if (ovf) continue;
         for (uint32_t q = l; q < tot && q < (uint32_t)STAGE; q += 64) {
             const int g = sm.g[w][q];
-            const uint32_t hl = sm.lo[w][q];
-            const float4 L = stored_hit(E, mod_from(sm.mod[w][g]), hl, 0);
-            MdOut o;
-            md_anchor(K, L.x, L.y, o);
-            o.bend = sm.bend[w][q];
-            o.sv = sm.sv[w][q];
-            write_md(E, K, off + q, sm.sl[w][g].x, hl, sm.up[w][q], o, mod_from(sm.mod[w][g]), sm.nb[w][g]);
+            write_md(E, K, off + q, sm.sl[w][g].x, sm.lo[w][q], sm.up[w][q], sm.bend[w][q],
+                     mod_from(sm.mod[w][g]), sm.nb[w][g]);
         }
         if (tot > (uint32_t)STAGE) {
             // beyond the staging: enumerate again and write directly
-            enum_md<G>(E, K, sm, w, np,
-                       [&](bool ok, int g, uint32_t hl, uint32_t hu, const MdOut &o, uint32_t pos) {
+            enum_md<G>(E, K, sm, w, nlo,
+                       [&](bool ok, int g, uint32_t hl, uint32_t hu, float bend, uint32_t pos) {
                 if (ok && pos >= STAGE)
-                    write_md(E, K, off + pos, sm.sl[w][g].x, hl, hu, o, mod_from(sm.mod[w][g]), sm.nb[w][g]);
+                    write_md(E, K, off + pos, sm.sl[w][g].x, hl, hu, bend, mod_from(sm.mod[w][g]),
+                             sm.nb[w][g]);
             });
         }
         wave_lds_sync();
