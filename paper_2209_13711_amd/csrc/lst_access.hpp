@@ -1,10 +1,19 @@
-// Device-side accessors of the arena shared by the kernel files: the
-// overflow flag and the compact index over stored quintuplets.
+// Device-side helpers shared by the kernel files: the order of a wave's LDS
+// accesses, the overflow flag and the compact index over stored objects.
 #pragma once
 
 #include "lst_internal.hpp"
 
 namespace lst {
+
+__device__ __forceinline__ void wave_lds_sync()
+{
+    // orders the wave's LDS writes before its later LDS reads by other lanes
+    // (a wave's LDS operations complete in issue order)
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 __device__ __forceinline__ bool upstream_overflow(const EvDev &E)
 {
@@ -39,15 +48,23 @@ __device__ __forceinline__ int32_t t5_hit(const EvDev &E, int32_t t, int j)
 // with a binary search over it.
 __device__ __forceinline__ uint32_t obj_prefix(const EvDev &E, int type, uint32_t *s_pre)
 {
-    if (threadIdx.x == 0) {
+    static_assert(NSH < 64, "a region per lane");
+    if (threadIdx.x < 64) {
+        const int l = (int)threadIdx.x;
         const uint32_t rc = E.rc[type];
-        uint32_t acc = 0;
-        for (int r = 0; r < NSH; ++r) {
-            s_pre[r] = acc;
-            const uint32_t c = E.gc[gc_shard(type, r)];
-            acc += c < rc ? c : rc;
+        uint32_t c = 0;
+        if (l < NSH) {
+            c = E.gc[gc_shard(type, l)];
+            c = c < rc ? c : rc;
         }
-        s_pre[NSH] = acc;
+        uint32_t x = c;
+#pragma unroll
+        for (int d = 1; d < NSH; d <<= 1) {
+            const uint32_t up = __shfl_up(x, d, 64);
+            x += l >= d ? up : 0u;
+        }
+        if (l < NSH) s_pre[l + 1] = x;
+        if (l == 0) s_pre[0] = 0;
     }
     __syncthreads();
     return s_pre[NSH];

@@ -294,9 +294,10 @@ size_t carve(lst_ctx *c, char *base, const lst_caps &k, EvDev &E, void **zero_ba
         E.pl_k3 = cv.take<int32_t>(nt3);
         E.pl_k5d = cv.take<float4>(nt5);
         E.pl_k3d = cv.take<float4>(nt3);
-        E.pl_d5 = cv.take<float4>(k.px_cand);
-        E.pl_d3 = cv.take<float4>(k.px_cand);
-        E.pl_dt = cv.take<float4>(nt5);
+        E.pl_k5k = cv.take<uint8_t>(nt5);
+        E.pl_sdd = cv.take<float4>(k.seeds);
+        E.pl_sdk = cv.take<uint8_t>(k.seeds);
+        E.sd_pos = cv.take<int32_t>(k.seeds);
         E.c5_seed = cv.take<int32_t>(k.px_cand);
         E.c5_obj = cv.take<int32_t>(k.px_cand);
         E.c5_score = cv.take<float>(k.px_cand);
@@ -307,7 +308,6 @@ size_t carve(lst_ctx *c, char *base, const lst_caps &k, EvDev &E, void **zero_ba
         E.c3_keep = cv.take<uint8_t>(k.px_cand);
         E.sd_c5 = cv.take<int2>(k.seeds);
         E.sd_c3 = cv.take<int2>(k.seeds);
-        E.sd_free = cv.take<int32_t>(k.seeds);
         E.hmin_o = cv.take<unsigned long long>(k.hits);
         E.hmin_p = cv.take<unsigned long long>(k.px_hits);
         E.hflag_o = cv.take<uint8_t>(k.hits);

@@ -39,7 +39,6 @@ enum GlobalCounter {
     GC_DROP,           // [OT_COUNT] objects removed by per-module capacities
     GC_PX5 = GC_DROP + OT_COUNT,   // pT5 link candidates
     GC_PX3,            // pT3 link candidates
-    GC_PXFREE,         // seeds that no kept pT5 uses (sd_free)
     GC_SH = GC_PAD     // [OT_COUNT][NSH] reservation shards, one line each
 };
 __host__ __device__ constexpr int gc_shard(int type, int s) { return GC_SH + (type * NSH + s) * GC_PAD; }
@@ -145,19 +144,21 @@ struct EvDev {
     uint8_t *sd_used, *sd_keep;      // [cap_seeds] linked by a kept pT5/pT3; a track candidate
     float4 *t5_dir, *t3_dir;         // [span] directions of kept quintuplets, of triplets
     uint8_t *t5_clean;               // [span] kept quintuplet left after cross-cleaning
-    // per-event lists (PXL_*), the kept quintuplets and the triplets also per
-    // azimuth bin: counts, offsets, fill counters ([PXL_COUNT][cap_ev x PX_NB
-    // + 1] each; a list's key is ev x PX_NB + bin, or ev), entries
+    // lists per (event, azimuth bin) (PXL_*): counts, offsets, fill counters
+    // ([PXL_COUNT][cap_ev x PX_NB + 1] each; a list's key is ev x PX_NB + bin),
+    // entries
     int32_t *pl_cnt, *pl_off, *pl_fill;
     int32_t *pl_k5, *pl_k3;          // kept quintuplets, triplets
     float4 *pl_k5d, *pl_k3d;         // their directions, in list order
-    float4 *pl_d5, *pl_d3, *pl_dt;   // directions of kept pT5, cleaned pT3, cleaned T5
+    uint8_t *pl_k5k;                 // a listed quintuplet left after cross-cleaning
+    float4 *pl_sdd;                  // [cap_seeds] the seeds' directions, in list order
+    uint8_t *pl_sdk;                 // [cap_seeds] its kept candidate: 1 pT5, 2 cleaned pT3
+    int32_t *sd_pos;                 // [cap_seeds] a seed's place in its list
     // link candidates of pT5 (c5) and pT3 (c3): seed, object, score, kept
     int32_t *c5_seed, *c5_obj, *c3_seed, *c3_obj;   // [cap_pxc]
     float *c5_score, *c3_score;
     uint8_t *c5_keep, *c3_keep;
     int2 *sd_c5, *sd_c3;             // [cap_seeds] first candidate and count of each seed
-    int32_t *sd_free;                // [cap_seeds] seeds that no kept pT5 uses
     unsigned long long *hmin_o;      // [cap_hits] smallest key per grouped outer hit
     unsigned long long *hmin_p;      // [cap_px]   smallest key per pixel hit
     uint8_t *hflag_o, *hflag_p;      // hits held by track candidates so far
@@ -216,7 +217,8 @@ hipError_t launch_t5(const EvDev &E, const ModDev &M, const Consts &K, int grid,
                      hipStream_t s);
 hipError_t launch_dedup(const EvDev &E, const ModDev &M, int grid, hipStream_t s);
 // pixel objects (lst_pixel.hip)
-enum { PXL_K5 = 0, PXL_K3, PXL_D5, PXL_D3, PXL_DT, PXL_COUNT };
+// lists: kept quintuplets, triplets, seeds
+enum { PXL_K5 = 0, PXL_K3, PXL_SD, PXL_COUNT };
 constexpr int PX_NB = 64;   // azimuth bins of the per-event object lists
 struct PixConsts {
     float sig2p, sigz, wl2, dr2, x5p, x5z, x3p, x3z;

@@ -34,15 +34,6 @@ __device__ __forceinline__ unsigned long long lanes_below()
     return (1ull << lane_id()) - 1ull;
 }
 
-__device__ __forceinline__ void wave_lds_sync()
-{
-    // orders the wave's LDS writes before its later LDS reads by other lanes
-    // (a wave's LDS operations complete in issue order)
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // inclusive max-scan of non-negative values over the 64 lanes: shifts within
 // rows of 16 lanes, then the last lane of a row broadcast to the next rows
 // (DPP row_shr:1,2,4,8, row_bcast:15, row_bcast:31)

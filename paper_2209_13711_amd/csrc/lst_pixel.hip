@@ -19,16 +19,21 @@
 //    themselves (the smaller seed index keeps a shared pixel hit);
 //  - track candidates: pT5, pT3, T5 and pLS left after cleaning.
 //
-// The collections are small (thousands per event), so every step is a
-// plain data-parallel pass: one wave per seed scans the objects of its event
-// from a per-event list, one wave per object scans the direction lists of
-// its event in the cross-cleaning, one thread per candidate for the rest.
-// Per-hit minima use 64-bit atomics on (score bits, seed); ties on that key
-// are resolved by the hit tuples.  List counters take one atomic per wave
-// and list key (one address taking an atomic per object would
-// serialise thousands of device-scope atomics).  Every per-event list is
-// kept per (event, azimuth bin), so that a seed or an object scans only the
-// bins its window or closeness reaches.
+// The collections are small (thousands per event) and a step's work takes a
+// few microseconds, so what counts is how many launches and dependent loads
+// there are: ten kernels (eleven for larger batches), each with enough lanes
+// per object that its loads are one chain.  A wave takes a few seeds and scans
+// the objects of their event from a per-event list; 16 lanes take a
+// candidate, a wave an object of the cross-cleaning.  Per-hit minima use
+// 64-bit atomics on (removal, score bits, seed), taken as soon as a candidate
+// is accepted; ties on that key are resolved by the hit tuples.  List counters
+// take one atomic per wave and list key (one address taking an atomic per
+// object would serialise thousands of device-scope atomics).  Every per-event
+// list is kept per (event, azimuth bin), so that a seed or an object scans only
+// the bins its window or closeness reaches; the survivors of a step are marks
+// on the entries of the seeds' or quintuplets' list and no list of their own.
+// One PU200 event: 205 us in 20 launches with a pass, a count, a scan and a
+// list per step, 88 us like this.
 #include <algorithm>
 
 #include "lst_access.hpp"
@@ -104,7 +109,7 @@ __device__ __forceinline__ int32_t agg_add(int32_t *cnt, int key, bool act)
     unsigned long long todo = __ballot(act);
     while (todo) {
         const int lead = __builtin_ctzll(todo);
-        const int k = __shfl(key, lead, 64);
+        const int k = __builtin_amdgcn_readlane(key, lead);
         const unsigned long long grp = todo & __ballot(key == k);
         if ((grp >> l) & 1ull) {
             lead_of = lead;
@@ -121,26 +126,6 @@ __device__ __forceinline__ int32_t agg_add(int32_t *cnt, int key, bool act)
 
 // Objects handed to one wave, consecutive, in the one-wave-per-object passes
 constexpr int PX_WCHUNK = 2;
-
-// A count per list key kept by one wave over its run of objects: one atomic
-// when the key changes and one at the end.
-struct EvRun {
-    int ev = -1;
-    int32_t n = 0;
-    __device__ void add(int32_t *cnt, int e)
-    {
-        if (e != ev) {
-            flush(cnt);
-            ev = e;
-        }
-        ++n;
-    }
-    __device__ void flush(int32_t *cnt)
-    {
-        if (n > 0 && px_lane() == 0) atomicAdd(&cnt[ev], n);
-        n = 0;
-    }
-};
 
 // ---------------------------------------------------------------- input
 // A pixel batch as sent (px_pack_words) into its arrays: hit indices made
@@ -185,7 +170,7 @@ __global__ __launch_bounds__(BLOCK) void k_px_init(EvDev E)
 {
     if (upstream_overflow(E)) return;
     const int t0 = blockIdx.x * BLOCK + threadIdx.x, st = gridDim.x * BLOCK;
-    const int n_ev = E.desc[D_NEV], n_px = E.desc[D_NPX], n_sd = E.desc[D_NSEEDS];
+    const int n_px = E.desc[D_NPX], n_sd = E.desc[D_NSEEDS];
     const int n_hits = (int)E.gc[GC_N_SORTED];
     const int n_pl = PXL_COUNT * (E.cap_ev * PX_NB + 1);
     for (int i = t0; i < n_pl; i += st) {
@@ -196,7 +181,6 @@ __global__ __launch_bounds__(BLOCK) void k_px_init(EvDev E)
         E.sd_c5[i] = make_int2(0, 0);
         E.sd_c3[i] = make_int2(0, 0);
     }
-    (void)n_ev;
     for (int i = t0; i < n_hits; i += st) {
         E.hmin_o[i] = KEY_NONE;
         E.hflag_o[i] = 0;
@@ -214,76 +198,77 @@ __global__ __launch_bounds__(BLOCK) void k_px_init(EvDev E)
     }
 }
 
-// reset of the per-hit minima between two duplicate removals; with
-// list_free, also the list of the seeds that no kept pT5 uses (run inside
-// the kernels that precede the next users)
-__device__ __forceinline__ void rekey_body(const EvDev &E, bool list_free)
-{
-    const int t0 = blockIdx.x * BLOCK + threadIdx.x, st = gridDim.x * BLOCK;
-    const int n_px = E.desc[D_NPX], n_hits = (int)E.gc[GC_N_SORTED], n_sd = E.desc[D_NSEEDS];
-    for (int i = t0; i < n_hits; i += st) E.hmin_o[i] = KEY_NONE;
-    for (int i = t0; i < n_px; i += st) E.hmin_p[i] = KEY_NONE;
-    if (!list_free) return;
-    for (int s0 = blockIdx.x * BLOCK; s0 < n_sd; s0 += st) {
-        const int s = s0 + (int)threadIdx.x;
-        const bool act = s < n_sd && !E.sd_used[s];
-        const int32_t at = agg_add(reinterpret_cast<int32_t *>(E.gc + GC_PXFREE), 0, act);
-        if (act) E.sd_free[at] = s;
-    }
-}
-
 __device__ __forceinline__ int md_event(const EvDev &E, int32_t md, int n_mod)
 {
     return E.md_slot[md] / n_mod;
 }
 
-// directions of the kept quintuplets and of every triplet, counted per
-// (event, azimuth bin)
+// The passes over the listed objects: kept quintuplets, triplets and seeds
+// side by side, a block of threads of one kind at a time (list PXL_*, index v
+// of n in it).
+struct PxBlocks {
+    uint32_t n5, n3, ns, b5, b3, bs;
+    __device__ PxBlocks(const EvDev &E, uint32_t *s_pre5, uint32_t *s_pre3)
+    {
+        n5 = obj_prefix(E, OT_T5, s_pre5);
+        n3 = obj_prefix(E, OT_T3, s_pre3);
+        ns = (uint32_t)E.desc[D_NSEEDS];
+        b5 = (n5 + BLOCK - 1) / BLOCK;
+        b3 = b5 + (n3 + BLOCK - 1) / BLOCK;
+        bs = b3 + (ns + BLOCK - 1) / BLOCK;
+    }
+    __device__ int list(uint32_t b, uint32_t &v, uint32_t &n) const
+    {
+        const int k = b < b5 ? PXL_K5 : b < b3 ? PXL_K3 : PXL_SD;
+        v = (b - (k == PXL_K5 ? 0u : k == PXL_K3 ? b5 : b3)) * BLOCK + threadIdx.x;
+        n = k == PXL_K5 ? n5 : k == PXL_K3 ? n3 : ns;
+        return k;
+    }
+};
+
+// directions of the kept quintuplets and of every triplet; with the seeds,
+// counted per (event, azimuth bin)
 __global__ __launch_bounds__(BLOCK) void k_obj_dir(EvDev E, int n_mod)
 {
-    __shared__ uint32_t s_pre[NSH + 1];
+    __shared__ uint32_t s_pre5[NSH + 1], s_pre3[NSH + 1];
     if (upstream_overflow(E)) return;
-    const uint32_t n5 = obj_prefix(E, OT_T5, s_pre);
-    for (uint32_t v0 = blockIdx.x * BLOCK; v0 < n5; v0 += gridDim.x * BLOCK) {
-        const uint32_t v = v0 + threadIdx.x;
-        bool act = false;
-        int ev = 0;
-        if (v < n5) {
-            const int32_t t = obj_at(E, OT_T5, s_pre, v);
-            if (E.t5_keep[t]) {
+    const PxBlocks B(E, s_pre5, s_pre3);
+    for (uint32_t b = blockIdx.x; b < B.bs; b += gridDim.x) {
+        uint32_t v, n;
+        const int list = B.list(b, v, n);
+        bool act = v < n;
+        int key = 0;
+        if (act && list == PXL_K5) {
+            const int32_t t = obj_at(E, OT_T5, s_pre5, v);
+            act = E.t5_keep[t] != 0;
+            if (act) {
                 const MdV A = load_md(E, E.t5_md0[t]), C = load_md(E, E.t5_md2[t]),
                           Q = load_md(E, E.t5_md4[t]);
                 const float4 d = obj_dir(A, Q, bridge_curv(A, C, Q));
                 E.t5_dir[t] = d;
-                ev = md_event(E, E.t5_md0[t], n_mod) * PX_NB + dir_bin(d);
-                act = true;
+                key = md_event(E, E.t5_md0[t], n_mod) * PX_NB + dir_bin(d);
+            } else {
+                E.t5_clean[t] = 0;
             }
-        }
-        (void)agg_add(pl(E, E.pl_cnt, PXL_K5), ev, act);
-    }
-    __syncthreads();
-    const uint32_t n3 = obj_prefix(E, OT_T3, s_pre);
-    for (uint32_t v0 = blockIdx.x * BLOCK; v0 < n3; v0 += gridDim.x * BLOCK) {
-        const uint32_t v = v0 + threadIdx.x;
-        int ev = 0;
-        if (v < n3) {
-            const int32_t t = obj_at(E, OT_T3, s_pre, v);
+        } else if (act && list == PXL_K3) {
+            const int32_t t = obj_at(E, OT_T3, s_pre3, v);
             const float4 d = obj_dir(load_md(E, E.t3_a[t]), load_md(E, E.t3_c[t]), E.t3_k[t]);
             E.t3_dir[t] = d;
-            ev = md_event(E, E.t3_a[t], n_mod) * PX_NB + dir_bin(d);
+            key = md_event(E, E.t3_a[t], n_mod) * PX_NB + dir_bin(d);
+        } else if (act) {
+            key = E.sd_ev[v] * PX_NB + dir_bin(E.sd_dir[v]);
         }
-        (void)agg_add(pl(E, E.pl_cnt, PXL_K3), ev, v < n3);
+        (void)agg_add(pl(E, E.pl_cnt, list), key, act);
     }
 }
 
-// exclusive scan of a list's counts, n_ev x mult keys (block 0: list0,
-// block 1: list1); off[n] = the total
-__global__ __launch_bounds__(1024) void k_pl_scan(EvDev E, int list0, int list1, int mult)
+// exclusive scan of the lists' counts, one block per list; off[n] = the total
+__global__ __launch_bounds__(1024) void k_pl_scan(EvDev E)
 {
     __shared__ int32_t s_part[1024];
     if (upstream_overflow(E)) return;
-    const int list = blockIdx.x == 0 ? list0 : list1;
-    const int n = E.desc[D_NEV] * mult;
+    const int list = (int)blockIdx.x;
+    const int n = E.desc[D_NEV] * PX_NB;
     const int32_t *cnt = pl(E, E.pl_cnt, list);
     int32_t *off = pl(E, E.pl_off, list);
     const int per = (n + 1023) / 1024;
@@ -307,46 +292,87 @@ __global__ __launch_bounds__(1024) void k_pl_scan(EvDev E, int list0, int list1,
     if (threadIdx.x == 1023) off[n] = s_part[1023];
 }
 
-// kept quintuplets and triplets into their per-(event, bin) lists
+// Arenas of up to PX_SELF events scan their counts inside k_obj_fill: each
+// block scans the few hundred counts for itself, one key per thread (block 0
+// writes the offsets for the later kernels): 9.4 us against 10.7 after a scan
+// of its own, itself 3.8 us and a launch.  Past one key per thread the scan
+// grows with the events in every block, where one block per list does it once.
+constexpr int PX_SELF = BLOCK / PX_NB;
+
+// kept quintuplets, triplets and seeds into their per-(event, bin) lists
+template <bool SELF>
 __global__ __launch_bounds__(BLOCK) void k_obj_fill(EvDev E, int n_mod)
 {
-    __shared__ uint32_t s_pre[NSH + 1];
+    __shared__ uint32_t s_pre5[NSH + 1], s_pre3[NSH + 1];
+    __shared__ int32_t s_off[SELF ? PXL_COUNT : 1][BLOCK], s_w[PXL_COUNT][WAVES];
     if (upstream_overflow(E)) return;
-    const uint32_t n5 = obj_prefix(E, OT_T5, s_pre);
-    const int32_t *o5 = pl(E, E.pl_off, PXL_K5);
-    int32_t *f5 = pl(E, E.pl_fill, PXL_K5);
-    for (uint32_t v0 = blockIdx.x * BLOCK; v0 < n5; v0 += gridDim.x * BLOCK) {
-        const uint32_t v = v0 + threadIdx.x;
-        int32_t t = 0;
-        int ev = 0;
-        bool act = false;
-        if (v < n5) {
-            t = obj_at(E, OT_T5, s_pre, v);
-            act = E.t5_keep[t] != 0;
-            if (act) ev = md_event(E, E.t5_md0[t], n_mod) * PX_NB + dir_bin(E.t5_dir[t]);
-        }
-        const int32_t at = agg_add(f5, ev, act);
-        if (act) {
-            E.pl_k5[o5[ev] + at] = t;
-            E.pl_k5d[o5[ev] + at] = E.t5_dir[t];
+    if constexpr (SELF) {
+        const int l = px_lane(), w = (int)(threadIdx.x >> 6);
+        int32_t c[PXL_COUNT], x[PXL_COUNT];
+#pragma unroll
+        for (int k = 0; k < PXL_COUNT; ++k)
+            c[k] = x[k] = (int)threadIdx.x < E.cap_ev * PX_NB ? pl(E, E.pl_cnt, k)[threadIdx.x] : 0;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1)
+#pragma unroll
+            for (int k = 0; k < PXL_COUNT; ++k) {
+                const int32_t up = __shfl_up(x[k], d, 64);
+                x[k] += l >= d ? up : 0;
+            }
+#pragma unroll
+        for (int k = 0; k < PXL_COUNT; ++k)
+            if (l == 63) s_w[k][w] = x[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < PXL_COUNT; ++k) {
+            int32_t before = 0;
+            for (int q = 0; q < w; ++q) before += s_w[k][q];
+            const int32_t ex = before + x[k] - c[k];
+            s_off[k][threadIdx.x] = ex;
+            if (blockIdx.x == 0 && (int)threadIdx.x < E.cap_ev * PX_NB) {
+                int32_t *off = pl(E, E.pl_off, k);
+                off[threadIdx.x] = ex;
+                if ((int)threadIdx.x == E.cap_ev * PX_NB - 1) off[threadIdx.x + 1] = ex + c[k];
+            }
         }
     }
-    __syncthreads();
-    const uint32_t n3 = obj_prefix(E, OT_T3, s_pre);
-    const int32_t *o3 = pl(E, E.pl_off, PXL_K3);
-    int32_t *f3 = pl(E, E.pl_fill, PXL_K3);
-    for (uint32_t v0 = blockIdx.x * BLOCK; v0 < n3; v0 += gridDim.x * BLOCK) {
-        const uint32_t v = v0 + threadIdx.x;
-        int32_t t = 0;
-        int ev = 0;
-        if (v < n3) {
-            t = obj_at(E, OT_T3, s_pre, v);
-            ev = md_event(E, E.t3_a[t], n_mod) * PX_NB + dir_bin(E.t3_dir[t]);
+    const PxBlocks B(E, s_pre5, s_pre3);   // (its barrier also covers the offsets)
+    for (uint32_t b = blockIdx.x; b < B.bs; b += gridDim.x) {
+        uint32_t v, n;
+        const int list = B.list(b, v, n);
+        bool act = v < n;
+        int key = 0;
+        int32_t t = (int32_t)v;
+        float4 d = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (act && list == PXL_K5) {
+            t = obj_at(E, OT_T5, s_pre5, v);
+            act = E.t5_keep[t] != 0;
+            if (act) {
+                d = E.t5_dir[t];
+                key = md_event(E, E.t5_md0[t], n_mod) * PX_NB + dir_bin(d);
+            }
+        } else if (act && list == PXL_K3) {
+            t = obj_at(E, OT_T3, s_pre3, v);
+            d = E.t3_dir[t];
+            key = md_event(E, E.t3_a[t], n_mod) * PX_NB + dir_bin(d);
+        } else if (act) {
+            d = E.sd_dir[t];
+            key = E.sd_ev[t] * PX_NB + dir_bin(d);
         }
-        const int32_t at = agg_add(f3, ev, v < n3);
-        if (v < n3) {
-            E.pl_k3[o3[ev] + at] = t;
-            E.pl_k3d[o3[ev] + at] = E.t3_dir[t];
+        int32_t at = agg_add(pl(E, E.pl_fill, list), key, act);
+        if (!act) continue;
+        if constexpr (SELF) at += s_off[list][key];
+        else at += pl(E, E.pl_off, list)[key];
+        if (list == PXL_K5) {
+            E.pl_k5[at] = t;
+            E.pl_k5d[at] = d;
+        } else if (list == PXL_K3) {
+            E.pl_k3[at] = t;
+            E.pl_k3d[at] = d;
+        } else {
+            E.sd_pos[t] = at;
+            E.pl_sdd[at] = d;
+            E.pl_sdk[at] = 0;
         }
     }
 }
@@ -368,116 +394,214 @@ __device__ __forceinline__ int32_t c_ohit(const EvDev &E, int32_t obj, int j)
     return (j & 1) ? E.md_hup[m] : E.md_hlo[m];
 }
 
-// WPS waves per seed: the objects of its event in the azimuth bins of its
-// link window, 64 at a time (wave q of the seed takes every WPS-th chunk);
-// window, then the link chi2 on the lanes inside it.  A block of PX_LW
-// waves takes PX_LW / WPS seeds per round (pT5: every seed; pT3: the seeds
-// that no kept pT5 uses, from their list), stages the accepted candidates in
-// LDS and reserves room for the round's candidates with one atomic, so each
-// seed's candidates are consecutive (its range in sd_c5 / sd_c3).  A wave
-// with more than PX_STAGE candidates scans again and writes the rest
-// directly.
-constexpr int PX_LW = 16, PX_STAGE = 64;
+// A candidate's key among those that share a hit: score, then the seed's
+// index in its event.  A score is a sum of squares over positive variances,
+// so its sign bit is free; the top two bits order the three duplicate
+// removals that share the per-hit minima, each below the ones before it (pT5
+// 2, pT3 1, pLS 0), so that the minima need no reset in between.
+template <int KIND>
+__device__ __forceinline__ unsigned long long c_key(float score, int32_t seed_local)
+{
+    return ((unsigned long long)(KIND == 5 ? 2 : 1) << 62) |
+           ((unsigned long long)(__float_as_uint(score) & 0x7fffffffu) << 31) | (uint32_t)seed_local;
+}
 
+// hit j of a candidate: pixel hits 0 .. 3, then the outer ones (may differ
+// between lanes); its minimum, its flag
+template <int KIND>
+__device__ __forceinline__ int32_t c_hit(const EvDev &E, int32_t s, int32_t obj, int j)
+{
+    return j < 4 ? E.sd_hits[4 * s + j] : c_ohit<KIND>(E, obj, j - 4);
+}
+
+template <int KIND>
+__device__ __forceinline__ unsigned long long *c_min(const EvDev &E, int32_t s, int32_t obj, int j)
+{
+    return (j < 4 ? E.hmin_p : E.hmin_o) + c_hit<KIND>(E, s, obj, j);
+}
+
+// NS seeds per wave: the objects of their events in the azimuth bins of their
+// link windows are walked as one list, 64 at a time; those inside the window
+// are queued in LDS, and the link chi2 runs on 64 of them together.  The chi2
+// is what costs here (some thousand instructions, a few objects per chunk
+// inside the window), so it runs on full waves and not once per chunk:
+// one PU200 event, pT5 / pT3 23.5 / 21.6 us with the minima of the duplicate
+// removal in a launch of their own (14.5 / 12.0), 24.8 / 27.2 with them here,
+// 21.1 / 22.8 on blocks of 4 waves instead of 16, 15.7 / 18.2 with the queue.
+// Two, four or eight seeds per wave: 16.6, 15.8, 18.9 us (pT5); one or two
+// 18.0, 17.6 (pT3).
+// A block reserves room for its round's candidates with one atomic; the queue
+// is in seed order, so each seed's candidates are consecutive (its range in
+// sd_c5 / sd_c3).  A wave with more than PX_STAGE candidates scans again and
+// writes the rest directly.
+constexpr int PX_LW = 4, PX_STAGE = 128;
+
+template <int NS>
 struct SmLink {
     int32_t obj[PX_LW][PX_STAGE];
     float score[PX_LW][PX_STAGE];
+    uint8_t slot[PX_LW][PX_STAGE];
+    int32_t qt[PX_LW][128];          // queue: object, seed of the wave
+    uint8_t qs[PX_LW][128];
+    float4 dir[PX_LW][NS];
+    float pix[PX_LW][NS][12];        // its four hits
     uint32_t cnt[PX_LW], base;
 };
 
-template <int KIND, int WPS>
-__device__ __forceinline__ void link_scan(const EvDev &E, const Consts &K, const PixConsts &P,
-                                          int s, int ev, const float4 &d, const LPt *pix, int q,
-                                          uint32_t &n_acc, SmLink &sm, int w, uint32_t write_base,
-                                          bool second)
+template <int KIND, int NS>
+__device__ __forceinline__ uint32_t link_scan(const EvDev &E, const Consts &K, const PixConsts &P,
+                                              int s0, int n_sd, uint32_t (&n_of)[NS], SmLink<NS> &sm,
+                                              int w, uint32_t write_base, bool second)
 {
-    constexpr int NP = 4 + KIND, IC = KIND == 5 ? 6 : 4;
+    constexpr int NP = 4 + KIND, IC = KIND == 5 ? 6 : 4, NR = 2 * NS;
     const int l = px_lane();
     const unsigned long long below = (1ull << l) - 1ull;
     const int32_t *off = pl(E, E.pl_off, KIND == 5 ? PXL_K5 : PXL_K3);
     const int32_t *lst = KIND == 5 ? E.pl_k5 : E.pl_k3;
     const float4 *dir = KIND == 5 ? E.pl_k5d : E.pl_k3d;   // in list order
     const float x2p = KIND == 5 ? P.x5p : P.x3p, x2z = KIND == 5 ? P.x5z : P.x3z;
-    int a[2], b[2];
-    window_bins(d, P.wphi, a[0], b[0], a[1], b[1]);
-    for (int part = 0; part < 2; ++part) {
-        if (a[part] > b[part]) continue;
-        const int32_t i0 = off[ev * PX_NB + a[part]] + 64 * q, i1 = off[ev * PX_NB + b[part] + 1];
-        // the next chunk's entries are loaded while this one is tested
-        int32_t tn = 0;
-        float4 dn = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (i0 + l < i1) {
-            tn = lst[i0 + l];
-            dn = dir[i0 + l];
-        }
-        for (int32_t i = i0 + l, base = i0; base < i1; base += 64 * WPS, i += 64 * WPS) {
-            const int32_t t = tn;
-            const float4 dt = dn;
-            if (i + 64 * WPS < i1) {
-                tn = lst[i + 64 * WPS];
-                dn = dir[i + 64 * WPS];
+    // the list ranges of the seeds' windows (two per seed: the wrap at +-pi)
+    int32_t from = 0, len = 0;
+    if (l < NR) {
+        const int s = s0 + (l >> 1);
+        if (s < n_sd && (KIND == 5 || !E.sd_used[s])) {
+            const float4 d = E.sd_dir[s];
+            const int ev = E.sd_ev[s];
+            int a[2], b[2];
+            window_bins(d, P.wphi, a[0], b[0], a[1], b[1]);
+            const int lo = (l & 1) ? a[1] : a[0], hi = (l & 1) ? b[1] : b[0];
+            if (lo <= hi) {
+                from = off[ev * PX_NB + lo];
+                len = off[ev * PX_NB + hi + 1] - from;
             }
-            bool ok = false;
-            float score = 0.0f;
-            if (i < i1 && link_window(d, dt, P.wl2)) {
-                LPt pts[NP];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) pts[k] = pix[k];
-#pragma unroll
-                for (int j = 0; j < KIND; ++j) pts[4 + j] = lpt_md(load_md(E, obj_md<KIND>(E, t, j)));
-                ok = link_accept<NP, IC>(K, pts, P.sig2p, P.sigz, x2p, x2z, score);
-            }
-            const unsigned long long m = __ballot(ok);
-            if (ok) {
-                const uint32_t pos = n_acc + (uint32_t)__popcll(m & below);
-                if (!second && pos < PX_STAGE) {
-                    sm.obj[w][pos] = t;
-                    sm.score[w][pos] = score;
-                } else if (second && pos >= PX_STAGE) {
-                    const uint32_t at = write_base + pos;
-                    if (at < (uint32_t)E.cap_pxc) {
-                        (KIND == 5 ? E.c5_seed : E.c3_seed)[at] = s;
-                        (KIND == 5 ? E.c5_obj : E.c3_obj)[at] = t;
-                        (KIND == 5 ? E.c5_score : E.c3_score)[at] = score;
-                    }
-                }
-            }
-            n_acc += (uint32_t)__popcll(m);
+            if (!(l & 1)) sm.dir[w][l >> 1] = d;
         }
     }
+    if (l < 4 * NS && s0 + (l >> 2) < n_sd) {
+        const int32_t h = E.sd_hits[4 * (s0 + (l >> 2)) + (l & 3)];
+        float *x = &sm.pix[w][l >> 2][3 * (l & 3)];
+        x[0] = E.px_x[h];
+        x[1] = E.px_y[h];
+        x[2] = E.px_z[h];
+    }
+    wave_lds_sync();
+    int32_t st[NR], pre[NR + 1];
+    pre[0] = 0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        st[r] = __builtin_amdgcn_readlane(from, r) - pre[r];
+        pre[r + 1] = pre[r] + __builtin_amdgcn_readlane(len, r);
+    }
+    const int32_t tot = pre[NR];
+#pragma unroll
+    for (int q = 0; q < NS; ++q) n_of[q] = 0;
+    uint32_t n_acc = 0;
+    int qn = 0;
+    // entry f of the joint list
+    auto entry = [&](int32_t f, int &q, int32_t &t, float4 &d) {
+        int32_t b = st[0];
+        q = 0;
+#pragma unroll
+        for (int r = 1; r < NR; ++r)
+            if (f >= pre[r]) {
+                b = st[r];
+                q = r >> 1;
+            }
+        if (f < tot) {
+            t = lst[b + f];
+            d = dir[b + f];
+        }
+    };
+    // the link chi2 of the queue's first n <= 64
+    auto link = [&](int n) {
+        bool ok = false;
+        float score = 0.0f;
+        int32_t t = 0;
+        int q = 0;
+        if (l < n) {
+            t = sm.qt[w][l];
+            q = sm.qs[w][l];
+            const float *x = sm.pix[w][q];
+            LPt pts[NP];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) pts[k] = lpt_px(x[3 * k], x[3 * k + 1], x[3 * k + 2]);
+#pragma unroll
+            for (int j = 0; j < KIND; ++j) pts[4 + j] = lpt_md(load_md(E, obj_md<KIND>(E, t, j)));
+            ok = link_accept<NP, IC>(K, pts, P.sig2p, P.sigz, x2p, x2z, score);
+        }
+        const unsigned long long m = __ballot(ok);
+        if (ok) {
+            const uint32_t pos = n_acc + (uint32_t)__popcll(m & below);
+            if (!second && pos < PX_STAGE) {
+                sm.obj[w][pos] = t;
+                sm.score[w][pos] = score;
+                sm.slot[w][pos] = (uint8_t)q;
+            } else if (second && pos >= PX_STAGE) {
+                const uint32_t at = write_base + pos;
+                if (at < (uint32_t)E.cap_pxc) {
+                    const int32_t s = s0 + q;
+                    (KIND == 5 ? E.c5_seed : E.c3_seed)[at] = s;
+                    (KIND == 5 ? E.c5_obj : E.c3_obj)[at] = t;
+                    (KIND == 5 ? E.c5_score : E.c3_score)[at] = score;
+                    for (int j = 0; j < 4 + 2 * KIND; ++j)
+                        atomicMin(c_min<KIND>(E, s, t, j), c_key<KIND>(score, E.sd_local[s]));
+                }
+            }
+        }
+        n_acc += (uint32_t)__popcll(m);
+#pragma unroll
+        for (int k = 0; k < NS; ++k) n_of[k] += (uint32_t)__popcll(m & __ballot(q == k));
+    };
+    int qx = 0;
+    int32_t tn = 0;
+    float4 dn = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    entry(l, qx, tn, dn);
+    for (int32_t f0 = 0; f0 < tot; f0 += 64) {
+        const int q = qx;
+        const int32_t t = tn;
+        const float4 dt = dn;
+        entry(f0 + 64 + l, qx, tn, dn);   // loaded while this chunk is tested
+        const bool in = f0 + l < tot && link_window(sm.dir[w][q], dt, P.wl2);
+        const unsigned long long m = __ballot(in);
+        if (in) {
+            const int at = qn + (int)__popcll(m & below);
+            sm.qt[w][at] = t;
+            sm.qs[w][at] = (uint8_t)q;
+        }
+        qn += (int)__popcll(m);
+        if (qn < 64) continue;
+        wave_lds_sync();
+        link(64);
+        qn -= 64;
+        const int32_t mt = sm.qt[w][64 + l];
+        const uint8_t ms = sm.qs[w][64 + l];
+        wave_lds_sync();
+        if (l < qn) {
+            sm.qt[w][l] = mt;
+            sm.qs[w][l] = ms;
+        }
+    }
+    wave_lds_sync();
+    if (qn > 0) link(qn);
+    wave_lds_sync();
+    return n_acc;
 }
 
-template <int KIND, int WPS>
+template <int KIND, int NS>
 __global__ __launch_bounds__(PX_LW * 64) void k_px_link(EvDev E, Consts K, PixConsts P)
 {
-    static_assert(PX_LW % WPS == 0, "whole seeds per block");
-    __shared__ SmLink sm;
-    const int l = px_lane(), w = (int)(threadIdx.x >> 6), q = w % WPS;
-    const int n = KIND == 5 ? E.desc[D_NSEEDS] : (int)E.gc[GC_PXFREE];
+    __shared__ SmLink<NS> sm;
+    const int l = px_lane(), w = (int)(threadIdx.x >> 6);
+    const int n = E.desc[D_NSEEDS];
     int32_t *c_seed = KIND == 5 ? E.c5_seed : E.c3_seed;
     int32_t *c_obj = KIND == 5 ? E.c5_obj : E.c3_obj;
     float *c_score = KIND == 5 ? E.c5_score : E.c3_score;
     int2 *sd_c = KIND == 5 ? E.sd_c5 : E.sd_c3;
-    constexpr int SPB = PX_LW / WPS;   // seeds per block and round
     if (upstream_overflow(E)) return;
-    for (int r0 = blockIdx.x * SPB; r0 < n; r0 += gridDim.x * SPB) {
-        const int v = r0 + w / WPS;
-        const bool act = v < n;
-        const int s = act ? (KIND == 5 ? v : E.sd_free[v]) : 0;
-        uint32_t n_acc = 0;
-        int ev = 0;
-        float4 d = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        LPt pix[4];
-        if (act) {
-            ev = E.sd_ev[s];
-            d = E.sd_dir[s];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int32_t h = E.sd_hits[4 * s + k];
-                pix[k] = lpt_px(E.px_x[h], E.px_y[h], E.px_z[h]);
-            }
-            link_scan<KIND, WPS>(E, K, P, s, ev, d, pix, q, n_acc, sm, w, 0u, false);
-        }
+    for (int r0 = blockIdx.x * PX_LW * NS; r0 < n; r0 += gridDim.x * PX_LW * NS) {
+        const int s0 = r0 + w * NS;
+        uint32_t n_of[NS];
+        const uint32_t n_acc = link_scan<KIND, NS>(E, K, P, s0, n, n_of, sm, w, 0u, false);
         if (l == 0) sm.cnt[w] = n_acc;
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -486,70 +610,46 @@ __global__ __launch_bounds__(PX_LW * 64) void k_px_link(EvDev E, Consts K, PixCo
             sm.base = tot ? atomicAdd(&E.gc[KIND == 5 ? GC_PX5 : GC_PX3], tot) : 0u;
         }
         __syncthreads();
-        // the waves of one seed are adjacent, so each seed's range is consecutive
         uint32_t mine = sm.base;
         for (int k = 0; k < w; ++k) mine += sm.cnt[k];
-        if (act) {
-            const uint32_t cap = (uint32_t)E.cap_pxc;
-            if (l == 0 && q == 0) {
-                uint32_t all = 0;
-                for (int k = 0; k < WPS; ++k) all += sm.cnt[w + k];
-                const uint32_t first = mine < cap ? mine : cap;
-                const uint32_t last = mine + all < cap ? mine + all : cap;
-                sd_c[s] = make_int2((int)first, (int)(last - first));
-                if (mine + all > cap) atomicOr(&E.gc[GC_OVERFLOW], 1u << OT_COUNT);
-            }
-            const uint32_t staged = n_acc < PX_STAGE ? n_acc : PX_STAGE;
-            for (uint32_t k = l; k < staged; k += 64) {
-                const uint32_t at = mine + k;
-                if (at < cap) {
-                    c_seed[at] = s;
-                    c_obj[at] = sm.obj[w][k];
-                    c_score[at] = sm.score[w][k];
-                }
-            }
-            if (n_acc > PX_STAGE) {
-                uint32_t again = 0;
-                link_scan<KIND, WPS>(E, K, P, s, ev, d, pix, q, again, sm, w, mine, true);
+        const uint32_t cap = (uint32_t)E.cap_pxc;
+        if (l == 0 && mine + n_acc > cap) atomicOr(&E.gc[GC_OVERFLOW], 1u << OT_COUNT);
+        uint32_t at = mine;   // each seed's range
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            const uint32_t first = at < cap ? at : cap;
+            at += n_of[q];
+            const uint32_t last = at < cap ? at : cap;
+            if (l == 0 && s0 + q < n) sd_c[s0 + q] = make_int2((int)first, (int)(last - first));
+        }
+        const uint32_t staged = n_acc < PX_STAGE ? n_acc : PX_STAGE;
+        for (uint32_t k = l; k < staged; k += 64) {
+            if (mine + k < cap) {
+                c_seed[mine + k] = s0 + sm.slot[w][k];
+                c_obj[mine + k] = sm.obj[w][k];
+                c_score[mine + k] = sm.score[w][k];
             }
         }
+        // into the minima of their hits, 16 lanes per candidate
+        const int j = l & 15;
+        for (uint32_t k = (uint32_t)(l >> 4); k < staged; k += 4)
+            if (mine + k < cap && j < 4 + 2 * KIND) {
+                const int32_t s = s0 + sm.slot[w][k];
+                atomicMin(c_min<KIND>(E, s, sm.obj[w][k], j),
+                          c_key<KIND>(sm.score[w][k], E.sd_local[s]));
+            }
+        if (n_acc > PX_STAGE)
+            (void)link_scan<KIND, NS>(E, K, P, s0, n, n_of, sm, w, mine, true);
         __syncthreads();   // the stage is rewritten by the next round
     }
 }
 
 // ---------------------------------------------------------------- duplicate removal
 template <int KIND>
-__device__ __forceinline__ unsigned long long c_key(const EvDev &E, uint32_t c)
-{
-    const float sc = KIND == 5 ? E.c5_score[c] : E.c3_score[c];
-    const int32_t s = KIND == 5 ? E.c5_seed[c] : E.c3_seed[c];
-    return ((unsigned long long)__float_as_uint(sc) << 32) | (uint32_t)E.sd_local[s];
-}
-
-template <int KIND>
 __device__ __forceinline__ uint32_t n_cand(const EvDev &E)
 {
     const uint32_t n = E.gc[KIND == 5 ? GC_PX5 : GC_PX3];
     return n < (uint32_t)E.cap_pxc ? n : (uint32_t)E.cap_pxc;
-}
-
-
-// every candidate's key (score bits, seed's index in its event) into the
-// per-hit minima of its collection
-template <int KIND>
-__global__ __launch_bounds__(BLOCK) void k_pxd_min(EvDev E)
-{
-    if (upstream_overflow(E)) return;
-    const uint32_t n = n_cand<KIND>(E);
-    for (uint32_t c = blockIdx.x * BLOCK + threadIdx.x; c < n; c += gridDim.x * BLOCK) {
-        const unsigned long long key = c_key<KIND>(E, c);
-        const int32_t s = KIND == 5 ? E.c5_seed[c] : E.c3_seed[c];
-        const int32_t o = KIND == 5 ? E.c5_obj[c] : E.c3_obj[c];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) atomicMin(&E.hmin_p[E.sd_hits[4 * s + k]], key);
-#pragma unroll
-        for (int j = 0; j < 2 * KIND; ++j) atomicMin(&E.hmin_o[c_ohit<KIND>(E, o, j)], key);
-    }
 }
 
 // per-event hit index of outer hit j of an object
@@ -559,58 +659,44 @@ __device__ __forceinline__ int32_t c_orig(const EvDev &E, int32_t obj, int j)
     return hit_orig(E, c_ohit<KIND>(E, obj, j));
 }
 
+// Lane j of the 16 of candidate c (act: there is one): does it survive among
+// the candidates that share its hit j?  True for the lanes without a hit.
+// Equal (score, seed): the smaller outer hit tuple wins; the seed's
+// candidates are consecutive, lane j compares every 16th.
 template <int KIND>
-__global__ __launch_bounds__(BLOCK) void k_pxd_keep(EvDev E, int n_mod)
+__device__ __forceinline__ bool c_keep16(const EvDev &E, uint32_t c, bool act, int32_t s, int32_t o,
+                                         float sc, int32_t h, int j)
 {
-    if (upstream_overflow(E)) return;
-    const uint32_t n = n_cand<KIND>(E);
-    for (uint32_t c0 = blockIdx.x * BLOCK; c0 < n; c0 += gridDim.x * BLOCK) {
-        const uint32_t c = c0 + threadIdx.x;
-        if (c >= n) continue;
-        const unsigned long long key = c_key<KIND>(E, c);
-        const int32_t s = KIND == 5 ? E.c5_seed[c] : E.c3_seed[c];
-        const int32_t o = KIND == 5 ? E.c5_obj[c] : E.c3_obj[c];
-        bool keep = true;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) keep = keep && E.hmin_p[E.sd_hits[4 * s + k]] == key;
-#pragma unroll
-        for (int j = 0; j < 2 * KIND; ++j) keep = keep && E.hmin_o[c_ohit<KIND>(E, o, j)] == key;
-        if (keep) {
-            // equal (score, seed): the smaller outer hit tuple wins; the
-            // seed's candidates are consecutive
-            const float sc = KIND == 5 ? E.c5_score[c] : E.c3_score[c];
-            const int2 rg = (KIND == 5 ? E.sd_c5 : E.sd_c3)[s];
-            for (uint32_t u = (uint32_t)rg.x; u < (uint32_t)(rg.x + rg.y) && keep; ++u) {
-                if (u == c) continue;
-                const float scu = KIND == 5 ? E.c5_score[u] : E.c3_score[u];
-                if (__float_as_uint(scu) != __float_as_uint(sc)) continue;
-                const int32_t ou = KIND == 5 ? E.c5_obj[u] : E.c3_obj[u];
-                for (int j = 0; j < 2 * KIND; ++j) {
-                    const int32_t a = c_orig<KIND>(E, ou, j), b = c_orig<KIND>(E, o, j);
-                    if (a != b) {
-                        if (a < b) keep = false;
-                        break;
-                    }
+    const int g = px_lane() & 48;
+    bool ok = true;
+    if (act && j < 4 + 2 * KIND)
+        ok = (j < 4 ? E.hmin_p : E.hmin_o)[h] == c_key<KIND>(sc, E.sd_local[s]);
+    if ((((__ballot(ok) >> g) & 0xffffull) == 0xffffull) && act) {
+        const int2 rg = (KIND == 5 ? E.sd_c5 : E.sd_c3)[s];
+        for (uint32_t u = (uint32_t)(rg.x + j); u < (uint32_t)(rg.x + rg.y); u += 16) {
+            if (u == c) continue;
+            const float scu = KIND == 5 ? E.c5_score[u] : E.c3_score[u];
+            if (__float_as_uint(scu) != __float_as_uint(sc)) continue;
+            const int32_t ou = KIND == 5 ? E.c5_obj[u] : E.c3_obj[u];
+            for (int k = 0; k < 2 * KIND; ++k) {
+                const int32_t a = c_orig<KIND>(E, ou, k), b = c_orig<KIND>(E, o, k);
+                if (a != b) {
+                    if (a < b) ok = false;
+                    break;
                 }
             }
         }
-        if (KIND == 5) {
-            E.c5_keep[c] = keep;
-            if (keep) E.sd_used[s] = 1;
-            (void)agg_add(pl(E, E.pl_cnt, PXL_D5), E.sd_ev[s] * PX_NB + dir_bin(E.sd_dir[s]), keep);
-        } else {
-            E.c3_keep[c] = keep;
-        }
     }
-    (void)n_mod;
+    return ok;
 }
 
 // ---------------------------------------------------------------- cross-cleaning
-// any direction of the event's list within dr2 of d: the whole wave scans
-// the list's azimuth bins around d (half-width wdr) 64 entries at a time
-// (wave-uniform arguments)
+// any direction of the event's list, of an entry that takes(i), within dr2 of
+// d: the whole wave scans the list's azimuth bins around d (half-width wdr) 64
+// entries at a time (wave-uniform arguments)
+template <class F>
 __device__ __forceinline__ bool wave_near_any(const EvDev &E, int list, int ev, const float4 *dirs,
-                                              const float4 &d, float dr2, float wdr)
+                                              const float4 &d, float dr2, float wdr, F &&takes)
 {
     const int32_t *off = pl(E, E.pl_off, list);
     int a[2], b[2];
@@ -620,7 +706,13 @@ __device__ __forceinline__ bool wave_near_any(const EvDev &E, int list, int ev, 
         const int32_t i0 = off[ev * PX_NB + a[part]], i1 = off[ev * PX_NB + b[part] + 1];
         for (int32_t bb = i0; bb < i1; bb += 64) {
             const int32_t i = bb + px_lane();
-            if (__ballot(i < i1 && close_dir(d, dirs[i], dr2))) return true;
+            bool near = false;
+            if (i < i1) {
+                const float4 q = dirs[i];   // loaded along with the entry's state
+                const bool in = takes(i);
+                near = close_dir(d, q, dr2) && in;
+            }
+            if (__ballot(near)) return true;
         }
     }
     return false;
@@ -635,140 +727,81 @@ __device__ __forceinline__ void wave_run(uint32_t n, uint32_t &first, uint32_t &
     last = first + PX_WCHUNK < n ? first + PX_WCHUNK : n;
 }
 
-// surviving pT5: their directions into the event list, their hits flagged
-__global__ __launch_bounds__(BLOCK) void k_pt5_mark(EvDev E)
+// Surviving pT5 and pT3, 16 lanes per candidate: one per hit, so that a
+// candidate's reads take one chain of loads instead of one after another
+// (PU200, pT5 / pT3: keep, mark and, for the pT3, clean 31 / 32 us with a
+// thread per candidate and a launch each, 4.8 / 10.2 us here).
+// Hits and seeds of a survivor are marked, 1 for a pT5 and 2 for a pT3; a
+// seed's mark also goes to its place in the seeds' azimuth list, which is the
+// list of the survivors' directions (a seed has one survivor at most).  A pT3
+// near a pT5 or sharing a hit with one is a duplicate: it looks for ones
+// only, so the marks of the pT3 set meanwhile don't matter to it.
+template <int KIND>
+__global__ __launch_bounds__(BLOCK) void k_pxd_keep(EvDev E, PixConsts P)
 {
+    constexpr uint8_t MARK = KIND == 5 ? 1 : 2;
     if (upstream_overflow(E)) return;
-    const uint32_t n = n_cand<5>(E);
-    const int32_t *off = pl(E, E.pl_off, PXL_D5);
-    int32_t *fill = pl(E, E.pl_fill, PXL_D5);
-    for (uint32_t c0 = blockIdx.x * BLOCK; c0 < n; c0 += gridDim.x * BLOCK) {
-        const uint32_t c = c0 + threadIdx.x;
-        const bool act = c < n && E.c5_keep[c];
-        int32_t s = 0;
-        int ev = 0;
+    const uint32_t n = n_cand<KIND>(E);
+    const int l = px_lane(), j = l & 15, g = l & 48;
+    for (uint32_t c0 = blockIdx.x * (BLOCK / 16); c0 < n; c0 += gridDim.x * (BLOCK / 16)) {
+        const uint32_t c = c0 + (threadIdx.x >> 4);
+        const bool act = c < n, hit = act && j < 4 + 2 * KIND;
+        int32_t s = 0, o = 0, h = 0;
+        float sc = 0.0f;
         if (act) {
-            s = E.c5_seed[c];
-            ev = E.sd_ev[s] * PX_NB + dir_bin(E.sd_dir[s]);
+            s = (KIND == 5 ? E.c5_seed : E.c3_seed)[c];
+            o = (KIND == 5 ? E.c5_obj : E.c3_obj)[c];
+            sc = (KIND == 5 ? E.c5_score : E.c3_score)[c];
         }
-        const int32_t at = agg_add(fill, ev, act);
-        if (!act) continue;
-        const int32_t o = E.c5_obj[c];
-        E.pl_d5[off[ev] + at] = E.sd_dir[s];
-        for (int k = 0; k < 4; ++k) E.hflag_p[E.sd_hits[4 * s + k]] = 1;
-        for (int j = 0; j < 10; ++j) E.hflag_o[c_ohit<5>(E, o, j)] = 1;
-    }
-    // the pT5 minima are read no more: reset for the pT3 duplicate removal
-    rekey_body(E, true);
-}
-
-// pT3 near a pT5 or sharing a hit with one are duplicates (one wave per
-// candidate: lane k < 4 reads pixel hit k's flag, lane 4 + j outer hit j's)
-__global__ __launch_bounds__(BLOCK) void k_pt3_clean(EvDev E, PixConsts P)
-{
-    if (upstream_overflow(E)) return;
-    const uint32_t n = n_cand<3>(E);
-    const int l = px_lane();
-    int32_t *cnt = pl(E, E.pl_cnt, PXL_D3);
-    uint32_t first, last, step;
-    wave_run(n, first, last, step);
-    for (; first < n; first += step, last = first + PX_WCHUNK < n ? first + PX_WCHUNK : n) {
-        EvRun run;
-        for (uint32_t c = first; c < last; ++c) {
-            if (!E.c3_keep[c]) continue;
-            const int32_t s = E.c3_seed[c], o = E.c3_obj[c];
-            bool hit = false;
-            if (l < 4) hit = E.hflag_p[E.sd_hits[4 * s + l]] != 0;
-            else if (l < 10) hit = E.hflag_o[c_ohit<3>(E, o, l - 4)] != 0;
-            const int ev = E.sd_ev[s];
-            const float4 d = E.sd_dir[s];
-            bool keep = __ballot(hit) == 0ull;
-            if (keep) keep = !wave_near_any(E, PXL_D5, ev, E.pl_d5, d, P.dr2, P.wdr);
-            if (l == 0) E.c3_keep[c] = keep;
-            if (keep) run.add(cnt, ev * PX_NB + dir_bin(d));
+        if (hit) h = c_hit<KIND>(E, s, o, j);
+        uint8_t *flag = (j < 4 ? E.hflag_p : E.hflag_o) + h;
+        bool ok = c_keep16<KIND>(E, c, act, s, o, sc, h, j) && act;
+        if (KIND == 3) {
+            if (hit && *flag == 1) ok = false;
+            unsigned long long m = __ballot(ok);
+            for (int q = 0; q < 64; q += 16) {
+                if (((m >> q) & 0xffffull) != 0xffffull) continue;
+                const int sq = __builtin_amdgcn_readlane(s, q);
+                if (wave_near_any(E, PXL_SD, E.sd_ev[sq], E.pl_sdd, E.sd_dir[sq], P.dr2, P.wdr,
+                                  [&](int32_t i) { return E.pl_sdk[i] == 1; }) && g == q)
+                    ok = false;
+            }
         }
-        run.flush(cnt);
+        const bool keep = ((__ballot(ok) >> g) & 0xffffull) == 0xffffull;
+        if (act && j == 0) {
+            (KIND == 5 ? E.c5_keep : E.c3_keep)[c] = keep;
+            if (keep) {
+                E.sd_used[s] = 1;
+                E.pl_sdk[E.sd_pos[s]] = MARK;
+            }
+        }
+        if (keep && hit) *flag = MARK;
     }
 }
 
-// cleaned pT3: directions into the event list, hits flagged, seeds used
-__global__ __launch_bounds__(BLOCK) void k_pt3_mark(EvDev E)
-{
-    if (upstream_overflow(E)) return;
-    const uint32_t n = n_cand<3>(E);
-    const int32_t *off = pl(E, E.pl_off, PXL_D3);
-    int32_t *fill = pl(E, E.pl_fill, PXL_D3);
-    for (uint32_t c0 = blockIdx.x * BLOCK; c0 < n; c0 += gridDim.x * BLOCK) {
-        const uint32_t c = c0 + threadIdx.x;
-        const bool act = c < n && E.c3_keep[c];
-        int32_t s = 0;
-        int ev = 0;
-        if (act) {
-            s = E.c3_seed[c];
-            ev = E.sd_ev[s] * PX_NB + dir_bin(E.sd_dir[s]);
-        }
-        const int32_t at = agg_add(fill, ev, act);
-        if (!act) continue;
-        const int32_t o = E.c3_obj[c];
-        E.pl_d3[off[ev] + at] = E.sd_dir[s];
-        E.sd_used[s] = 1;
-        for (int k = 0; k < 4; ++k) E.hflag_p[E.sd_hits[4 * s + k]] = 1;
-        for (int j = 0; j < 6; ++j) E.hflag_o[c_ohit<3>(E, o, j)] = 1;
-    }
-}
-
-// kept quintuplets near, or sharing a hit with, a pT5 or cleaned pT3
+// kept quintuplets near, or sharing a hit with, a pT5 or cleaned pT3 (in list
+// order: those left are the list's entries with pl_k5k set)
 __global__ __launch_bounds__(BLOCK) void k_t5_clean(EvDev E, PixConsts P, int n_mod)
 {
-    __shared__ uint32_t s_pre[NSH + 1];
     if (upstream_overflow(E)) return;
-    const uint32_t n5 = obj_prefix(E, OT_T5, s_pre);
+    const uint32_t n5 = (uint32_t)pl(E, E.pl_off, PXL_K5)[E.desc[D_NEV] * PX_NB];
     const int l = px_lane();
-    int32_t *cnt = pl(E, E.pl_cnt, PXL_DT);
     uint32_t first, last, step;
     wave_run(n5, first, last, step);
     for (; first < n5; first += step, last = first + PX_WCHUNK < n5 ? first + PX_WCHUNK : n5) {
-        EvRun run;
         for (uint32_t v = first; v < last; ++v) {
-            const int32_t t = obj_at(E, OT_T5, s_pre, v);
-            bool keep = E.t5_keep[t] != 0;
-            if (keep) {
-                const bool hit = l < 10 && E.hflag_o[c_ohit<5>(E, t, l)] != 0;
-                keep = __ballot(hit) == 0ull;
-                const int ev = md_event(E, E.t5_md0[t], n_mod);
-                const float4 d = E.t5_dir[t];
-                if (keep) keep = !wave_near_any(E, PXL_D5, ev, E.pl_d5, d, P.dr2, P.wdr);
-                if (keep) keep = !wave_near_any(E, PXL_D3, ev, E.pl_d3, d, P.dr2, P.wdr);
-                if (keep) run.add(cnt, ev * PX_NB + dir_bin(d));
+            const int32_t t = E.pl_k5[v];
+            const bool hit = l < 10 && E.hflag_o[c_ohit<5>(E, t, l)] != 0;
+            bool keep = __ballot(hit) == 0ull;
+            if (keep)
+                keep = !wave_near_any(E, PXL_SD, md_event(E, E.t5_md0[t], n_mod), E.pl_sdd, E.pl_k5d[v],
+                                      P.dr2, P.wdr, [&](int32_t i) { return E.pl_sdk[i] != 0; });
+            if (l == 0) {
+                E.t5_clean[t] = keep;
+                E.pl_k5k[v] = keep;
             }
-            if (l == 0) E.t5_clean[t] = keep;
         }
-        run.flush(cnt);
     }
-}
-
-__global__ __launch_bounds__(BLOCK) void k_t5_clean_fill(EvDev E, int n_mod)
-{
-    __shared__ uint32_t s_pre[NSH + 1];
-    if (upstream_overflow(E)) return;
-    const uint32_t n5 = obj_prefix(E, OT_T5, s_pre);
-    const int32_t *off = pl(E, E.pl_off, PXL_DT);
-    int32_t *fill = pl(E, E.pl_fill, PXL_DT);
-    for (uint32_t v0 = blockIdx.x * BLOCK; v0 < n5; v0 += gridDim.x * BLOCK) {
-        const uint32_t v = v0 + threadIdx.x;
-        int32_t t = 0;
-        int ev = 0;
-        bool act = false;
-        if (v < n5) {
-            t = obj_at(E, OT_T5, s_pre, v);
-            act = E.t5_clean[t] != 0;
-            if (act) ev = md_event(E, E.t5_md0[t], n_mod) * PX_NB + dir_bin(E.t5_dir[t]);
-        }
-        const int32_t at = agg_add(fill, ev, act);
-        if (act) E.pl_dt[off[ev] + at] = E.t5_dir[t];
-    }
-    // the pT3 minima are read no more: reset for the pLS cleaning
-    rekey_body(E, false);
 }
 
 // unlinked pLS: a pixel hit held by a candidate, or near one, is a
@@ -787,9 +820,12 @@ __global__ __launch_bounds__(BLOCK) void k_pls_clean(EvDev E, PixConsts P)
             bool keep = __ballot(hit) == 0ull;
             const int ev = E.sd_ev[s];
             const float4 d = E.sd_dir[s];
-            if (keep) keep = !wave_near_any(E, PXL_D5, ev, E.pl_d5, d, P.dr2, P.wdr);
-            if (keep) keep = !wave_near_any(E, PXL_D3, ev, E.pl_d3, d, P.dr2, P.wdr);
-            if (keep) keep = !wave_near_any(E, PXL_DT, ev, E.pl_dt, d, P.dr2, P.wdr);
+            if (keep)
+                keep = !wave_near_any(E, PXL_SD, ev, E.pl_sdd, d, P.dr2, P.wdr,
+                                      [&](int32_t i) { return E.pl_sdk[i] != 0; });
+            if (keep)
+                keep = !wave_near_any(E, PXL_K5, ev, E.pl_k5d, d, P.dr2, P.wdr,
+                                      [&](int32_t i) { return E.pl_k5k[i] != 0; });
             if (l == 0) E.sd_keep[s] = keep;
             if (keep && l < 4)
                 atomicMin(&E.hmin_p[E.sd_hits[4 * s + l]], (unsigned long long)(uint32_t)E.sd_local[s]);
@@ -831,38 +867,31 @@ hipError_t launch_pixel(const EvDev &E, const Consts &K, const PixConsts &P, hip
     const int n_mod = E.cap_slots / E.cap_ev;
     const int g_hits = px_grid(std::max<int64_t>(E.cap_hits, E.cap_px), BLOCK);
     const int g_sd = px_grid(E.cap_seeds, BLOCK);
-    // waves per seed in the link scans: a pT5 window holds a few dozen kept
+    // seeds per wave in the link scans: a pT5 window holds a few dozen kept
     // quintuplets, a pT3 window hundreds of triplets
-    constexpr int PX_WPS5 = 1, PX_WPS3 = 4;
-    const int g_link5 = px_grid(E.cap_seeds, PX_LW / PX_WPS5);
-    const int g_link3 = px_grid(E.cap_seeds, PX_LW / PX_WPS3);
-    const int g_c = px_grid(E.cap_pxc, BLOCK);
-    const int g_obj = px_grid((int64_t)E.rc[OT_T3] * NSH, BLOCK);
+    constexpr int PX_NS5 = 4, PX_NS3 = 2;
+    const int g_link5 = px_grid(E.cap_seeds, PX_LW * PX_NS5);
+    const int g_link3 = px_grid(E.cap_seeds, PX_LW * PX_NS3);
+    const int g_obj = px_grid((int64_t)(E.rc[OT_T3] + E.rc[OT_T5]) * NSH + E.cap_seeds, BLOCK);
+    const int g_keep = px_grid(E.cap_pxc, BLOCK / 16);
     // one wave per object, PX_WCHUNK objects per wave
-    const int g_cw = px_grid(E.cap_pxc, WAVES * PX_WCHUNK);
     const int g_objw = px_grid((int64_t)E.rc[OT_T5] * NSH, WAVES * PX_WCHUNK);
     const int g_sdc = px_grid(E.cap_seeds, WAVES * PX_WCHUNK);
     hipLaunchKernelGGL(k_px_init, dim3(g_hits), dim3(BLOCK), 0, s, E);
     hipLaunchKernelGGL(k_obj_dir, dim3(g_obj), dim3(BLOCK), 0, s, E, n_mod);
-    hipLaunchKernelGGL(k_pl_scan, dim3(2), dim3(1024), 0, s, E, (int)PXL_K5, (int)PXL_K3, PX_NB);
-    hipLaunchKernelGGL(k_obj_fill, dim3(g_obj), dim3(BLOCK), 0, s, E, n_mod);
-    // pT5
-    hipLaunchKernelGGL((k_px_link<5, PX_WPS5>), dim3(g_link5), dim3(PX_LW * 64), 0, s, E, K, P);
-    hipLaunchKernelGGL(k_pxd_min<5>, dim3(g_c), dim3(BLOCK), 0, s, E);
-    hipLaunchKernelGGL(k_pxd_keep<5>, dim3(g_c), dim3(BLOCK), 0, s, E, n_mod);
-    hipLaunchKernelGGL(k_pl_scan, dim3(1), dim3(1024), 0, s, E, (int)PXL_D5, (int)PXL_D5, PX_NB);
-    hipLaunchKernelGGL(k_pt5_mark, dim3(std::max(g_c, g_hits)), dim3(BLOCK), 0, s, E);
+    if (E.cap_ev <= PX_SELF) {
+        hipLaunchKernelGGL(k_obj_fill<true>, dim3(g_obj), dim3(BLOCK), 0, s, E, n_mod);
+    } else {
+        hipLaunchKernelGGL(k_pl_scan, dim3(PXL_COUNT), dim3(1024), 0, s, E);
+        hipLaunchKernelGGL(k_obj_fill<false>, dim3(g_obj), dim3(BLOCK), 0, s, E, n_mod);
+    }
+    hipLaunchKernelGGL((k_px_link<5, PX_NS5>), dim3(g_link5), dim3(PX_LW * 64), 0, s, E, K, P);
+    hipLaunchKernelGGL(k_pxd_keep<5>, dim3(g_keep), dim3(BLOCK), 0, s, E, P);
     // pT3 from the seeds no pT5 uses
-    hipLaunchKernelGGL((k_px_link<3, PX_WPS3>), dim3(g_link3), dim3(PX_LW * 64), 0, s, E, K, P);
-    hipLaunchKernelGGL(k_pxd_min<3>, dim3(g_c), dim3(BLOCK), 0, s, E);
-    hipLaunchKernelGGL(k_pxd_keep<3>, dim3(g_c), dim3(BLOCK), 0, s, E, n_mod);
+    hipLaunchKernelGGL((k_px_link<3, PX_NS3>), dim3(g_link3), dim3(PX_LW * 64), 0, s, E, K, P);
+    hipLaunchKernelGGL(k_pxd_keep<3>, dim3(g_keep), dim3(BLOCK), 0, s, E, P);
     // cross-cleaning
-    hipLaunchKernelGGL(k_pt3_clean, dim3(g_cw), dim3(BLOCK), 0, s, E, P);
-    hipLaunchKernelGGL(k_pl_scan, dim3(1), dim3(1024), 0, s, E, (int)PXL_D3, (int)PXL_D3, PX_NB);
-    hipLaunchKernelGGL(k_pt3_mark, dim3(g_c), dim3(BLOCK), 0, s, E);
     hipLaunchKernelGGL(k_t5_clean, dim3(g_objw), dim3(BLOCK), 0, s, E, P, n_mod);
-    hipLaunchKernelGGL(k_pl_scan, dim3(1), dim3(1024), 0, s, E, (int)PXL_DT, (int)PXL_DT, PX_NB);
-    hipLaunchKernelGGL(k_t5_clean_fill, dim3(std::max(g_obj, g_hits)), dim3(BLOCK), 0, s, E, n_mod);
     hipLaunchKernelGGL(k_pls_clean, dim3(g_sdc), dim3(BLOCK), 0, s, E, P);
     hipLaunchKernelGGL(k_pls_keep, dim3(g_sd), dim3(BLOCK), 0, s, E);
     return hipGetLastError();
