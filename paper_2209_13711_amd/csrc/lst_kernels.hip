@@ -573,7 +573,9 @@ __host__ __device__ __forceinline__ int group_mods(int n_mod) { return (n_mod + 
 
 // f(hit, module, sensor) for every hit: four consecutive hits per 16-byte
 // load of the module ids, the last one to three hits one per thread.  A
-// wave's active lanes are always its first ones.
+// wave's active lanes are always its first ones, but not always the same: of
+// the lanes that take the last one to three hits, all but the first may have
+// sat out the last groups of four (6, 7 or 11 hits past a multiple of 4096).
 template <class F>
 __device__ __forceinline__ void each_hit_id(const HitsIn &in, int n_hits, F &&f)
 {
@@ -626,17 +628,21 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
     for (int k = threadIdx.x; k < n_bin; k += GROUP_BLOCK) s_bin[k] = 0u;
     if (threadIdx.x == 0) s_before = s_bad = s_full = 0u;
     __syncthreads();
-    uint32_t before = 0, own = 0;           // the wave's hits before the range, in it
+    // the wave's hits before the range and in it, as its first active lane
+    // counts them: that is lane 0, which takes part in every ballot, and the
+    // places in the list have to come from one count
+    uint32_t before = 0, own = 0;
     auto mine = [&](int h, uint32_t dm, uint32_t s, bool in) {
         const unsigned long long mk = __ballot(in);
         if (!mk) return;
+        const uint32_t listed = (uint32_t)__builtin_amdgcn_readfirstlane((int)own);
         if (in) {
             const int key = 2 * (int)dm + (int)s;
             atomicAdd(&s_bin[key], 1u);
-            const uint32_t at = own + (uint32_t)__popcll(mk & lanes_below());
+            const uint32_t at = listed + (uint32_t)__popcll(mk & lanes_below());
             if (at < (uint32_t)GROUP_LIST) s_list[at] = make_int2(h, key);
         }
-        own += (uint32_t)__popcll(mk);
+        own = listed + (uint32_t)__popcll(mk);
     };
     uint32_t m_max = 0, s_bits = 0;
     each_hit_id(in, n_hits, [&](int h, int32_t m, uint32_t s) {
@@ -660,7 +666,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
         });
     }
     if (bad) s_bad = 1u;
-    // lanes past the hits of a last, partial group missed its counts
+    // (the lanes that sat out a partial group missed its counts)
     before = (uint32_t)__builtin_amdgcn_readfirstlane((int)before);
     own = (uint32_t)__builtin_amdgcn_readfirstlane((int)own);
     if (l == 0) {
