@@ -1348,6 +1348,12 @@ struct ShardCounts {
     uint32_t rc[OT_COUNT];
     uint32_t n(int t, int s) const { return std::min(gc[gc_shard(t, s)], rc[t]); }
     size_t span(int t) const { return (size_t)rc[t] * NSH; }
+    uint32_t error() const
+    {
+        uint32_t e = gc[GC_ERROR];
+        for (int i = 0; i < GROUP_PARTS; ++i) e |= gc[GC_GROUP + i];
+        return e;
+    }
     int64_t stored(int t) const
     {
         int64_t k = 0;
@@ -1688,8 +1694,8 @@ static int chain_checksum(lst_ctx *c, uint64_t *out)
     ShardCounts S;
     int rc = read_shards(c, S);
     if (rc) return rc;
-    if (S.gc[GC_OVERFLOW] || S.gc[GC_ERROR] & 6)
-        return fail(c, LST_E_CAPACITY, "tuning run overflowed or timed out (%u, %u)", S.gc[GC_OVERFLOW], S.gc[GC_ERROR]);
+    if (S.gc[GC_OVERFLOW] || S.error() & 6)
+        return fail(c, LST_E_CAPACITY, "tuning run overflowed or timed out (%u, %u)", S.gc[GC_OVERFLOW], S.error());
     std::vector<int32_t> sorig, hlo, hup, slot, m[5];
     std::vector<uint8_t> keep;
     if ((rc = sorted_orig(c, sorig, S.gc[GC_N_SORTED])) || (rc = d2h(c, hlo, E.md_hlo, S.span(OT_MD))) ||

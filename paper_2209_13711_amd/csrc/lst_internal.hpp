@@ -32,7 +32,7 @@ enum ObjType { OT_MD = 0, OT_SEG, OT_T3, OT_T5, OT_COUNT };
 constexpr int GC_PAD = 64;   // uint32 stride of padded counters
 enum GlobalCounter {
     GC_OVERFLOW = 0,   // bit k: object type k ran out of its region
-    GC_ERROR,          // bit 0: invalid hit skipped
+    GC_ERROR,          // error flags; those of GC_GROUP come on top
     GC_N_SORTED,       // number of grouped hits
     GC_TIEPOOL,        // entries taken from the dedup tie pool
     GC_SCAN,           // tile tickets of the look-back scan
@@ -42,7 +42,13 @@ enum GlobalCounter {
     GC_SH = GC_PAD     // [OT_COUNT][NSH] reservation shards, one line each
 };
 __host__ __device__ constexpr int gc_shard(int type, int s) { return GC_SH + (type * NSH + s) * GC_PAD; }
-constexpr int GC_COUNT = GC_SH + OT_COUNT * NSH * GC_PAD;
+// after the shards: a word for each range of modules of the one-launch grouping
+// (GROUP_PARTS), nonzero when its hits did not fit the positions it had counted
+// (part of the error flags).  Every block stores its own word, so the words
+// need no clearing before the launch.
+constexpr int GROUP_PARTS = 256;      // one block per CU
+constexpr int GC_GROUP = GC_SH + OT_COUNT * NSH * GC_PAD;
+constexpr int GC_COUNT = GC_GROUP + GROUP_PARTS;
 
 
 // MI355X dispatches workgroup i to XCD i % 8, and each XCD has its own L2.

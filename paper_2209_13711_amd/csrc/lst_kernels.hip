@@ -565,7 +565,6 @@ __global__ __launch_bounds__(SORT_EV_BLOCK) void k_scatter_ev(EvDev E, ModDev M)
 // (128 ranges: 2.3 us more).
 constexpr int GROUP_BLOCK = 1024;
 constexpr int GROUP_WAVES = GROUP_BLOCK / 64;
-constexpr int GROUP_PARTS = 256;      // one block per CU
 constexpr int GROUP_LIST = 256;       // hits of its range a wave lists in LDS; more are found by a second read
 constexpr int GROUP_ILP = 8;          // groups of four hits whose ids a thread loads together
 
@@ -618,7 +617,7 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
     uint32_t *s_bin = s_dyn + 2 * GROUP_LIST * GROUP_WAVES;
     // the chain's counters; the two words this kernel itself reports through
     // are stored by the last block alone
-    for (int i = blockIdx.x * GROUP_BLOCK + threadIdx.x; i < GC_COUNT; i += gridDim.x * GROUP_BLOCK)
+    for (int i = blockIdx.x * GROUP_BLOCK + threadIdx.x; i < GC_GROUP; i += gridDim.x * GROUP_BLOCK)
         if (i != GC_ERROR && i != GC_N_SORTED) E.gc[i] = 0u;
     const int n_hits = E.desc[D_NHITS];
     const HitsIn in = hits_at(E.hits, n_hits);
@@ -699,9 +698,18 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
         E.gc[GC_ERROR] = s_bad;
     }
     __syncthreads();
+    bool wrong = false;     // inconsistent grouping: nothing is read or written for it
     auto put = [&](int h, int key) {
+        if ((uint32_t)h >= (uint32_t)n_hits || (uint32_t)key >= (uint32_t)n_bin) {
+            wrong = true;
+            return;
+        }
         const float x = in.x[h], y = in.y[h], z = in.z[h];
         const uint32_t pos = atomicAdd(&s_bin[key], 1u);
+        if (pos >= (uint32_t)E.cap_hits) {
+            wrong = true;
+            return;
+        }
         if (E.half16)
             E.hsort_h[pos] = half_hit(mod_frame(M, (int)m0 + (key >> 1)), x, y, z, h);
         else
@@ -714,6 +722,8 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
             if ((uint32_t)m - m0 < n_m && s <= 1u) put(h, 2 * (m - (int)m0) + (int)s);
         });
     }
+    wrong = __syncthreads_or(wrong) != 0;
+    if (threadIdx.x == 0) E.gc[GC_GROUP + part] = wrong ? 4u : 0u;
 }
 
 static size_t group_lds_bytes(int n_mod)

@@ -25,14 +25,17 @@ namespace lst {
 
 __device__ __forceinline__ int rd_lane() { return threadIdx.x & 63; }
 
-// the chain's counters as the host getters need them
+// the chain's counters as the host getters need them (every thread of the block calls it)
 __device__ __forceinline__ void put_header(const EvDev &E, ReadHdr *h)
 {
+    uint32_t group = 0;
+    for (int i = threadIdx.x; i < GROUP_PARTS; i += blockDim.x) group |= E.gc[GC_GROUP + i];
+    const bool fault = __syncthreads_or(group != 0u) != 0;
     for (int i = threadIdx.x; i < OT_COUNT * NSH; i += blockDim.x)
         h->shard[i / NSH][i % NSH] = E.gc[gc_shard(i / NSH, i % NSH)];
     if (threadIdx.x == 0) {
         h->overflow = E.gc[GC_OVERFLOW];
-        h->error = E.gc[GC_ERROR];
+        h->error = E.gc[GC_ERROR] | (fault ? 4u : 0u);
     }
 }
 
