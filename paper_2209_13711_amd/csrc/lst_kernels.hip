@@ -609,12 +609,15 @@ __device__ __forceinline__ void each_hit_id(const HitsIn &in, int n_hits, F &&f)
 
 __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
 {
-    extern __shared__ uint32_t s_dyn[];     // the waves' lists, then the bins [2 group_mods(n_mod)]
+    // the waves' lists, whose type aligns the block to their 8-byte entries,
+    // then the bins [2 group_mods(n_mod)]
+    extern __shared__ int2 s_dyn[];
+    static_assert(alignof(int2) == 8, "entries are written 8 bytes at a time");
     __shared__ uint32_t s_before, s_bad, s_full, s_w[GROUP_WAVES], s_own[GROUP_WAVES];
     const int n_mod = M.n_mod, per_part = group_mods(n_mod), part = blockIdx.x;
     const int w = wave_id(), l = lane_id();
-    int2 *s_list = reinterpret_cast<int2 *>(s_dyn) + w * GROUP_LIST;
-    uint32_t *s_bin = s_dyn + 2 * GROUP_LIST * GROUP_WAVES;
+    int2 *s_list = s_dyn + w * GROUP_LIST;
+    uint32_t *s_bin = reinterpret_cast<uint32_t *>(s_dyn + GROUP_LIST * GROUP_WAVES);
     // the chain's counters; the two words this kernel itself reports through
     // are stored by the last block alone
     for (int i = blockIdx.x * GROUP_BLOCK + threadIdx.x; i < GC_GROUP; i += gridDim.x * GROUP_BLOCK)
