@@ -20,6 +20,14 @@ __device__ __forceinline__ bool upstream_overflow(const EvDev &E)
     return E.gc[GC_OVERFLOW] != 0u;
 }
 
+// Objects that the getters' kernels must not follow: a stage overflowed, or a
+// wait of the grouping or of a grid barrier timed out, after which the stored
+// indices may be of any value.
+__device__ __forceinline__ bool objects_unusable(const EvDev &E)
+{
+    return upstream_overflow(E) || (E.gc[GC_ERROR] & 6u) != 0u;
+}
+
 // per-event index of grouped hit h (either storage)
 __device__ __forceinline__ int32_t hit_orig(const EvDev &E, int32_t h)
 {

@@ -97,7 +97,7 @@ template <int TYPE>
 __global__ __launch_bounds__(BLOCK) void k_pack_count(EvDev E, PackArgs A)
 {
     __shared__ uint32_t s_pre[NSH + 1], s_n;
-    if (upstream_overflow(E)) return;
+    if (objects_unusable(E)) return;
     if (threadIdx.x == 0) s_n = 0;
     const uint32_t n = obj_prefix(E, TYPE, s_pre);
     uint32_t first, last, mine = 0;
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(BLOCK) void k_pack_rows(EvDev E, PackArgs A)
     __shared__ uint32_t s_pre[NSH + 1], s_w[WAVES];
     __shared__ int32_t s_idx[BLOCK];
     if (blockIdx.x == 0) put_header(E, A.hdr);
-    if (upstream_overflow(E)) {
+    if (objects_unusable(E)) {
         if (blockIdx.x == 0 && threadIdx.x == 0) A.hdr->rows = 0;
         return;
     }
@@ -309,7 +309,7 @@ __device__ __forceinline__ uint64_t px_key(const EvDev &E, const PackArgs &A, co
 __global__ __launch_bounds__(BLOCK) void k_px_count(EvDev E, PackArgs A)
 {
     __shared__ uint32_t s_pre[NSH + 1], s_n;
-    if (upstream_overflow(E)) return;
+    if (objects_unusable(E)) return;
     if (threadIdx.x == 0) s_n = 0;
     const PxList L = px_list(E, A, s_pre);
     __syncthreads();
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(BLOCK) void k_px_count(EvDev E, PackArgs A)
 __global__ __launch_bounds__(BLOCK) void k_px_keys(EvDev E, PackArgs A)
 {
     __shared__ uint32_t s_pre[NSH + 1], s_w[WAVES];
-    if (upstream_overflow(E)) return;
+    if (objects_unusable(E)) return;
     const PxList L = px_list(E, A, s_pre);
     uint32_t mine = 0, before;
     for (uint32_t b = threadIdx.x; b < blockIdx.x; b += BLOCK) mine += E.rd_cnt[b];
@@ -377,7 +377,7 @@ constexpr int PX_RANK = 4, PX_KEYS = 8;
 __global__ __launch_bounds__(BLOCK) void k_px_rows(EvDev E, PackArgs A)
 {
     if (blockIdx.x == 0) put_header(E, A.hdr);
-    const uint32_t n = upstream_overflow(E) ? 0u : E.rd_cnt[PACK_BLOCKS];
+    const uint32_t n = objects_unusable(E) ? 0u : E.rd_cnt[PACK_BLOCKS];
     if (blockIdx.x == 0 && threadIdx.x == 0) A.hdr->rows = n;
     if (n > A.cap_rows) return;   // the buffer grows and the rows are packed again
     const uint32_t l = (uint32_t)rd_lane(), width = (uint32_t)A.width;
@@ -506,6 +506,7 @@ __device__ __forceinline__ void obj_counts(const EvDev &E, int n_mod, int n_ev, 
 {
     __shared__ uint32_t s_pre[NSH + 1];
     __shared__ unsigned long long s_tab[RC_EVENTS][RC_OBJ];
+    const uint32_t n_md = E.rc[OT_MD] * NSH;   // mini-doublets: after a fault an index may be any
     const int n_row = min(n_ev - ev0, RC_EVENTS);
     for (int i = threadIdx.x; i < n_row * RC_OBJ; i += BLOCK) s_tab[i / RC_OBJ][i % RC_OBJ] = 0;
     const uint32_t n = obj_prefix(E, TYPE, s_pre);   // (its barrier also covers the table)
@@ -522,16 +523,27 @@ __device__ __forceinline__ void obj_counts(const EvDev &E, int n_mod, int n_ev, 
     };
     for (uint32_t v = b * BLOCK + threadIdx.x; v < n; v += blocks * BLOCK) {
         const int32_t t = obj_at(E, TYPE, s_pre, v);
-        const int ev = (n_ev == 1 ? 0 : E.md_slot[first_md<TYPE>(E, t)] / n_mod) - ev0;
+        int ev = 0;
+        if (n_ev > 1) {
+            const int32_t md = first_md<TYPE>(E, t);
+            if ((uint32_t)md >= n_md) continue;
+            ev = E.md_slot[md] / n_mod - ev0;
+        }
         if (ev < 0 || ev >= n_row) continue;
         if (ev != run) {
             flush();
             run = ev;
         }
         ++cnt;
-        if constexpr (TYPE == OT_SEG) s1 += (uint64_t)E.seg_cnt[E.seg_out[t]];
+        if constexpr (TYPE == OT_SEG) {
+            const int32_t md = E.seg_out[t];
+            if ((uint32_t)md < n_md) s1 += (uint64_t)E.seg_cnt[md];
+        }
         if constexpr (TYPE == OT_T3)
-            if (stage >= 5) s1 += (uint64_t)E.t3_cnt[E.t3_c[t]];
+            if (stage >= 5) {
+                const int32_t md = E.t3_c[t];
+                if ((uint32_t)md < n_md) s1 += (uint64_t)E.t3_cnt[md];
+            }
         if constexpr (TYPE == OT_T5) {
             if (stage >= 7) s1 += E.t5_keep[t];
             if (stage >= 8) s2 += E.t5_clean[t];
