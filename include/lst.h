@@ -427,11 +427,14 @@ int lst_get_t3_logits(lst_ctx *ctx, int32_t event, float *logits_host, uint8_t *
  * standardised, 40..63 zero), y [n] labels (0/1).  The loss is the mean
  * binary cross entropy on the logits; gradients flow through the BF16
  * roundings unchanged.  Every sum runs in a fixed order, so results are
- * bit-for-bit reproducible. */
+ * bit-for-bit reproducible for a given n and workspace. */
 
-/* device workspace lst_mlp_backward needs for n rows: 4 (n + 128 x
- * LST_MLP_NPARAM) bytes (per-row losses, partial gradients of up to 128 row
- * chunks) */
+/* device workspace of lst_mlp_backward for n rows: per-row losses and the
+ * partial gradients of the row chunks, 4 (n + 64 x LST_MLP_NPARAM) bytes up to
+ * 4096 rows, 4 (n + 128 x LST_MLP_NPARAM) above.  The calls accept 4 (n + 64 x
+ * LST_MLP_NPARAM) bytes for any n; more than 4096 rows then run in at most 64
+ * chunks instead of 128, which is slower and adds up the gradient in the order
+ * of that split. */
 size_t lst_mlp_workspace_bytes(int64_t n);
 
 /* x = BF16((feat - mean) * istd), zero padded to 64 columns; feat [n][40] FP32 */
@@ -445,8 +448,9 @@ int lst_mlp_forward(lst_ctx *ctx, const float *params, const uint16_t *x, int64_
                     uint16_t *h1, float *h2, void *stream);
 
 /* grad [LST_MLP_NPARAM] = dL/dparams and *loss (device) for the batch whose
- * forward saved logits, h1, h2.  work: device scratch of work_bytes >=
- * lst_mlp_workspace_bytes(n) (else LST_E_CAPACITY). */
+ * forward saved logits, h1, h2.  work: device scratch of work_bytes,
+ * lst_mlp_workspace_bytes(n) or the least given there (below it
+ * LST_E_CAPACITY). */
 int lst_mlp_backward(lst_ctx *ctx, const float *params, const uint16_t *x, const uint8_t *y,
                      int64_t n, const float *logits, const uint16_t *h1, const float *h2,
                      void *work, size_t work_bytes, float *grad, float *loss, void *stream);
@@ -457,7 +461,8 @@ int lst_mlp_backward(lst_ctx *ctx, const float *params, const uint16_t *x, const
  * fixed device array inside the library, one per GPU, 3.5 MB, held from the
  * first lst_create on that GPU until the process ends; n at most 8192 rows
  * (else LST_E_CAPACITY, nothing launched).  The call allocates nothing and
- * gives the same results as lst_mlp_backward.  Every call on one GPU shares
+ * gives the same results as lst_mlp_backward with a workspace of
+ * lst_mlp_workspace_bytes(n).  Every call on one GPU shares
  * that array: calls that overlap on one GPU (different streams, threads or
  * contexts) race and must be ordered by the caller. */
 int lst_mlp_backward_noalloc(lst_ctx *ctx, const float *params, const uint16_t *x,
@@ -479,8 +484,9 @@ int lst_mlp_adam(lst_ctx *ctx, float *params, const float *grad, float *m, float
  * host array of n_steps batch indices, each in 0 .. n_rows / batch - 1
  * (checked before anything is launched, else LST_E_INVALID).  logits, h1
  * and h2 are not used (kept for the signature; may be NULL).  Device
- * buffers: work (work_bytes >= lst_mlp_workspace_bytes(batch), else
- * LST_E_CAPACITY), grad, m, v [LST_MLP_NPARAM], losses [n_rows / batch].
+ * buffers: work (work_bytes as for lst_mlp_backward on a batch, and the same
+ * results for the same work_bytes), grad, m, v [LST_MLP_NPARAM], losses
+ * [n_rows / batch].
  * Hyper-parameters as for lst_mlp_adam. */
 int lst_mlp_train_steps(lst_ctx *ctx, float *params, const uint16_t *x, const uint8_t *y,
                         int64_t n_rows, int64_t batch, const int32_t *order, int32_t n_steps,

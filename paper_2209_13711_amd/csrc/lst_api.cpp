@@ -1056,10 +1056,10 @@ int lst_mlp_backward(lst_ctx *c, const float *params, const uint16_t *x, const u
     int rc = mlp_args(c, n, {params, x, y, logits, h1, h2, work, grad, loss});
     if (rc) return rc;
     if (n == 0) return fail(c, LST_E_INVALID, "empty batch");
-    if (work_bytes < mlp_workspace_bytes(n))
+    if (work_bytes < mlp_workspace_least(n))
         return fail(c, LST_E_CAPACITY, "workspace %zu bytes, %zu needed", work_bytes,
-                    mlp_workspace_bytes(n));
-    HIPCHK(c, mlp_backward(params, x, y, n, logits, h1, h2, (float *)work, grad, loss,
+                    mlp_workspace_least(n));
+    HIPCHK(c, mlp_backward(params, x, y, n, logits, h1, h2, (float *)work, work_bytes, grad, loss,
                            (hipStream_t)stream));
     return LST_OK;
 }
@@ -1076,8 +1076,8 @@ int lst_mlp_backward_noalloc(lst_ctx *c, const float *params, const uint16_t *x,
                     (long long)n, (long long)MLP_FIXED_MAX_ROWS);
     // every workspace word the kernels read is written by them first in the
     // same call: nothing to clear
-    HIPCHK(c, mlp_backward(params, x, y, n, logits, h1, h2, (float *)c->fixed_work, grad, loss,
-                           (hipStream_t)stream));
+    HIPCHK(c, mlp_backward(params, x, y, n, logits, h1, h2, (float *)c->fixed_work,
+                           sizeof(float) * MLP_FIXED_SCRATCH_FLOATS, grad, loss, (hipStream_t)stream));
     return LST_OK;
 }
 
@@ -1112,9 +1112,9 @@ int lst_mlp_train_steps(lst_ctx *c, float *params, const uint16_t *x, const uint
     if (!(lr > 0.0f) || !(beta1 >= 0.0f && beta1 < 1.0f) || !(beta2 >= 0.0f && beta2 < 1.0f) ||
         !(eps > 0.0f))
         return fail(c, LST_E_INVALID, "Adam hyper-parameters");
-    if (work_bytes < mlp_workspace_bytes(batch))
+    if (work_bytes < mlp_workspace_least(batch))
         return fail(c, LST_E_CAPACITY, "workspace %zu bytes, %zu needed", work_bytes,
-                    mlp_workspace_bytes(batch));
+                    mlp_workspace_least(batch));
     const int64_t n_batches = n_rows / batch;
     for (int32_t i = 0; i < n_steps; ++i)
         if (order[i] < 0 || order[i] >= n_batches)
@@ -1130,8 +1130,8 @@ int lst_mlp_train_steps(lst_ctx *c, float *params, const uint16_t *x, const uint
         const float c1 = (float)(1.0 - std::pow((double)beta1, step));
         const float c2 = (float)(1.0 - std::pow((double)beta2, step));
         // forward, backward and Adam in two launches with the same arithmetic
-        HIPCHK(c, mlp_train_step(params, xb, yb, batch, (float *)work, grad, losses + order[i], m,
-                                 v, lr, beta1, beta2, eps, c1, c2, s));
+        HIPCHK(c, mlp_train_step(params, xb, yb, batch, (float *)work, work_bytes, grad, losses + order[i],
+                                 m, v, lr, beta1, beta2, eps, c1, c2, s));
     }
     return LST_OK;
 }

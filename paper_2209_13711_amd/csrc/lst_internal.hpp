@@ -294,20 +294,22 @@ hipError_t launch_t3_features(const EvDev &E, const Consts &K, int grid, hipStre
 constexpr int MLP_NIN = 40, MLP_NH = 64;
 constexpr int MLP_NPARAM = MLP_NH * MLP_NIN + MLP_NH + MLP_NH * MLP_NH + MLP_NH + MLP_NH + 1;
 size_t mlp_workspace_bytes(int64_t n);
+size_t mlp_workspace_least(int64_t n);   // what a backward pass on n rows accepts
 hipError_t mlp_prepare(const float *F, const float *mean, const float *istd, int64_t n, uint16_t *X,
                        hipStream_t s);
 hipError_t mlp_forward(const float *P, const uint16_t *X, int64_t n, float *logits, uint16_t *h1,
                        float *h2, hipStream_t s);
 hipError_t mlp_backward(const float *P, const uint16_t *X, const uint8_t *y, int64_t n,
                         const float *logits, const uint16_t *h1, const float *h2, float *work,
-                        float *grad, float *loss, hipStream_t s);
+                        size_t work_bytes, float *grad, float *loss, hipStream_t s);
 hipError_t mlp_adam(float *P, const float *grad, float *m, float *v, float lr, float b1, float b2,
                     float eps, float c1, float c2, hipStream_t s);
 hipError_t mlp_train_step(float *P, const uint16_t *X, const uint8_t *y, int64_t n, float *work,
-                          float *grad, float *loss, float *m, float *v, float lr, float b1, float b2,
-                          float eps, float c1, float c2, hipStream_t s);
-// row chunks of the gradient sums at most: one 64-row batch each up to 8192 rows
-constexpr int MLP_GRAD_CHUNKS = 128;
+                          size_t work_bytes, float *grad, float *loss, float *m, float *v, float lr,
+                          float b1, float b2, float eps, float c1, float c2, hipStream_t s);
+// row chunks of the gradient sums at most: one 64-row batch each up to 8192
+// rows; in a workspace that holds no more than MLP_GRAD_CHUNKS_FEW, up to 4096
+constexpr int MLP_GRAD_CHUNKS = 128, MLP_GRAD_CHUNKS_FEW = 64;
 // fixed backward workspace (no allocation): rows it holds, its size in floats
 // (n loss rows + the chunks x MLP_NPARAM at n = MLP_FIXED_MAX_ROWS), and its
 // device address on `device` (looked up once per device, then cached)
