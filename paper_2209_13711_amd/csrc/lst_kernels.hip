@@ -1750,14 +1750,14 @@ hipError_t launch_t5(const EvDev &E, const ModDev &M, const Consts &K, int grid,
 // by the hit tuple.  A quintuplet vetoed by the learned scorer takes no part.
 //
 // First pass: a 64-bit minimum per hit of (score, quintuplet index), whose
-// returned old value shows a tie with the minimum of the moment.  Whoever
-// sees one records itself in the hit's tie list, and the quintuplet it
-// displaces, if it does: so the list and the final minimum's index together
-// hold every quintuplet of the hit that reaches the final minimum.  (The first
-// to reach it recorded itself only if something tied with it was there, and is
-// the minimum's index until displaced.)  The list may also hold quintuplets
-// tied at an earlier, larger minimum, and some twice; the second pass looks at
-// the scores.  TIE_SLOTS entries are in the hit's own slots, further ones in a
+// returned old value shows a tie with the minimum of the moment.  Of the two,
+// the one that is not the minimum's index afterwards goes into the hit's tie
+// list: the newcomer, or the one it displaces.  So the list and the final
+// minimum's index together hold every quintuplet of the hit that reaches the
+// final minimum, one record per tie.  (With the newcomer recorded also where
+// it displaces the other, dense events spilled into the pool: 27 entries on a
+// stress event, none now.)  The list may also hold quintuplets tied at an
+// earlier, larger minimum; the second pass looks at the scores.  TIE_SLOTS entries are in the hit's own slots, further ones in a
 // pool.  One pass instead of two (minima, then ties against the final minima);
 // PU200-like event, all of duplicate removal, 7.2 + 5.1 + 5.2 -> 7.7 + 5.8 us;
 // 16 of them 36.5 + 19.8 + 24.5 -> 40.4 + 25.5 us.
@@ -1793,10 +1793,8 @@ __device__ __forceinline__ void dedup_min_body(const EvDev &E, uint32_t *s_pre)
         if (!veto) old = atomicMin(&E.hmin[h], key);
         E.t5_hs[(size_t)t * 10 + j] = h;
         E.t5_ho[(size_t)t * 10 + j] = hit_orig(E, h);
-        if (!veto && (uint32_t)(old >> 32) == sc && old != ~0ull) {
-            tie_record(E, h, t);
-            if (key < old) tie_record(E, h, (int32_t)(uint32_t)old);
-        }
+        if (!veto && (uint32_t)(old >> 32) == sc && old != ~0ull)
+            tie_record(E, h, key < old ? (int32_t)(uint32_t)old : t);
     }
 }
 
