@@ -158,10 +158,31 @@ __device__ __forceinline__ uint2 relu4(const f32x4 &a, const float4 &b)
     return make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
 }
 
+// The last layer's sum over the hidden units 16 nt + 4 q + r: a lane adds its
+// tiles nt in order for each r (t[r]), then come the 16 sums (q, r) by halves,
+// q ^ 2, q ^ 1, r ^ 2, r ^ 1; every lane of a candidate returns it.  Against 64
+// bits the layer is 7.7e-8 off like this (of the logits' norm, 1000 to 20,000
+// rows), 9.0e-8 to 9.6e-8 with a lane's 16 terms one after the other.  A lane
+// sends the sums that its partner keeps, so five values cross the wave and not
+// eight; 200,003 rows take 23.1 us with the preparation, 22.7 in the shorter
+// order.
+__device__ __forceinline__ float logit_sum(const float t[4])
+{
+    const int l = threadIdx.x & 63;
+    const bool hi = l & 32, odd = l & 16;
+    float a = hi ? t[2] : t[0], b = hi ? t[3] : t[1];   // r = 0 or 2, 1 or 3
+    a += __shfl_xor(hi ? t[0] : t[2], 32, 64);
+    b += __shfl_xor(hi ? t[1] : t[3], 32, 64);
+    float v = odd ? b : a;
+    v += __shfl_xor(odd ? a : b, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    v += __shfl_xor(v, 16, 64);
+    return v;
+}
+
 // Forward of 16 candidates: x[ks] = inputs 32 ks + 8 q .. +7 of candidate l%16.
 // Every lane returns the logit of its candidate.  save(nt, h1, h2), when
 // given, receives the lane's units 16 nt + 4 q .. +3 of both hidden layers.
-// The logit adds a lane's 16 terms in order, then the four quarters'.
 template <class F>
 __device__ __forceinline__ float mlp_tile(const MlpW &w, const MlpOps &o, const bf16x8 x[KP / 32], F &&save)
 {
@@ -182,7 +203,7 @@ __device__ __forceinline__ float mlp_tile(const MlpW &w, const MlpOps &o, const 
 #pragma unroll
     for (int ks = 0; ks < KP / 32; ++ks)
         hk[ks] = __builtin_bit_cast(bf16x8, make_uint4(h[2 * ks].x, h[2 * ks].y, h[2 * ks + 1].x, h[2 * ks + 1].y));
-    float v = 0.0f;
+    float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};   // terms of the logit
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt) {
         acc[nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -200,13 +221,11 @@ __device__ __forceinline__ float mlp_tile(const MlpW &w, const MlpOps &o, const 
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             h2[r] = z[r] > 0.0f ? z[r] : 0.0f;
-            v += h2[r] * w3[r];
+            t[r] += h2[r] * w3[r];
         }
         save(nt, h[nt], make_float4(h2[0], h2[1], h2[2], h2[3]));
     }
-    v += __shfl_xor(v, 16, 64);
-    v += __shfl_xor(v, 32, 64);
-    return v + w.b3;
+    return logit_sum(t) + w.b3;
 }
 
 // ---------------------------------------------------------------- training forward
@@ -468,7 +487,7 @@ __global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t 
         float z = 0.0f;
         if (FWD) {
             // mlp_tile's products, each wave its half of the units; the lower
-            // half then adds both halves' terms of the logits in its order
+            // half then adds both halves' terms of the logits in mlp_tile's order
             f32x4 a[HT];
 #pragma unroll
             for (int i = 0; i < HT; ++i) {
@@ -506,21 +525,20 @@ __global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t 
             }
             __syncthreads();              // the upper half's terms
             if (!half) {
+                float t[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int i = 0; i < HT; ++i)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) z += p[i][r];
+                    for (int r = 0; r < 4; ++r) t[r] += p[i][r];
 #pragma unroll
                 for (int i = 0; i < HT; ++i) {
                     const float4 v = sp[rg][i][l];
-                    z += v.x;
-                    z += v.y;
-                    z += v.z;
-                    z += v.w;
+                    t[0] += v.x;
+                    t[1] += v.y;
+                    t[2] += v.z;
+                    t[3] += v.w;
                 }
-                z += __shfl_xor(z, 16, 64);
-                z += __shfl_xor(z, 32, 64);
-                z += sm.w.b3;
+                z = logit_sum(t) + sm.w.b3;
             }
         }
         // row terms: the first quarter of the lower half takes the group's rows
