@@ -338,7 +338,7 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_prepare8(const float *F, const fl
 // l supplies A[l%16][l/16] and B[l/16][l%16], receives D rows 4 (l/16) + r,
 // column l%16).  The vector sums are kept per lane over its rows and combined
 // in a fixed order at the end.  A block writes its chunk's partial gradient;
-// k_mlp_reduce adds the chunks in chunk order.  Every sum runs in an order
+// k_mlp_reduce adds the chunks in an order of its own.  Every sum runs in an order
 // fixed by n and the most chunks, so the gradient is bit-for-bit reproducible,
 // and the forward-fused and the stored-activation variants give the same bits.
 //
@@ -712,13 +712,15 @@ __global__ void k_mlp_adam(float *P, const float *grad, AdamArgs a)
 }
 
 // The end of a backward pass in one launch: grad[p] is the sum of the
-// chunks' partials in chunk order, followed (ADAM) by the Adam update of
-// parameter p with the same operations as k_mlp_adam; the block past the
-// parameters takes the mean loss (loss_body).  A block takes RD_P parameters:
-// its waves load a share of the chunks each, all in flight, into LDS, and one
-// wave adds them in order, its optimiser state loaded meanwhile.  Latency
-// bound (two loads deep): 4.1 us for 64 chunks, 4.6 us with one thread loading
-// all chunks of a parameter on 28 blocks and the optimiser state after the sum.
+// chunks' partials, followed (ADAM) by the Adam update of parameter p with the
+// same operations as k_mlp_adam; the block past the parameters takes the mean
+// loss (loss_body).  A block takes RD_P parameters: wave w loads chunks w,
+// w + 4, ..., all in flight, and adds them in that order; the first wave, its
+// optimiser state loaded meanwhile, adds the four sums by pairs.  Against 64
+// bits dW1 of 8192 rows is 6.3e-8 off like this, 1.69e-7 with the 128 chunks
+// one after the other, 1.22e-7 with 64 chunks of two batches.  Latency bound
+// (two loads deep): 3.9 us for 64 or 79 chunks, 4.6 us with one thread loading all
+// chunks of a parameter on 28 blocks and the optimiser state after the sum.
 constexpr int RD_P = 64;
 
 template <bool ADAM>
@@ -730,7 +732,7 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_reduce(const float *part, int nch
         loss_body(loss_rows, n, loss);
         return;
     }
-    __shared__ float s_v[GRAD_CHUNKS][RD_P];
+    __shared__ float s_v[WAVES][RD_P];
     constexpr int PER = GRAD_CHUNKS / WAVES;
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63, p = blockIdx.x * RD_P + l;
     const bool live = p < NPARAM;
@@ -746,13 +748,14 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_reduce(const float *part, int nch
         const int c = w + WAVES * u;
         t[u] = live && c < nch ? part[(int64_t)c * NPARAM + p] : 0.0f;
     }
+    float acc = 0.0f;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) s_v[w + WAVES * u][l] = t[u];
+    for (int u = 0; u < PER; ++u) acc += t[u];   // (past the chunks zeros, which change nothing)
+    s_v[w][l] = acc;
     __syncthreads();
     if (w > 0 || !live) return;
-    float acc = 0.0f;
-#pragma unroll 8
-    for (int c = 0; c < nch; ++c) acc += s_v[c][l];
+    static_assert(WAVES == 4, "four sums");
+    acc = (s_v[0][l] + s_v[1][l]) + (s_v[2][l] + s_v[3][l]);
     grad[p] = acc;
     if (ADAM) {
         adam_update(q, m, v, acc, a);

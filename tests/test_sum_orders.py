@@ -1,6 +1,7 @@
 """Orders in which the scorer's kernels add, on the CPU in FP32: none may be
 further off than the orders used before (16 lanes of four terms each for a
-logit), against sums in FP64."""
+logit, at most 64 chunks of rows one after the other for a gradient), against
+sums in FP64."""
 import numpy as np
 import pytest
 
@@ -33,6 +34,14 @@ def logit_sum_lanes(t):
     return a[:, 0]
 
 
+def chunk_sum(p):
+    """partial sums of up to 128 chunks [.., chunks]: every fourth in order, the
+    four sums by pairs"""
+    p = np.concatenate([p, np.zeros(p.shape[:-1] + (128 - p.shape[-1],), F)], -1)
+    w = [serial(np.concatenate([np.zeros(p.shape[:-1] + (1,), F), p[..., k::4]], -1)) for k in range(4)]
+    return (w[0] + w[1]) + (w[2] + w[3])
+
+
 def rms(got, terms):
     ref = terms.astype(np.float64).sum(-1)
     return float(np.sqrt(((got - ref) ** 2).mean() / (ref ** 2).mean()))
@@ -45,3 +54,14 @@ def test_logit_sum_is_no_further_off(seed):
     t = h2 * rng.normal(0, 0.125, 64).astype(F)
     assert logit_sum(t).dtype == F
     assert rms(logit_sum(t), t) <= rms(logit_sum_lanes(t), t)
+
+
+@pytest.mark.parametrize("rows", [64, 4096, 5056, 8192])
+def test_chunk_sum_is_no_further_off(rows):
+    """rows of random terms, 64 to a chunk, or twice as many where that would
+    be more than 64 chunks"""
+    t = np.random.default_rng(rows).normal(0.02, 1, (4000, rows)).astype(F)
+    batches = serial(t.reshape(4000, -1, 64))
+    per = 2 if rows > 4096 else 1
+    was = serial(np.stack([serial(t[:, k:k + 64 * per]) for k in range(0, rows, 64 * per)], -1))
+    assert rms(chunk_sum(batches), t) <= rms(was, t)
