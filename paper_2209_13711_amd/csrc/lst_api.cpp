@@ -1350,9 +1350,9 @@ struct ShardCounts {
     size_t span(int t) const { return (size_t)rc[t] * NSH; }
     uint32_t error() const
     {
-        uint32_t e = gc[GC_ERROR];
-        for (int i = 0; i < GROUP_PARTS; ++i) e |= gc[GC_GROUP + i];
-        return e;
+        uint32_t group = 0;
+        for (int i = 0; i < GC_GROUP_WORDS; ++i) group |= gc[GC_GROUP + i];
+        return gc[GC_ERROR] | (group ? 4u : 0u);
     }
     int64_t stored(int t) const
     {

@@ -42,13 +42,16 @@ enum GlobalCounter {
     GC_SH = GC_PAD     // [OT_COUNT][NSH] reservation shards, one line each
 };
 __host__ __device__ constexpr int gc_shard(int type, int s) { return GC_SH + (type * NSH + s) * GC_PAD; }
-// after the shards: a word for each range of modules of the one-launch grouping
-// (GROUP_PARTS), nonzero when its hits did not fit the positions it had counted
-// (part of the error flags).  Every block stores its own word, so the words
-// need no clearing before the launch.
+// after the shards: a byte for each wave of the one-launch grouping (GROUP_WAVES
+// for each of its GROUP_PARTS ranges of modules), nonzero when its hits did not
+// fit the positions it had counted (part of the error flags).  Every wave stores
+// its own byte, so the bytes need no clearing before the launch, and no wave
+// waits for another one's stores.
 constexpr int GROUP_PARTS = 256;      // one block per CU
+constexpr int GROUP_WAVES = 16;
 constexpr int GC_GROUP = GC_SH + OT_COUNT * NSH * GC_PAD;
-constexpr int GC_COUNT = GC_GROUP + GROUP_PARTS;
+constexpr int GC_GROUP_WORDS = GROUP_PARTS * GROUP_WAVES / 4;
+constexpr int GC_COUNT = GC_GROUP + GC_GROUP_WORDS;
 
 
 // MI355X dispatches workgroup i to XCD i % 8, and each XCD has its own L2.

@@ -563,8 +563,7 @@ __global__ __launch_bounds__(SORT_EV_BLOCK) void k_scatter_ev(EvDev E, ModDev M)
 // the three kernels above, which they keep.  Measured in the chain: 200
 // tracks 5.5 us for 4.0 + 5.8 + 3.7, PU200-like 15.7 us for 8.2 + 7.1 + 4.6
 // (128 ranges: 2.3 us more).
-constexpr int GROUP_BLOCK = 1024;
-constexpr int GROUP_WAVES = GROUP_BLOCK / 64;
+constexpr int GROUP_BLOCK = 64 * GROUP_WAVES;
 constexpr int GROUP_LIST = 256;       // hits of its range a wave lists in LDS; more are found by a second read
 constexpr int GROUP_ILP = 8;          // groups of four hits whose ids a thread loads together
 
@@ -725,8 +724,8 @@ __global__ __launch_bounds__(GROUP_BLOCK) void k_group(EvDev E, ModDev M)
             if ((uint32_t)m - m0 < n_m && s <= 1u) put(h, 2 * (m - (int)m0) + (int)s);
         });
     }
-    wrong = __syncthreads_or(wrong) != 0;
-    if (threadIdx.x == 0) E.gc[GC_GROUP + part] = wrong ? 4u : 0u;
+    const bool any = __ballot(wrong) != 0ull;
+    if (l == 0) reinterpret_cast<uint8_t *>(E.gc + GC_GROUP)[part * GROUP_WAVES + w] = any ? 4 : 0;
 }
 
 static size_t group_lds_bytes(int n_mod)

@@ -29,7 +29,11 @@ __device__ __forceinline__ int rd_lane() { return threadIdx.x & 63; }
 __device__ __forceinline__ void put_header(const EvDev &E, ReadHdr *h)
 {
     uint32_t group = 0;
-    for (int i = threadIdx.x; i < GROUP_PARTS; i += blockDim.x) group |= E.gc[GC_GROUP + i];
+    const uint4 *words = reinterpret_cast<const uint4 *>(E.gc + GC_GROUP);
+    for (int i = threadIdx.x; i < GC_GROUP_WORDS / 4; i += blockDim.x) {
+        const uint4 v = words[i];
+        group |= v.x | v.y | v.z | v.w;
+    }
     const bool fault = __syncthreads_or(group != 0u) != 0;
     for (int i = threadIdx.x; i < OT_COUNT * NSH; i += blockDim.x)
         h->shard[i / NSH][i % NSH] = E.gc[gc_shard(i / NSH, i % NSH)];

@@ -8,13 +8,13 @@ import pytest
 from synth import events as E
 from synth import geometry as G
 from synth import params as PR
-from tests.test_gpu_group_fault import GROUP, counters
+from tests.test_gpu_group_fault import GROUP, GROUP_BYTES, counters
 
 pytestmark = pytest.mark.gpu
 
 
 def _overwrite(ctx):
-    ctx.arena[counters(ctx) + 4 * (GROUP + 256):] = 0x7f
+    ctx.arena[counters(ctx) + 4 * GROUP + GROUP_BYTES:] = 0x7f
 
 
 def _all_refuse(lst, calls):
