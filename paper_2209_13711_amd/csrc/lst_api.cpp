@@ -545,7 +545,10 @@ static int clamp_grid(int64_t g) { return (int)std::max<int64_t>(1, std::min<int
 // ones 827 -> 704, three stress events 664 -> 489 (triplets 221 -> 98), ten
 // small uneven ones 119 -> 101, two of 100 tracks 59 -> 56.  Groups of 8 lanes
 // gain more on some (segments of the uneven batch) and lose on others
-// (mini-doublets there: 193 us more).
+// (mini-doublets there: 193 us more).  The line lies at the arena, on which a
+// captured graph depends; one event in an arena of 2, 7 or 16 is within 1 us
+// either way (200 tracks 56.8 us, 56.4 in the one-event shape; PU200-like 81.3
+// and 82.3).
 static void default_tuning(lst_ctx *c)
 {
     Tuning &t = c->tune;

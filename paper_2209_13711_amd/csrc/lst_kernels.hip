@@ -553,16 +553,16 @@ __global__ __launch_bounds__(SORT_EV_BLOCK) void k_scatter_ev(EvDev E, ModDev M)
 // knows its first position without waiting for any other block; then it scans
 // its bins and stores its hits.  Reading the ids once per range (275 KB per
 // block on a PU200-like event, from the L2s) costs less than the two
-// dependent launches it saves.  What bounds it is VALU issue (every block
-// looks at every hit) and the latency of four phases, so a hit takes four
-// instructions unless it is in the range: ids out of range are rare, and only
-// their presence is noted (largest module id, bits of the sensor ids); a block
-// that saw any counts again, leaving them out.
+// dependent launches it saves.  What bounds it is the latency of its phases and
+// VALU issue (38 % of the cycles, 3.6 waves per SIMD: every block looks at every
+// hit), so a hit takes four instructions unless it is in the range: ids out of
+// range are rare, and only their presence is noted (largest module id, bits of
+// the sensor ids); a block that saw any counts again, leaving them out.
 // Several events would read ids of events that are not theirs to know how
 // many valid hits precede them: three stress events took 57 us, 46 us with
-// the three kernels above, which they keep.  Measured in the chain: 200
-// tracks 5.5 us for 4.0 + 5.8 + 3.7, PU200-like 15.7 us for 8.2 + 7.1 + 4.6
-// (128 ranges: 2.3 us more).
+// the three kernels above, which they keep.  Measured in the chain with new
+// hits each call: 200 tracks 7.2 us for 4.0 + 5.8 + 3.7, PU200-like 17.0 us for
+// 8.2 + 7.1 + 4.6 (128 ranges: 2.3 us more); 14.5 with its hits in the caches.
 constexpr int GROUP_BLOCK = 64 * GROUP_WAVES;
 constexpr int GROUP_LIST = 256;       // hits of its range a wave lists in LDS; more are found by a second read
 constexpr int GROUP_ILP = 8;          // groups of four hits whose ids a thread loads together
@@ -892,10 +892,11 @@ __device__ __forceinline__ ModF mod_from(const ModL &r)
 // time, so a slot with many hits is shared by all lanes of the wave.  The list
 // is in slot order, so each slot's accepted pairs are consecutive in the
 // wave's output, in lower-major pair order.  Against the whole window per
-// pair: 16 PU200 events 72 -> 70 us, 16 uneven ones 185 -> 144, the stress
+// pair: 16 PU200 events 72 -> 70 us, 24 uneven ones 185 -> 145, the stress
 // configuration in binary16 storage 89 -> 59; one PU200 event (few hits per
-// slot: bound by the chain of loads) 12.6 -> 13.7, within the runs' spread at
-// the chain's end (81.2 -> 81.8).
+// slot: bound by the chain of loads) is slower in the default shape, 12.6 ->
+// 13.4 (the whole chain 81.2 -> 81.8 when it came), and takes 11.5 in the 16-lane
+// groups the tuner picks.
 // The staging without the lower hit's step (write_md computes it again) leaves
 // LDS for six blocks per CU instead of four; half the staging would be a
 // little faster on one event (12.8) and sends the dense modules of the uneven
@@ -1758,8 +1759,8 @@ hipError_t launch_t5(const EvDev &E, const ModDev &M, const Consts &K, int grid,
 // stress event, none now.)  The list may also hold quintuplets tied at an
 // earlier, larger minimum; the second pass looks at the scores.  TIE_SLOTS entries are in the hit's own slots, further ones in a
 // pool.  One pass instead of two (minima, then ties against the final minima);
-// PU200-like event, all of duplicate removal, 7.2 + 5.1 + 5.2 -> 7.7 + 5.8 us;
-// 16 of them 36.5 + 19.8 + 24.5 -> 40.4 + 25.5 us.
+// PU200-like event, all of duplicate removal, 7.2 + 5.1 + 5.2 -> 6.9 + 5.5 us;
+// 16 of them 36.5 + 19.8 + 24.5 -> 37.7 + 20.5 us.
 //
 // one thread per (quintuplet, hit); the hit indices are cached per
 // quintuplet ([t][10], sorted and per-event) for the later pass

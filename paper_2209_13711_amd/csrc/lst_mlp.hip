@@ -232,10 +232,10 @@ __device__ __forceinline__ float mlp_tile(const MlpW &w, const MlpOps &o, const 
 // X: [n][KP] BF16 rows (features standardised, zero padded).  A wave takes
 // tiles of 16 rows, its operands straight from memory (a row is 128 bytes) and
 // the next tile's on their way; few blocks, so that staging the weights (27 KB
-// a block) is spread over many tiles.  200,003 rows 13.7 us (25.6 MB read, 5 us
-// at the copy rate; the rest is staging and six tiles' latency per wave), 25.2
+// a block) is spread over many tiles.  200,003 rows 12.5-13.7 us (25.6 MB read, 5
+// us at the copy rate; the rest is staging and six tiles' latency per wave), 25.2
 // us with inputs and hidden layer through LDS and weights staged by 2048
-// blocks; 5000 rows with the hidden layers saved 6.1 us, 7.4 before.
+// blocks; 5000 rows with the hidden layers saved 6.2 us, 7.4 before.
 constexpr int FWD_BLOCKS = 512;   // two per CU: what its registers allow
 
 template <bool SAVE>
@@ -346,8 +346,8 @@ __global__ __launch_bounds__(BLOCK) void k_mlp_prepare8(const float *F, const fl
 // loads, small products and barriers.  So eight waves rather than four (two
 // per SIMD: the products' and the tiles' chains halve), the batch's rows and
 // labels are loaded before the weights, and a row's sigmoid and loss are
-// computed once, by one lane.  4096 rows 17.7 -> 13.1 us, 5000 rows (79 blocks
-// of one batch instead of 40 of two) 29.0 -> 12.7 us.  Of the 13 us, weights
+// computed once, by one lane.  4096 rows 17.7 -> 13.3 us, 5000 rows (79 blocks
+// of one batch instead of 40 of two) 29.0 -> 12.4 us.  Of the 13 us, weights
 // and rows to LDS take 2.7, the forward 2, the row terms 0.9, dz1 1.5, the
 // tiles 2.8 (their products alone 1.5), the partial sums 1.4.  Step-ordered
 // copies of the operands for 16-byte LDS reads made the tiles slower (5.8 us:
@@ -661,7 +661,7 @@ __global__ __launch_bounds__(GB) void k_mlp_grad(const float *P, const uint16_t 
 // GP_U rows per thread are loaded before they are added
 constexpr int GP_U = 16;
 
-// mean of the per-row losses: one block, fixed-order partials and tree
+
 __device__ __forceinline__ void loss_body(const float *loss_rows, int64_t n, float *loss)
 {
     __shared__ float part[BLOCK];
